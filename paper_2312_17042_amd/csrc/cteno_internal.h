@@ -62,14 +62,86 @@ __host__ __device__ inline size_t avix(int64_t i, int e, int E, int VW) {
 inline int64_t pad64(int64_t n) { return (n + kTile - 1) / kTile * kTile; }
 inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 
-// pseudo-inverse stream of one cell, consumed slot by slot: for slot j the K
-// central entries P_c[k][j], then (j < 12) the two directional entries
-// P_d[j/4][c][j%4]
+// Entries of a cell's pseudo-inverse stream, slot by slot.  r <= 3: for slot j
+// the K central entries P_c[k][j], then (j < 12) the two directional entries
+// P_d[j/4][c][j%4]; pinv_offset is slot j's first entry in that order (the
+// order of the stream in memory is quad_index's).
 __host__ __device__ constexpr int pinv_offset(int j, int K) {
     return j <= 12 ? j * (K + 2) : 12 * (K + 2) + (j - 12) * K;
 }
 inline int pinv_entries(int r) {
     return r <= 3 ? pinv_offset(dims_S(r), dims_K(r)) : dims_S(r) * ho_slot_entries(r);
+}
+// r <= 3: the stream feeds 4 x 4 matrix instructions, four coefficients (rows)
+// by the variables (columns).  The K + 2 coefficients of a slot form MA full row
+// groups of central ones (0..3, and 4..7 at degree 3) and one last group: the
+// last central coefficient (row 0) and the two directional ones of slots 0..11
+// (rows 1 and 2).
+template <int R>
+struct QuadDims {
+    static constexpr int K = (R + 1) * (R + 2) / 2 - 1;
+    static constexpr int M = 2 * K;
+    static constexpr int S = M > 12 ? M : 12;
+    static constexpr int SP = (S + 3) / 4 * 4;
+    static constexpr int MA = R == 3 ? 2 : 1;
+    static constexpr int G = (S + 3) / 4;          // groups of four slots
+    static constexpr int SK = (G + 1) / 2 * 2;     // row numbers per cell and slot % 4
+    static constexpr int E = pinv_offset(S, K);
+    static_assert(K == 4 * MA + 1, "row groups of degree 2 and 3");
+};
+// Scalar index of coefficient e (0..K-1 central, K, K + 1 directional) of slot j
+// of cell i, in tiles of 16 cells (one wave).
+//   FP32 (VW 4): an instruction takes one slot of 16 cells, lane 4 c + o row o
+//   of cell c.  A lane's entries in slot order, in vectors of four (rows of 64
+//   lanes): the full groups; then the last group's of slots 0..11 for rows 0..2;
+//   then its row 0 of slots 12..15 (a vector) and 16, 17 (a pair).
+//   FP64 (VW 2): an instruction takes four slots of four cells, lane 16 k + 4 b
+//   + o slot 4 g + k, row o of cell 4 s + b.  Per s: the full groups in pairs
+//   (degree 3: both groups of a g; degree 2: g = 0, 1, then g = 2 alone; the
+//   last g of degree 3 has k < 2 only); the last group's g = 0, 1 in pairs and
+//   g = 2 alone for rows 0..2, then row 0 of g = 3 and (k < 2) g = 4.
+template <int R>
+__host__ __device__ inline size_t quad_index(int64_t i, int j, int e, int VW) {
+    using D = QuadDims<R>;
+    constexpr int MA = D::MA, NA = D::S * MA;
+    const int c16 = (int)(i & 15);
+    const size_t base = (size_t)(i >> 4) * (D::E * 16);
+    const int m = e / 4, o = e % 4;                 // last group: m = MA, o = 0..2
+    if (VW == 4) {
+        if (m < MA) {
+            const int p = j * MA + m;
+            return base + (size_t)((p / 4 * 16 + c16) * 4 + o) * 4 + p % 4;
+        }
+        const size_t b = base + NA * 64;
+        if (j < 12) return b + (size_t)((j / 4 * 16 + c16) * 3 + o) * 4 + j % 4;
+        if (j < 16) return b + 576 + c16 * 4 + (j - 12);
+        return b + 640 + c16 * 2 + (j - 16);
+    }
+    const int k = j & 3, g = j >> 2, kb = 4 * k + (c16 & 3), lane = 4 * kb + o;
+    const size_t sb = base + (size_t)(c16 >> 2) * (D::E * 4);
+    if (m < MA) {
+        if (R == 3) return sb + (size_t)g * 128 + lane * 2 + m;
+        return g < 2 ? sb + lane * 2 + g : sb + 128 + lane;
+    }
+    const size_t b = sb + (R == 3 ? 576 : 192);
+    if (g < 2) return b + (kb * 3 + o) * 2 + g;
+    if (g == 2) return b + 96 + kb * 3 + o;
+    return b + 144 + (g - 3) * 16 + kb;
+}
+// index of slot j's entry in a mesh's row-number table: per cell the slots 0, 4,
+// 8, ..., then 1, 5, 9, ... (padded to SK each)
+template <int R>
+__host__ __device__ inline size_t lslot_index(int64_t i, int j) {
+    constexpr int SK = QuadDims<R>::SK;
+    return (size_t)i * (4 * SK) + (j & 3) * SK + (j >> 2);
+}
+inline int row_entries(int r) { return 4 * (r == 2 ? QuadDims<2>::SK : QuadDims<3>::SK); }
+// entry e in pinv_offset's order
+template <int R>
+__host__ __device__ inline size_t quad_index_entry(int64_t i, int e, int VW) {
+    constexpr int K = QuadDims<R>::K;
+    const int j = e < 12 * (K + 2) ? e / (K + 2) : 12 + (e - 12 * (K + 2)) / K;
+    return quad_index<R>(i, j, e - pinv_offset(j, K), VW);
 }
 // r >= 4: vector-tiled stream with tiles of CT cells (CT = 64 / nv: one lane
 // per cell and variable), VW = 4 (FP32) or 2 (FP64) entries per vector
@@ -85,6 +157,13 @@ constexpr uint32_t kNbOwner = 0x40000000u;
 constexpr uint32_t kNbIndexMask = 0x0FFFFFFFu;
 // boundary faces: kind in bits 0-1; an inflow face's row in the inflow table in bits 2-29
 constexpr uint32_t kNbInflowMask = 0x0FFFFFFFu;
+// listed faces of a fused-stage block (64 cells): bits 0..5 the evaluating cell
+// in the block, 6..7 its local face; bits 8..13 the other cell and 14..15 its
+// local face, or bit 31 and the boundary kind in bits 8..9
+constexpr uint32_t kBfBoundary = 0x80000000u;
+// side records: the other side's number in bits 0..27, kNbOwner, and whether the
+// other cell lies in another 256-cell block
+constexpr uint32_t kSideFar = 0x80000000u;
 // slot entries at degree >= 4: bits 0..27 the cell (internal index), bits
 // 28..29 the directional stencil (face 0..2) that holds it, 3 for none
 constexpr uint32_t kSlotIndexMask = 0x0FFFFFFFu;

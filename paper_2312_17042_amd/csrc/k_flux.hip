@@ -1,6 +1,6 @@
 // Flux / residual / RK stage kernels, step control, the batched serving
 // kernels, layout conversions and utilities; the reconstruction dispatch.
-#include "kernels_common.h"
+#include "recon_quad.h"
 
 #include <mutex>
 
@@ -69,9 +69,8 @@ hipError_t launch_flux(const DeviceMesh &m, bool fp32, const FluxLaunch &f, hipS
 template <typename real, int NV, int PHYS>
 __global__ __launch_bounds__(256) void k_dt_partials(int64_t N, const double *U, const real *fr, const double *area,
                                                      double gamma, double ax, double ay, double *part) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double dtc = INFINITY;
-    if (i < N) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)gridDim.x * 256) {
         double u[NV], nrm[3][3];
 #pragma unroll
         for (int v = 0; v < NV; ++v) u[v] = U[i * NV + v];
@@ -82,14 +81,15 @@ __global__ __launch_bounds__(256) void k_dt_partials(int64_t N, const double *U,
             face_record<real>(fr, i, f, nx, ny, len, code);
             nrm[f][0] = nx; nrm[f][1] = ny; nrm[f][2] = len;
         }
-        dtc = cell_dt_bound<NV, PHYS>(u, nrm, area[i], gamma, ax, ay);
+        dtc = fmin(dtc, cell_dt_bound<NV, PHYS>(u, nrm, area[i], gamma, ax, ay));
     }
     const double bm = block_min(dtc);
     if (threadIdx.x == 0) part[blockIdx.x] = bm;
 }
 
-hipError_t launch_dt_partials(const DeviceMesh &m, bool fp32, const double *U, double *part, hipStream_t st) {
-    const unsigned grid = (unsigned)m.blocks();
+hipError_t launch_dt_partials(const DeviceMesh &m, bool fp32, const double *U, double *part, int64_t n_part,
+                              hipStream_t st) {
+    const unsigned grid = (unsigned)n_part;
     const bool f32 = (fp32 && m.fr32) || m.fr64 == nullptr;
     if (m.physics == CTENO_EULER) {
         if (f32) hipLaunchKernelGGL((k_dt_partials<float, 4, CTENO_EULER>), dim3(grid), dim3(256), 0, st, m.N, U,
@@ -181,24 +181,27 @@ __device__ __forceinline__ int find_slot(const BatchSlot *tab, int n, int64_t b)
 }
 
 template <int R, int SCHEME, int GFORM>
-__global__ __launch_bounds__(256) void k_reconstruct_batch(const ReconArgs<float, (R + 1) * (R + 2) / 2 - 1> a,
-                                                           const BatchSlot *tab, const int *n_slots, int stage) {
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    const int64_t b = blockIdx.x;
+__global__ __launch_bounds__(256) void k_reconstruct_batch(const ReconArgs<float> a, const BatchSlot *tab,
+                                                           const int *n_slots, int stage) {
+    const int64_t b = blockIdx.x >> 2;        // four groups of 64 cells per table block
     const int s = find_slot(tab, *n_slots, b);
     if (s < 0) return;                        // uniform across the block
     const BatchSlot &t = tab[s];
     if (t.ctrl->done) return;
-    __shared__ float ctab[recon_tab_size<K>()];
-    recon_tab_fill<float, K>(a, ctab);
-    __syncthreads();
-    const int64_t i = (b - t.block0) * blockDim.x + threadIdx.x;
+    const int64_t i = (b - t.block0) * 256 + (blockIdx.x & 3) * 64 + (threadIdx.x >> 2);
+    if ((i & ~int64_t(63)) >= t.N) return;    // a group past the padded cells: whole blocks
+    const int q = threadIdx.x & 3;
+    const ReconPtrs<float> ptr{t.U[stage], t.lslot, t.desc, t.hlist, t.flags, t.P, nullptr, nullptr,
+                               &t.ctrl->fallbacks, nullptr};
+    extern __shared__ __align__(16) double rows[];
+    double U0;
+    float out[3][2];
+    recon_quad<float, R, 4, SCHEME, GFORM, 0, 0>(a, ptr, rows, i, threadIdx.x, i < t.N, [](const int4 &) {}, U0, out);
     if (i >= t.N) return;
-    const ReconPtrs<float> ptr{t.U[stage], t.slot, t.flags, t.P, t.FV, nullptr, nullptr, &t.ctrl->fallbacks, ctab,
-                               nullptr};
-    float out[3][2][4];
-    recon_body<float, R, 4, SCHEME, GFORM, 0, 0>(a, ptr, i, out);
-    store_row<float, 3 * 2 * 4>(ptr.FV + i * 3 * 2 * 4, &out[0][0][0]);
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) t.FV[((i * 3 + f) * 2 + g) * 4 + q] = out[f][g];
 }
 
 __global__ __launch_bounds__(256) void k_flux_batch(const FluxArgs<float> a, const BatchSlot *tab, const int *n_slots) {
@@ -231,10 +234,10 @@ __global__ __launch_bounds__(1024) void k_control_batch(const BatchSlot *tab, co
 template <int R>
 static hipError_t batch_step_r(const DeviceMesh &proto, const BatchSlot *tab, const int *n_slots, int max_slots,
                                int64_t max_blocks, hipStream_t st) {
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    ReconArgs<float, K> ra;
-    std::memset(&ra, 0, sizeof ra);
-    fill_recon_constants<float, K>(proto, ra);
+    ReconArgs<float> ra;
+    fill_recon_constants<float>(proto, ra);
+    if (!ra.tab) return hipErrorInvalidValue;
+    const dim3 rgrid((unsigned)(4 * max_blocks));
     FluxArgs<float> fa{};
     std::memset(&fa, 0, sizeof fa);
     fa.gamma = (float)proto.gamma; fa.ax = (float)proto.ax; fa.ay = (float)proto.ay; fa.gamma64 = proto.gamma;
@@ -243,23 +246,23 @@ static hipError_t batch_step_r(const DeviceMesh &proto, const BatchSlot *tab, co
     hipLaunchKernelGGL(k_control_batch, dim3(max_slots), dim3(1024), 0, st, tab, n_slots);
     for (int stage = 0; stage < 3; ++stage) {
         if (proto.scheme == CTENO_SCHEME_CTENOZ && proto.gamma_form == CTENO_GAMMA_SCALED)
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENOZ, CTENO_GAMMA_SCALED>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENOZ, CTENO_GAMMA_SCALED>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         else if (proto.scheme == CTENO_SCHEME_CTENOZ)
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENOZ, CTENO_GAMMA_PAPER>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENOZ, CTENO_GAMMA_PAPER>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         else if (proto.scheme == CTENO_SCHEME_CWENO)
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CWENO, CTENO_GAMMA_PAPER>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CWENO, CTENO_GAMMA_PAPER>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         else if (proto.scheme == CTENO_SCHEME_TENO)
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_TENO, CTENO_GAMMA_PAPER>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_TENO, CTENO_GAMMA_PAPER>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         else if (proto.gamma_form == CTENO_GAMMA_LAMBDA)
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENO, CTENO_GAMMA_LAMBDA>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENO, CTENO_GAMMA_LAMBDA>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         else
-            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENO, CTENO_GAMMA_PAPER>), dim3(max_blocks),
-                               dim3(256), 0, st, ra, tab, n_slots, stage);
+            hipLaunchKernelGGL((k_reconstruct_batch<R, CTENO_SCHEME_CTENO, CTENO_GAMMA_PAPER>), rgrid,
+                               dim3(256), proto.row_bytes(), st, ra, tab, n_slots, stage);
         fa.stage = stage;
         hipLaunchKernelGGL(k_flux_batch, dim3(max_blocks), dim3(256), 0, st, fa, tab, n_slots);
     }
@@ -370,6 +373,15 @@ hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, size_t n
     return hipGetLastError();
 }
 
+__global__ void k_fill_u32(uint32_t *p, uint32_t v, size_t n) {
+    const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) p[k] = v;
+}
+hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_fill_u32, dim3(grid_for((int64_t)n)), dim3(256), 0, st, p, v, n);
+    return hipGetLastError();
+}
+
 __global__ void k_copy16(uint4 *dst, const uint4 *src, size_t n) {
     for (size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x)
         dst[k] = src[k];
@@ -419,18 +431,282 @@ void *scratch_device_ptr(int device) {
     return g_scratch_ptr[device];
 }
 
+// the cell of slot j of cell i, from the row-number table
+template <int R>
+__device__ __forceinline__ int32_t row_cell(const uint16_t *lslot, const int4 *desc, const int32_t *hlist,
+                                            int64_t i, int j) {
+    const int r = lslot[lslot_index<R>(i, j)];
+    return r < 64 ? (int32_t)((i & ~int64_t(63)) + r) : hlist[desc[i >> 6].x + r - 64];
+}
+// RL: the degree at r <= 3, 4 for the higher ones, 0 for the slot table
+template <int RL>
 __global__ void k_gather_entries(int n, const int32_t *idx, int E, int VW, const double *s64, const float *s32,
                                  const int32_t *si, double *dst, int ct) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)n * E) return;
     const int a = (int)(t / E), e = (int)(t % E);
-    const size_t src = ct == 64 ? avix(idx[a], e, E, VW) : hvix(idx[a], e, E, VW, ct);
+    size_t src;
+    if constexpr (RL == 0) src = avix(idx[a], e, E, VW);
+    else if constexpr (RL <= 3) src = quad_index_entry<RL>(idx[a], e, VW);
+    else src = hvix(idx[a], e, E, VW, ct);
     dst[t] = s64 ? s64[src] : (s32 ? (double)s32[src] : (double)si[src]);
 }
-hipError_t launch_gather_entries(int n, const int32_t *idx, int E, int VW, const double *src64, const float *src32,
-                                 const int32_t *srci, double *dst, hipStream_t st, int ct) {
-    hipLaunchKernelGGL(k_gather_entries, dim3(grid_for((int64_t)n * E)), dim3(256), 0, st, n, idx, E, VW, src64,
-                       src32, srci, dst, ct);
+template <int R>
+__global__ void k_gather_cells(int n, const int32_t *idx, int SP, const uint16_t *lslot, const int4 *desc,
+                               const int32_t *hlist, double *dst) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)n * SP) return;
+    dst[t] = (double)row_cell<R>(lslot, desc, hlist, idx[t / SP], (int)(t % SP));
+}
+hipError_t launch_gather_entries(const DeviceMesh &m, int n, const int32_t *idx, int E, const double *src64,
+                                 const float *src32, const int32_t *srci, double *dst, hipStream_t st) {
+    const int VW = src64 ? 2 : 4;
+    const dim3 grid(grid_for((int64_t)n * E)), block(256);
+#define GE_LAUNCH(RL) \
+    hipLaunchKernelGGL((k_gather_entries<RL>), grid, block, 0, st, n, idx, E, VW, src64, src32, srci, dst, m.stile)
+    if (!src64 && !src32 && !srci) {
+        if (m.r == 2) hipLaunchKernelGGL(k_gather_cells<2>, grid, block, 0, st, n, idx, E, m.lslot, m.desc, m.hlist, dst);
+        else hipLaunchKernelGGL(k_gather_cells<3>, grid, block, 0, st, n, idx, E, m.lslot, m.desc, m.hlist, dst);
+    } else if (srci) GE_LAUNCH(0);
+    else if (m.r == 2) GE_LAUNCH(2);
+    else if (m.r == 3) GE_LAUNCH(3);
+    else GE_LAUNCH(4);
+#undef GE_LAUNCH
+    return hipGetLastError();
+}
+
+// ===========================================================================
+// neighbour lists of the 64-cell groups
+// ===========================================================================
+
+// The cells outside group blockIdx.x that its stencils reach, each once and
+// ascending, in LDS; returns their number.  Bitonic sort of the group's
+// outside entries (padded with INT_MAX to a power of two), then the first of
+// each run moves to its rank.
+constexpr int kHaloSort = 2048;           // >= 64 cells x 18 slots
+__device__ __forceinline__ int group_halo(const int32_t *slot, int SP, int (&key)[kHaloSort],
+                                          int (&uniq)[kHaloSort]) {
+    __shared__ int cnt;
+    __shared__ int wsum[4];
+    const int64_t i0 = (int64_t)blockIdx.x * 64;
+    if (threadIdx.x == 0) cnt = 0;
+    for (int k = threadIdx.x; k < kHaloSort; k += 256) key[k] = 0x7FFFFFFF;
+    __syncthreads();
+    for (int k = threadIdx.x; k < 64 * SP; k += 256) {
+        const int m = slot[avix(i0 + (k & 63), k >> 6, SP, 4)];
+        if ((m >> 6) != (int)blockIdx.x) key[atomicAdd(&cnt, 1)] = m;
+    }
+    __syncthreads();
+    int n2 = 64;
+    while (n2 < cnt) n2 *= 2;
+    for (int len = 2; len <= n2; len *= 2)
+        for (int st = len / 2; st > 0; st /= 2) {
+            for (int p = threadIdx.x; p < n2 / 2; p += 256) {
+                const int a = 2 * p - (p & (st - 1)), b = a + st;
+                const int x = key[a], y = key[b];
+                if ((x > y) == ((a & len) == 0)) { key[a] = y; key[b] = x; }
+            }
+            __syncthreads();
+        }
+    // ranks of the first of each run: a contiguous share per thread
+    const int per = n2 < 256 ? 1 : n2 / 256, k0 = threadIdx.x * per;
+    int c = 0;
+    for (int k = k0; k < k0 + per && k < cnt; ++k) c += k == 0 || key[k] != key[k - 1];
+    int s = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(s, o, 64);
+        if ((threadIdx.x & 63) >= (unsigned)o) s += y;
+    }
+    if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = s;
+    __syncthreads();
+    int rank = s - c, total = 0;
+    for (int w = 0; w < 4; ++w) {
+        if (w < (int)(threadIdx.x >> 6)) rank += wsum[w];
+        total += wsum[w];
+    }
+    for (int k = k0; k < k0 + per && k < cnt; ++k)
+        if (k == 0 || key[k] != key[k - 1]) uniq[rank++] = key[k];
+    __syncthreads();
+    return total;
+}
+
+__global__ __launch_bounds__(256) void k_halo_counts(const int32_t *slot, int SP, int32_t *len) {
+    __shared__ int key[kHaloSort], uniq[kHaloSort];
+    const int n = group_halo(slot, SP, key, uniq);
+    if (threadIdx.x == 0) len[blockIdx.x] = n;
+}
+template <int R>
+__global__ __launch_bounds__(256) void k_halo_lists(const int32_t *slot, int SP, const int4 *desc,
+                                                    int32_t *hlist, uint16_t *lslot) {
+    __shared__ int key[kHaloSort], uniq[kHaloSort];
+    const int n = group_halo(slot, SP, key, uniq);
+    const int64_t i0 = (int64_t)blockIdx.x * 64;
+    for (int k = threadIdx.x; k < n; k += 256) hlist[desc[blockIdx.x].x + k] = uniq[k];
+    for (int k = threadIdx.x; k < 64 * 4 * QuadDims<R>::SK; k += 256) {
+        const int64_t i = i0 + (k & 63);
+        const int j = k >> 6, m = j < SP ? slot[avix(i, j, SP, 4)] : (int)i;     // pads: the cell itself
+        int row = m & 63;
+        if ((m >> 6) != (int)blockIdx.x) {
+            int lo = 0, hi = n - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (uniq[mid] < m) lo = mid + 1;
+                else hi = mid;
+            }
+            row = 64 + lo;
+        }
+        lslot[lslot_index<R>(i, j)] = (uint16_t)row;
+    }
+}
+hipError_t launch_halo_counts(const DeviceMesh &m, int32_t *len, hipStream_t st) {
+    if (m.r > 3 || 64 * m.SP > kHaloSort) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_halo_counts, dim3((unsigned)m.groups()), dim3(256), 0, st, m.slot, m.SP, len);
+    return hipGetLastError();
+}
+hipError_t launch_halo_lists(const DeviceMesh &m, hipStream_t st) {
+    if (m.r > 3 || 64 * m.SP > kHaloSort) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)m.groups());
+    if (m.r == 2)
+        hipLaunchKernelGGL(k_halo_lists<2>, grid, dim3(256), 0, st, m.slot, m.SP, m.desc, m.hlist, m.lslot);
+    else
+        hipLaunchKernelGGL(k_halo_lists<3>, grid, dim3(256), 0, st, m.slot, m.SP, m.desc, m.hlist, m.lslot);
+    return hipGetLastError();
+}
+
+// ===========================================================================
+// block data of the fused stage
+// ===========================================================================
+
+// the arrays of a DeviceMesh that these kernels read and write
+struct BlockMesh {
+    int64_t N, Np, n_cross;
+    const float *fr32;
+    const double *fr64, *area;
+    const int4 *desc;
+    float *frec32, *xrec32;
+    double *frec64, *xrec64, *xarea;
+    uint32_t *xid;
+    int2 *xcells;
+    explicit BlockMesh(const DeviceMesh &m)
+        : N(m.N), Np(m.Np), n_cross(m.n_cross), fr32(m.fr32), fr64(m.fr64), area(m.area), desc(m.desc),
+          frec32(m.frec32), xrec32(m.xrec32), frec64(m.frec64), xrec64(m.xrec64), xarea(m.xarea), xid(m.xid),
+          xcells(m.xcells) {}
+};
+
+// the neighbour code of face f of cell i, from either kind of face record
+__device__ __forceinline__ uint32_t face_code(const BlockMesh &m, int64_t i, int f) {
+    if (m.fr32) return (uint32_t)__float_as_int(m.fr32[avix(i, 4 * f + 3, 12, 4)]);
+    return (uint32_t)__double_as_longlong(m.fr64[avix(i, 4 * f + 3, 12, 2)]);
+}
+
+// exclusive sum over a wave and the total
+__device__ __forceinline__ int wave_scan(int x, int &total) {
+    int s = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(s, o, 64);
+        if ((int)(threadIdx.x & 63) >= o) s += y;
+    }
+    total = __shfl(s, 63, 64);
+    return s - x;
+}
+
+// a cell's listed faces and its faces to other blocks of `bc` cells, as bit masks
+__device__ __forceinline__ void cell_faces(const BlockMesh &m, int64_t i, int bc, uint32_t (&code)[3], int &listed,
+                                           int &cross) {
+    listed = cross = 0;
+    if (i >= m.N) return;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        code[f] = face_code(m, i, f);
+        if (code[f] & kNbBoundary) listed |= 1 << f;
+        else if ((int64_t)(code[f] & kNbIndexMask) / bc != i / bc) cross |= 1 << f;
+        else if (code[f] & kNbOwner) listed |= 1 << f;
+    }
+}
+
+// one wave per group
+__global__ __launch_bounds__(256) void k_block_counts(const BlockMesh m, const BlockCounts c) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, g = i >> 6;
+    if (i >= m.Np) return;                    // whole waves
+    uint32_t code[3];
+    int listed, cross, cross256, nf, nx, ns, n256;
+    cell_faces(m, i, 256, code, listed, cross256);
+    cell_faces(m, i, 64, code, listed, cross);
+    (void)wave_scan(__popc(listed), nf);
+    (void)wave_scan(cross ? 1 : 0, nx);
+    (void)wave_scan(__popc(cross), ns);
+    (void)wave_scan(cross256 ? 1 : 0, n256);
+    if ((threadIdx.x & 63) == 0) {
+        c.faces[g] = nf;
+        c.cross[g] = nx;
+        c.sides[g] = ns;
+        if (n256) atomicAdd(c.cross256, n256);
+    }
+}
+hipError_t launch_block_counts(const DeviceMesh &m, const BlockCounts &c, hipStream_t st) {
+    hipLaunchKernelGGL(k_block_counts, dim3(grid_for(m.Np)), dim3(256), 0, st, BlockMesh(m), c);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_block_lists(const BlockMesh m, const int32_t *xbase, const int32_t *sbase) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, g = i >> 6;
+    if (i >= m.Np) return;                    // whole waves
+    uint32_t code[3];
+    int listed, cross, total;
+    cell_faces(m, i, 64, code, listed, cross);
+    int64_t k = m.desc[g].z + wave_scan(__popc(listed), total);
+    const int64_t t = xbase[g] + wave_scan(cross ? 1 : 0, total);
+    const uint32_t s0 = (uint32_t)(sbase[g] + wave_scan(__popc(cross), total));
+    const uint32_t id = cross ? s0 | ((uint32_t)cross << 28) : 0u;
+    m.xid[i] = id;
+    if (i >= m.N) return;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+        if (!((listed >> f) & 1)) continue;
+        uint32_t bf = (uint32_t)(i & 63) | ((uint32_t)f << 6);
+        if (code[f] & kNbBoundary) bf |= kBfBoundary | ((code[f] & 3u) << 8);
+        else bf |= (code[f] & 63u) << 8 | ((code[f] >> 28) & 3u) << 14;
+        for (int e = 0; e < 3; ++e) {
+            if (m.frec32) m.frec32[4 * k + e] = m.fr32[avix(i, 4 * f + e, 12, 4)];
+            if (m.frec64) m.frec64[4 * k + e] = m.fr64[avix(i, 4 * f + e, 12, 2)];
+        }
+        if (m.frec32) m.frec32[4 * k + 3] = __int_as_float((int)bf);
+        if (m.frec64) m.frec64[4 * k + 3] = __longlong_as_double((long long)bf);
+        ++k;
+    }
+    if (cross) {
+        m.xcells[t] = make_int2((int)i, (int)id);
+        m.xarea[t] = m.area[i];
+    }
+}
+// one thread per cross cell: its side records (every cell's first side is known)
+__global__ __launch_bounds__(256) void k_side_records(const BlockMesh m) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= m.n_cross) return;
+    const int64_t i = m.xcells[t].x;
+    const uint32_t id = m.xid[i];
+    int64_t s = id & kNbIndexMask;
+    for (int f = 0; f < 3; ++f) {
+        if (!((id >> (28 + f)) & 1)) continue;
+        const uint32_t code = face_code(m, i, f), idj = m.xid[code & kNbIndexMask];
+        const int gf = (int)((code >> 28) & 3u);
+        const uint32_t other = (idj & kNbIndexMask) + __popc((idj >> 28) & ((1u << gf) - 1u));
+        const bool fb = (int64_t)(code & kNbIndexMask) / 256 != i / 256;
+        const uint32_t w = other | (code & kNbOwner) | (fb ? kSideFar : 0u);
+        for (int e = 0; e < 3; ++e) {
+            if (m.xrec32) m.xrec32[4 * s + e] = m.fr32[avix(i, 4 * f + e, 12, 4)];
+            if (m.xrec64) m.xrec64[4 * s + e] = m.fr64[avix(i, 4 * f + e, 12, 2)];
+        }
+        if (m.xrec32) m.xrec32[4 * s + 3] = __int_as_float((int)w);
+        if (m.xrec64) m.xrec64[4 * s + 3] = __longlong_as_double((long long)w);
+        ++s;
+    }
+}
+hipError_t launch_block_lists(const DeviceMesh &m, const int32_t *xbase, const int32_t *sbase, hipStream_t st) {
+    hipLaunchKernelGGL(k_block_lists, dim3(grid_for(m.Np)), dim3(256), 0, st, BlockMesh(m), xbase, sbase);
+    if (m.n_cross) hipLaunchKernelGGL(k_side_records, dim3(grid_for(m.n_cross)), dim3(256), 0, st, BlockMesh(m));
     return hipGetLastError();
 }
 

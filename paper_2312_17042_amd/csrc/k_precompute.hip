@@ -30,7 +30,6 @@ struct PreArgs {
     int *rank_fail;
     double *P64;
     float *P32;
-    int E64, E32;
     double Lx, Ly;
     int ex[K][2];
     double mean[K];
@@ -47,9 +46,10 @@ __global__ __launch_bounds__(64) void k_precompute(const PreArgs<R> a) {
     const int lane = threadIdx.x;
     const int64_t i = (int64_t)blockIdx.x * 64 + lane;
     if (i >= a.N) return;                 // lanes only touch their own LDS column: no barriers needed
-    auto put = [&](int e, double v) {
-        a.P64[avix(i, e, a.E64, 2)] = v;
-        if (a.P32) a.P32[avix(i, e, a.E32, 4)] = (float)v;
+    // coefficient e of slot j
+    auto put = [&](int j, int e, double v) {
+        a.P64[quad_index<R>(i, j, e, 2)] = v;
+        if (a.P32) a.P32[quad_index<R>(i, j, e, 4)] = (float)v;
     };
 
     const double x0 = a.verts[tix(i, 0, 6)], y0 = a.verts[tix(i, 1, 6)];
@@ -162,9 +162,8 @@ __global__ __launch_bounds__(64) void k_precompute(const PreArgs<R> a) {
             for (int k2 = j + 1; k2 < K; ++k2) s -= sA[k2 * S + j][lane] * x[k2];
             x[j] = s / sQ[2][j][lane];
         }
-        const int off = pinv_offset(m, K);
 #pragma unroll
-        for (int k = 0; k < K; ++k) put(off + k, rank_ok ? x[k] : 0.0);
+        for (int k = 0; k < K; ++k) put(m, k, rank_ok ? x[k] : 0.0);
     }
 
     // directional 4 x 2 systems in registers
@@ -219,9 +218,8 @@ __global__ __launch_bounds__(64) void k_precompute(const PreArgs<R> a) {
             }
             const double x1 = ok ? b[1] / rd[1] : 0.0;
             const double x0v = ok ? (b[0] - A[0][1] * x1) / rd[0] : 0.0;
-            const int off = pinv_offset(4 * s + m, K) + K;
-            put(off, x0v);
-            put(off + 1, x1);
+            put(4 * s + m, K, x0v);
+            put(4 * s + m, K + 1, x1);
         }
     }
     a.flags[i] = fl;
@@ -272,7 +270,7 @@ static hipError_t precompute_r(const DeviceMesh &m, const PrecomputeInputs &in, 
     a.N = m.N;
     a.verts = in.verts; a.slot = m.slot; a.slot_flag = in.slot_flag; a.slot_shift = in.slot_shift;
     a.flags = in.flags; a.rank_fail = in.rank_fail;
-    a.P64 = m.P64; a.P32 = m.P32; a.E64 = m.E64; a.E32 = m.E32;
+    a.P64 = m.P64; a.P32 = m.P32;
     a.Lx = m.Lx; a.Ly = m.Ly;
     for (int k = 0; k < PreArgs<R>::K; ++k) {
         a.ex[k][0] = m.tab.ex[k][0];
@@ -523,7 +521,7 @@ __global__ __launch_bounds__(256) void k_precompute_ho(const PreHoArgs<R> a) {
 template <int R>
 static hipError_t precompute_ho_r(const DeviceMesh &m, const PrecomputeInputs &in, hipStream_t st) {
     using D = HoDims<R>;
-    if (m.S != D::S || m.E64 != D::E || m.E32 != D::E || m.SP != D::SP) return hipErrorInvalidValue;
+    if (m.S != D::S || m.E != D::E || m.SP != D::SP) return hipErrorInvalidValue;
     PreHoArgs<R> a;
     a.N = m.N;
     a.verts = in.verts; a.slot = m.slot; a.slot_flag = in.slot_flag; a.slot_shift = in.slot_shift;

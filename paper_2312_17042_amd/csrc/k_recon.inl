@@ -1,38 +1,34 @@
-// Reconstruction of degree 2 and 3 (one lane per cell): the kernel and its
-// launch, for one arithmetic type; instantiated per type by k_recon_f32.hip
-// and k_recon_f64.hip.
+// Reconstruction of degree 2 and 3 (a quad of lanes per cell): the kernel and
+// its launch, for one arithmetic type; instantiated per type by
+// k_recon_f32.hip and k_recon_f64.hip.
 #pragma once
-#include "kernels_common.h"
+#include "recon_quad.h"
 
 namespace cteno {
 
-// The FP64 march in conserved variables is held to two waves per SIMD (its
-// directional coefficients wait in LDS); the other instances take the
-// registers they need
 template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS>
-__global__ __launch_bounds__(256, (std::is_same<real, double>::value && VARS == 0 && DMODE != 2) ? 2 : 1)
-void k_reconstruct(const ReconArgs<real, (R + 1) * (R + 2) / 2 - 1> a) {
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    constexpr bool F64 = std::is_same<real, double>::value;
-    __shared__ real tab[F64 ? 1 : recon_tab_size<K>()];
-    __shared__ double lad[F64 ? 3 * 2 * NV * 256 : 1];   // FP64: directional coefficients
-    recon_tab_fill<real, K>(a, tab);
-    __syncthreads();
-    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (i >= a.N) return;
-    if (a.done && *a.done) return;
-    const ReconPtrs<real> ptr{a.U, a.slot, a.flags, a.P, a.FV, a.delta, a.fr, a.fb_count, tab, lad};
-    real out[3][2][NV];
-    recon_body<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, i, out);
-    store_row<real, 3 * 2 * NV>(ptr.FV + i * 3 * 2 * NV, &out[0][0][0]);
+__global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, const ReconPtrs<real> ptr, int64_t N,
+                                                     real *FV) {
+    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * 64 + (threadIdx.x >> 2);
+    const int q = threadIdx.x & 3, v = NV == 4 ? q : 0;
+    const bool live = i < N;
+    extern __shared__ __align__(16) double rows[];
+    double U0;
+    real out[3][2];
+    if (!recon_quad<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, rows, i, threadIdx.x, live, [](const int4 &) {},
+                                                                    U0, out)) return;
+    if (!live || q >= NV) return;
+#pragma unroll
+    for (int f = 0; f < 3; ++f)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) FV[((i * 3 + f) * 2 + g) * NV + v] = out[f][g];
 }
 
-
 template <typename real, int R, int NV, int VARS>
-static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real, (R + 1) * (R + 2) / 2 - 1> &a, int dmode,
-                               unsigned grid, hipStream_t st) {
+static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real> &a, const ReconPtrs<real> &p, real *FV,
+                               int dmode, unsigned grid, hipStream_t st) {
 #define CT_LAUNCH(SCH, GF, DM) \
-    hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS>), dim3(grid), dim3(256), 0, st, a)
+    hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS>), dim3(grid), dim3(256), m.row_bytes(), st, a, p, m.N, FV)
 #define CT_DM(SCH, GF)                        \
     switch (dmode) {                          \
         case 0: CT_LAUNCH(SCH, GF, 0); break; \
@@ -52,32 +48,31 @@ static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real, (R + 1
 template <typename real, int R, int NV>
 static hipError_t reconstruct_t(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode,
                                 const int *done, hipStream_t st, unsigned long long *fb_count) {
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    ReconArgs<real, K> a;
-    a.N = m.N;
-    a.U = U;
-    a.slot = m.slot;
-    a.flags = m.flags;
-    if constexpr (std::is_same<real, double>::value) a.P = m.P64;
-    else a.P = m.P32;
-    if (!a.P) return hipErrorInvalidValue;
-    a.FV = (real *)FV;
-    a.delta = delta;
-    a.done = done;
-    if constexpr (std::is_same<real, double>::value) a.fr = m.fr64;
-    else a.fr = m.fr32;
-    fill_recon_constants<real, K>(m, a);
-    a.fb_count = fb_count;
-    const unsigned grid = (unsigned)m.blocks();
+    if (m.E != QuadDims<R>::E || m.SP != QuadDims<R>::SP) return hipErrorInvalidValue;
+    ReconArgs<real> a;
+    fill_recon_constants<real>(m, a);
+    ReconPtrs<real> p{};
+    p.U = U;
+    p.lslot = m.lslot;
+    p.desc = m.desc;
+    p.hlist = m.hlist;
+    p.flags = m.flags;
+    if constexpr (std::is_same<real, double>::value) { p.P = m.P64; p.fr = m.fr64; }
+    else { p.P = m.P32; p.fr = m.fr32; }
+    p.delta = delta;
+    p.fb = fb_count;
+    p.done = done;
+    if (!p.P || !a.tab || !p.lslot || !p.desc || !p.hlist) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)(m.Np / 64);
     if (m.vars == CTENO_VARS_CHARACTERISTIC) {
         if constexpr (NV == 4) {
-            if (!a.fr) return hipErrorInvalidValue;
-            reconstruct_launch<real, R, NV, 1>(m, a, dmode, grid, st);
+            if (!p.fr) return hipErrorInvalidValue;
+            reconstruct_launch<real, R, NV, 1>(m, a, p, (real *)FV, dmode, grid, st);
         } else {
             return hipErrorInvalidValue;
         }
     } else {
-        reconstruct_launch<real, R, NV, 0>(m, a, dmode, grid, st);
+        reconstruct_launch<real, R, NV, 0>(m, a, p, (real *)FV, dmode, grid, st);
     }
     return hipGetLastError();
 }

@@ -2,7 +2,7 @@
 // cell, a lane per cell for advection) for one arithmetic type;
 // instantiated per type by k_recon_ho_f32.hip and k_recon_ho_f64.hip.
 #pragma once
-#include "kernels_common.h"
+#include "recon_quad.h"
 
 namespace cteno {
 
@@ -99,26 +99,6 @@ __device__ __forceinline__ int finish_field_ho(const ReconHoArgs<real> a, real (
     return bits;
 }
 
-// value of x in lane u of each group of four lanes (a quad), by a DPP move
-template <int u>
-__device__ __forceinline__ float quad_bcast(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), u * 0x55, 0xF, 0xF, false));
-}
-template <int u>
-__device__ __forceinline__ double quad_bcast(double x) {
-    const long long b = __builtin_bit_cast(long long, x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xFFFFFFFFll), u * 0x55, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), u * 0x55, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
-// the value that lane `owner` of the quad holds in x[v] for the calling lane's v
-template <typename real, int owner>
-__device__ __forceinline__ real quad_take(const real (&x)[4], int v) {
-    const real x0 = quad_bcast<owner>(x[0]), x1 = quad_bcast<owner>(x[1]);
-    const real x2 = quad_bcast<owner>(x[2]), x3 = quad_bcast<owner>(x[3]);
-    return v == 0 ? x0 : v == 1 ? x1 : v == 2 ? x2 : x3;
-}
-
 // Coefficient e of the slot stream is accumulated by lane (e / VW) % 4 of
 // the quad, in its round (e / VW) / 4, component e % VW, for the GF full
 // rounds of four vectors; the four entries past them (the spread tail) by
@@ -126,8 +106,8 @@ __device__ __forceinline__ real quad_take(const real (&x)[4], int v) {
 // lanes.
 template <typename real, int VW, int GF, int e>
 __device__ __forceinline__ real ho_take1(const real (&acc)[GF][VW][4], const real (&acs)[4], int v) {
-    if constexpr (e < 4 * GF * VW) return quad_take<real, (e / VW) % 4>(acc[e / VW / 4][e % VW], v);
-    else return quad_take<real, e - 4 * GF * VW>(acs, v);
+    if constexpr (e < 4 * GF * VW) return quad_take<(e / VW) % 4>(acc[e / VW / 4][e % VW], v);
+    else return quad_take<e - 4 * GF * VW>(acs, v);
 }
 
 template <typename real, int VW, int GF, int e0, int n, int... k>
@@ -578,7 +558,7 @@ static hipError_t reconstruct_ho_t(const DeviceMesh &m, const double *U, void *F
     a.flags = m.flags;
     if constexpr (std::is_same<real, double>::value) { a.P = m.P64; a.tab = m.htab64; }
     else { a.P = m.P32; a.tab = m.htab32; }
-    if (!a.P || !a.tab || m.stile != 64 / NV || m.E64 != D::E) return hipErrorInvalidValue;
+    if (!a.P || !a.tab || m.stile != 64 / NV || m.E != D::E) return hipErrorInvalidValue;
     if constexpr (std::is_same<real, double>::value) a.fr = m.fr64;
     else a.fr = m.fr32;
     if (m.vars == CTENO_VARS_CHARACTERISTIC && (NV != 4 || !a.fr)) return hipErrorInvalidValue;

@@ -1,198 +1,312 @@
 // Fused SSP-RK3 stage of degree 2 and 3 for one arithmetic type;
 // instantiated per type by k_stage_f32.hip and k_stage_f64.hip.
 //
-// k_stage (part 0), one lane per cell, 256-cell blocks: the reconstruction of
-// the block's cells (sec. 2.1-2.6) goes to LDS; after a block barrier each
-// cell evaluates the fluxes (sec. 2.7) of its faces whose neighbour lies in
-// the same block from LDS, and of its boundary faces, and -- when no face
-// leads to another block -- applies its RK stage at once.  A cell with a
-// face to another block (a cross cell) stores the values of those faces and
-// its stage state from the other faces instead, both by its rank among the
-// cross cells (so part 1 reads them contiguously), and k_stage_cross (part
-// 1) adds the faces to other blocks.  Both cells of a face evaluate the same
-// flux from the same values (LDS holds exactly the values the other cell
-// computed), so the update stays conservative to FP64 round-off.  Face
-// values of faces inside a block never leave the chip.
+// k_stage (part 0), a quad of lanes per cell, a group of 64 cells per block:
+// the reconstruction of the group's cells (sec. 2.1-2.6) goes to LDS; after a
+// block barrier the lanes take the group's listed faces -- its boundary faces
+// and the faces between two of its cells -- one Gauss point each, and leave
+// the face's flux (sec. 2.7) in LDS for both of its cells, with opposite
+// signs; after a second barrier each cell sums its faces and applies its RK
+// stage, a lane per variable.  The values of a face to another group go to
+// memory, at the place of that side of the face, and k_stage_cross (part 1)
+// adds these faces to their cells' states.  The two cells of a face see
+// bitwise opposite terms, so the update stays conservative to FP64 round-off
+// without atomics.  Face values of faces inside a group never leave the chip.
 #pragma once
-#include "kernels_common.h"
+#include "recon_quad.h"
 
 namespace cteno {
 
-// FP64 in conserved variables is held to two waves per SIMD, like its
-// reconstruction kernel
-template <typename real, int R, int NV, int SCHEME, int GFORM, int VARS, int PHYS>
-__global__ __launch_bounds__(256, (std::is_same<real, double>::value && VARS == 0) ? 2 : 1)
-void k_stage(const ReconArgs<real, (R + 1) * (R + 2) / 2 - 1> ra, const FluxArgs<real> fa) {
-    constexpr int NQ = 2, ROW = 3 * NQ * NV;
-    constexpr bool F64 = std::is_same<real, double>::value;
-    // the block's face-point values; in FP64 the same space first holds the
-    // reconstruction's directional coefficients ([3][2][NV] x 256 doubles)
-    __shared__ __align__(16) real lfv[256 * ROW];
-    __shared__ __align__(16) double lterm[256 * 3 * NV]; // owners' terms of the faces inside the block
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    __shared__ real tab[F64 ? 1 : recon_tab_size<K>()];
-    __shared__ int wcross[4];                         // cross cells per wave
-    static_assert(!F64 || ROW == 3 * 2 * NV, "the face-value rows hold the directional coefficients");
-    recon_tab_fill<real, K>(ra, tab);
-    __syncthreads();
-    const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
-    const int64_t i = blk * 256 + threadIdx.x;
-    if (ra.done && *ra.done) return;           // uniform across the grid
-    const bool live = i < fa.N;
-    const FluxPtrs<real> ptr{fa.FV, fa.fr, fa.area, fa.Un, fa.Us, fa.Uout, fa.dt_ptr, nullptr, nullptr,
-                             fa.nonphys, fa.dt_part != nullptr};
-    real own[3][NQ][NV];
-    real nx[3], ny[3], len[3];
-    uint32_t code[3];
-    double u0[NV], us[NV], ar = 1.0;
-    if (live) {
-        const ReconPtrs<real> rp{ra.U, ra.slot, ra.flags, ra.P, nullptr, nullptr, ra.fr, ra.fb_count, tab,
-                                 F64 ? reinterpret_cast<double *>(lfv) : nullptr};
-        recon_body<real, R, NV, SCHEME, GFORM, 0, VARS>(ra, rp, i, own);
-    }
-    if constexpr (F64) __syncthreads();     // every lane is done with the coefficients in lfv
-    if (live) {
-        store_row<real, ROW>(lfv + threadIdx.x * ROW, &own[0][0][0]);
-        // the flux phase's operands, requested before the barrier
-#pragma unroll
-        for (int f = 0; f < 3; ++f) face_record<real>(fa.fr, i, f, nx[f], ny[f], len[f], code[f]);
-        rk_load<real, NV>(ptr, i, u0, us, ar);
-    }
-    __syncthreads();
-    // boundary faces and the faces inside the block that this cell owns;
-    // the owners' terms go to LDS for the other cells of those faces
-    double term[3][NV];
-    bool bad = false;
-    int kind[3];        // 0: computed here, 1: the owner's term, negated, 2: to another block
-    if (live) {
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            real oth[NQ][NV];
-            bool wallf = false;
-            kind[f] = 0;
-            if (code[f] & kNbBoundary) {
-                wallf = boundary_state<real, NV, PHYS, 2, NQ>(fa, fa.dt_ptr, code[f], own[f], oth);
-            } else {
-                const int64_t j = code[f] & kNbIndexMask;
-                if ((j >> 8) != blk) { kind[f] = 2; continue; }
-                if (!(code[f] & kNbOwner)) { kind[f] = 1; continue; }
-                const int g = (code[f] >> 28) & 3;
-                load_row<real, NQ * NV>(lfv + (j & 255) * ROW + g * NQ * NV, &oth[0][0]);
-            }
-            face_term<real, NV, PHYS, NQ>(fa, own[f], oth, true, wallf, nx[f], ny[f], len[f], term[f], bad);
-            if (!(code[f] & kNbBoundary)) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) lterm[(threadIdx.x * 3 + f) * NV + v] = term[f][v];
-            }
-        }
-    }
-    // a cross cell's rank among the block's cross cells (listed in ascending order)
-    const bool cross = live && (kind[0] == 2 || kind[1] == 2 || kind[2] == 2);
-    const unsigned long long cbal = __ballot(cross);
-    if ((threadIdx.x & 63) == 0) wcross[threadIdx.x >> 6] = __popcll(cbal);
-    __syncthreads();
-    double dtc = INFINITY;
-    if (live) {
-        double acc[NV], nrm[3][3];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            nrm[f][0] = (double)nx[f]; nrm[f][1] = (double)ny[f]; nrm[f][2] = (double)len[f];
-            if (kind[f] == 2) continue;
-            if (kind[f] == 1) {
-                // the owner evaluated F(owner side, this side; owner normal):
-                // this cell's term is its exact negation
-                const int64_t j = code[f] & kNbIndexMask;
-                const int g = (code[f] >> 28) & 3;
-#pragma unroll
-                for (int v = 0; v < NV; ++v) term[f][v] = -lterm[((j & 255) * 3 + g) * NV + v];
-            }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) acc[v] += term[f][v];
-        }
-        if (bad && fa.nonphys) atomicOr(fa.nonphys, 1);
-        if (!cross) {
-            dtc = rk_apply<real, NV, PHYS>(fa, ptr, i, acc, nrm, u0, us, ar);
-        } else {
-            const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-            int before = 0;
-#pragma unroll
-            for (int w = 0; w < 3; ++w) before += w < wv ? wcross[w] : 0;
-            const int64_t t = (int64_t)fa.xbase[blk] + before + __popcll(cbal & ((1ull << lane) - 1));
-            // only the values of the faces to other blocks leave the chip
-#pragma unroll
-            for (int f = 0; f < 3; ++f)
-                if (kind[f] == 2)
-                    store_row<real, NQ * NV>(const_cast<real *>(fa.FV) + t * ROW + f * NQ * NV, &own[f][0][0]);
-            // the stage state from the faces inside the block; part 1 adds
-            // dt times the residual of the others with rk_weight
-            const double dt = ptr.dt_ptr ? *ptr.dt_ptr : fa.dt_value;
-#pragma unroll
-            for (int v = 0; v < NV; ++v) fa.xpart[t * NV + v] = rk_value(fa.stage, u0[v], us[v], dt * (-acc[v] / ar));
-        }
-    }
-    if (fa.dt_part) {
-        const double bm = block_min(dtc);
-        if (threadIdx.x == 0) fa.dt_part[blockIdx.x] = bm;
+// record k of the blocks' listed faces, or side k
+__device__ __forceinline__ void packed_face(const float *rec, int64_t k, float &nx, float &ny, float &len,
+                                            uint32_t &code) {
+    const float4 r = reinterpret_cast<const float4 *>(rec)[k];
+    nx = r.x; ny = r.y; len = r.z;
+    code = (uint32_t)__float_as_int(r.w);
+}
+__device__ __forceinline__ void packed_face(const double *rec, int64_t k, double &nx, double &ny, double &len,
+                                            uint32_t &code) {
+    const double2 *b = reinterpret_cast<const double2 *>(rec) + 2 * k;
+    const double2 r0 = b[0], r1 = b[1];
+    nx = r0.x; ny = r0.y; len = r1.x;
+    code = (uint32_t)__double_as_longlong(r1.y);
+}
+
+// the state of the quad's cell in every lane
+template <int NV>
+__device__ __forceinline__ void quad_state(double un, double (&u)[NV]) {
+    u[0] = quad_bcast<0>(un);
+    if constexpr (NV == 4) {
+        u[1] = quad_bcast<1>(un);
+        u[2] = quad_bcast<2>(un);
+        u[3] = quad_bcast<3>(un);
     }
 }
 
-// part 1: one lane per cross cell, in cross-cell order: the faces to other
-// blocks from both sides' stored values, added to the partial stage state
-template <typename real, int NV, int PHYS>
-__global__ __launch_bounds__(256) void k_stage_cross(const FluxArgs<real> fa) {
+// The registers are held to five waves per SIMD in FP32 and four in FP64; FP64
+// with characteristic variables would spill at four (128 B a lane) and runs three
+template <typename real, int R, int NV, int SCHEME, int GFORM, int VARS, int PHYS>
+__global__ __launch_bounds__(256, (std::is_same<real, double>::value ? (VARS ? 3 : 4) : 5))
+void k_stage(const ReconArgs<real> ra, const ReconPtrs<real> rp, const FluxArgs<real> fa) {
     constexpr int NQ = 2, ROW = 3 * NQ * NV;
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (fa.ctrl && fa.ctrl->done) return;      // uniform across the grid
-    double dtc = INFINITY;
-    if (t < fa.n_cross) {
-        const int64_t i = fa.xcells[t];
-        const FluxPtrs<real> ptr{fa.FV, fa.fr, fa.area, fa.Un, fa.Us, fa.Uout, fa.dt_ptr, nullptr, nullptr,
-                                 fa.nonphys, fa.dt_part != nullptr};
-        double acc[NV];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-        double nrm[3][3];
-        bool bad = false;
+    constexpr bool F32 = std::is_same<real, float>::value;
+    extern __shared__ __align__(16) double rows[];       // the averages that the group reaches
+    __shared__ __align__(16) real lfv[64 * ROW];         // the group's face-point values
+    __shared__ __align__(16) real lterm[64 * 3 * NV];    // outward face fluxes of its cells
+    const int64_t grp = xcd_block(blockIdx.x, gridDim.x);
+    const int cl = threadIdx.x >> 2, q = threadIdx.x & 3, v = NV == 4 ? q : 0;
+    const int64_t i = grp * 64 + cl;
+    const bool live = i < fa.N;
+    const double dtp = *(fa.dt_ptr ? fa.dt_ptr : fa.area), dt = fa.dt_ptr ? dtp : fa.dt_value;
+    // requested behind the products: the update's operands and the lane's first
+    // listed face
+    double un0, ar, U0;
+    uint32_t xid, code;
+    real nx, ny, len, out[3][NQ];
+    int f0, nf;
+    auto mid = [&](const int4 &desc) {
+        un0 = fa.stage ? fa.Un[i * NV + v] : 0.0;        // (stage 0 does not use it)
+        ar = fa.area[i];
+        xid = fa.xid[i];
+        f0 = desc.z;
+        nf = desc.w;
+        // (a place past the list reads the list's last entry)
+        packed_face(fa.frec, f0 + max(min((int)(threadIdx.x >> 1), nf - 1), 0), nx, ny, len, code);
+    };
+    if (!recon_quad<real, R, NV, SCHEME, GFORM, 0, VARS>(ra, rp, rows, i, threadIdx.x, live, mid, U0, out)) return;
+    const int xmask = xid >> 28;                         // the cell's faces to other groups
+    if (q < NV) {
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
-            real nx, ny, len;
-            uint32_t code;
-            face_record<real>(fa.xfr, t, f, nx, ny, len, code);
-            nrm[f][0] = (double)nx; nrm[f][1] = (double)ny; nrm[f][2] = (double)len;
-            const int tn = fa.xnb[t * 3 + f];
-            if (tn < 0) continue;                 // a boundary, or inside the block: in part 0's state
-            const bool owner = (code & kNbOwner) != 0;
-            const int g = (code >> 28) & 3;
-            // both sides' values of this face, as part 0 stored them
-            real mine[NQ][NV], oth[NQ][NV];
-            load_row<real, NQ * NV>(fa.FV + t * ROW + f * NQ * NV, &mine[0][0]);
-            load_row<real, NQ * NV>(fa.FV + (int64_t)tn * ROW + g * NQ * NV, &oth[0][0]);
-            double term[NV];
-            face_term<real, NV, PHYS, NQ>(fa, mine, oth, owner, false, nx, ny, len, term, bad);
 #pragma unroll
-            for (int v = 0; v < NV; ++v) acc[v] += term[v];
+            for (int g = 0; g < NQ; ++g) lfv[cl * ROW + (f * NQ + g) * NV + v] = out[f][g];
+            if (!F32) lterm[(cl * 3 + f) * NV + v] = 0;  // stays for the faces to other groups
         }
-        if (bad && fa.nonphys) atomicOr(fa.nonphys, 1);
-        const double dt = ptr.dt_ptr ? *ptr.dt_ptr : fa.dt_value;
-        const double ar = fa.xarea[t], w = rk_weight(fa.stage);
-        double un[NV];
+        if (xmask) {
+            // only the values of these leave the chip
+            int64_t s = xid & kNbIndexMask;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) un[v] = fa.xpart[t * NV + v] + w * (dt * (-acc[v] / ar));
-        dtc = rk_store<real, NV, PHYS>(fa, ptr, i, un, nrm, ar);
+            for (int f = 0; f < 3; ++f)
+                if ((xmask >> f) & 1) {
+#pragma unroll
+                    for (int g = 0; g < NQ; ++g) const_cast<real *>(fa.FV)[(s * NQ + g) * NV + v] = out[f][g];
+                    ++s;
+                }
+        }
+    }
+    __syncthreads();
+    // the listed faces, a lane per face and Gauss point (lane pairs share a face)
+    bool bad = false;
+    for (int k = threadIdx.x; k < 2 * nf; k += 256) {
+        const int g = k & 1;
+        if (k >= 256) packed_face(fa.frec, f0 + (k >> 1), nx, ny, len, code);
+        const int own = ((code & 63u) * 3 + ((code >> 6) & 3u)) * NQ * NV;
+        const int oth = (((code >> 8) & 63u) * 3 + ((code >> 14) & 3u)) * NQ * NV;
+        real A[NV], B[NV], F[NV];
+        load_row<real, NV>(lfv + own + g * NV, A);
+        bool wallf = false;
+        if (code & kBfBoundary)
+            wallf = boundary_point<real, NV, PHYS>(fa, dt, grp * 64 + (code & 63u), (code >> 6) & 3u,
+                                                   (code >> 8) & 3u, g, A, B);
+        else
+            load_row<real, NV>(lfv + oth + (NQ - 1 - g) * NV, B);
+        if (PHYS == CTENO_EULER) {
+            if (wallf) bad |= !wall_flux<real>(fa.gamma, A, nx, ny, F);
+            else bad |= !hllc<real, F32 ? 0 : -1>(fa.gamma, A, B, nx, ny, F);
+        } else {
+            const real an = fa.ax * nx + fa.ay * ny;
+            F[0] = an * (an >= 0 ? A[0] : B[0]);
+        }
+        // the first lane of the pair leaves the owner's term, the second the
+        // other cell's, its exact negation
+        real term[NV];
+#pragma unroll
+        for (int w = 0; w < NV; ++w) {
+            const real Fo = pair_swap(F[w]);
+            real sum = 0;
+            sum += fa.gw[0] * (g ? Fo : F[w]);
+            sum += fa.gw[1] * (g ? F[w] : Fo);
+            const real t = len * sum;
+            term[w] = g ? -t : t;
+        }
+        if (!g) store_row<real, NV>(lterm + own / NQ, term);
+        else if (!(code & kBfBoundary)) store_row<real, NV>(lterm + oth / NQ, term);
+    }
+    if (bad && fa.nonphys) atomicOr(fa.nonphys, 1);
+    __syncthreads();
+    double dtc = INFINITY;
+    double acc = 0.0;
+#pragma unroll
+    for (int f = 0; f < 3; ++f) acc += (double)lterm[(cl * 3 + f) * NV + v];
+    const double un = rk_value(fa.stage, un0, U0, dt * (-acc / ar));
+    if (live && q < NV) {
+        if (!F32 || !xmask) {
+            // (FP64: a cross cell's state without its faces to other groups)
+            fa.Uout[i * NV + v] = un;
+        } else {
+            // FP32: part 1 sums a cross cell's faces; the terms of those inside
+            // the group (at most two) go to the places of its first side
+            int64_t k = 2 * (int64_t)(xid & kNbIndexMask);
+#pragma unroll
+            for (int f = 0; f < 3; ++f)
+                if (!((xmask >> f) & 1)) fa.xterm[k++ * NV + v] = lterm[(cl * 3 + f) * NV + v];
+        }
     }
     if (fa.dt_part) {
+        // the CFL bound of the new state
+        double u4[NV], nrm[3][3];
+        quad_state<NV>(un, u4);
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            real fx, fy, fl;
+            uint32_t fc;
+            face_record<real>(fa.fr, i, f, fx, fy, fl, fc);
+            nrm[f][0] = (double)fx; nrm[f][1] = (double)fy; nrm[f][2] = (double)fl;
+        }
+        if (live && !xmask) dtc = cell_dt_bound<NV, PHYS>(u4, nrm, ar, fa.gamma64, (double)fa.ax, (double)fa.ay);
         const double bm = block_min(dtc);
         if (threadIdx.x == 0) fa.dt_part[fa.part_off + blockIdx.x] = bm;
     }
 }
 
+// part 1: a quad of lanes per cross cell, ascending: the faces to other groups
+// from both sides' stored values.  Lane q takes Gauss point q % 2 of the cell's
+// side q / 2 (a cell has 1.3 on average; a third is a second round), then
+// variable q.  (A lane per cell ran up to six fluxes one after the other: 10.3
+// us on 16k cells in FP64, now 5.4.)
+// FP64 adds them to the state that part 0 left.  FP32 rounds face values of
+// the state at 1e-8 of it, so the order of the state's own sums shows in a
+// march: it sums the cell's faces in one order whatever the groups are -- those
+// inside its 256-cell block, then those to other blocks -- with the faces
+// inside its group as part 0 left them, and applies the RK stage here.
+template <typename real, int NV, int PHYS>
+__global__ __launch_bounds__(256) void k_stage_cross(const FluxArgs<real> fa, int64_t n_groups) {
+    constexpr int NQ = 2;
+    constexpr bool F32 = std::is_same<real, float>::value;
+    const int64_t t = (int64_t)blockIdx.x * 64 + (threadIdx.x >> 2);
+    const int q = threadIdx.x & 3, v = NV == 4 ? q : 0, g = q & 1;
+    if (fa.ctrl && fa.ctrl->done) return;      // uniform across the grid
+    const bool live = t < fa.n_cross;
+    const int64_t tl = live ? t : fa.n_cross - 1;
+    const int2 xc = fa.xcells[tl];
+    const int64_t i = xc.x;
+    const double ar = fa.xarea[tl];
+    const int xmask = (int)((uint32_t)xc.y >> 28), ns = __popc(xmask);
+    const int64_t s0 = (uint32_t)xc.y & kNbIndexMask;
+    double us, un0 = 0.0;
+    real inside[2];
+    if constexpr (F32) {
+        us = fa.Us[i * NV + v];
+        if (fa.stage) un0 = fa.Un[i * NV + v];
+#pragma unroll
+        for (int r = 0; r < 2; ++r) inside[r] = fa.xterm[(2 * s0 + r) * NV + v];     // (as many as 3 - ns count)
+    } else {
+        us = fa.Uout[i * NV + v];
+    }
+    real side[3] = {0, 0, 0};
+    int far[3] = {0, 0, 0};
+    const double dt = fa.dt_ptr ? *fa.dt_ptr : fa.dt_value;
+    bool bad = false;
+#pragma unroll 1
+    for (int k0 = 0; k0 < 3; k0 += 2) {
+        if (k0 > 0 && !__any(ns > k0)) break;
+        const int k = k0 + (q >> 1);
+        const bool on = k < ns;
+        const int64_t s = s0 + (on ? k : 0);
+        real nx, ny, len;
+        uint32_t code;
+        packed_face(fa.xrec, s, nx, ny, len, code);
+        // both cells of a face evaluate F(owner side, other side; owner
+        // normal) at the owner's points, so their terms are exact negatives
+        const bool owner = (code & kNbOwner) != 0;
+        const int64_t so = code & kNbIndexMask;
+        const int fr = (int)((code & kSideFar) != 0);
+        real A[NV], B[NV], F[NV], term[NV];
+        load_row<real, NV>(fa.FV + ((owner ? s : so) * NQ + g) * NV, A);
+        load_row<real, NV>(fa.FV + ((owner ? so : s) * NQ + (NQ - 1 - g)) * NV, B);
+        const real fx = owner ? nx : -nx, fy = owner ? ny : -ny;
+        if (PHYS == CTENO_EULER) {
+            bad |= !hllc<real, F32 ? 2 : -1>(fa.gamma, A, B, fx, fy, F, fr && g) && on;
+        } else {
+            const real an = fa.ax * fx + fa.ay * fy;
+            F[0] = an * (an >= 0 ? A[0] : B[0]);
+        }
+#pragma unroll
+        for (int w = 0; w < NV; ++w) {
+            const real Fo = pair_swap(F[w]);
+            real sum = 0;
+            sum += fa.gw[0] * (g ? Fo : F[w]);
+            sum += fa.gw[1] * (g ? F[w] : Fo);
+            const real x = len * sum;
+            term[w] = owner ? x : -x;
+        }
+        const real t0 = quad_take<0>(term, v), t1 = quad_take<2>(term, v);
+        const int b0 = quad_bcast_dyn(0, fr), b1 = quad_bcast_dyn(2, fr);
+        if (k0 == 0) {
+            side[0] = t0; far[0] = b0;
+            side[1] = t1; far[1] = b1;
+        } else {
+            side[2] = t0; far[2] = b0;
+        }
+    }
+    if (bad && live && fa.nonphys) atomicOr(fa.nonphys, 1);
+    double un, acc = 0.0;
+    if constexpr (F32) {
+        // the cell's faces in order, the far ones apart
+        double accf = 0.0;
+        int ks = 0, ki = 0;
+        bool anyfar = false;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            if ((xmask >> f) & 1) {
+                const double x = (double)(ks == 0 ? side[0] : ks == 1 ? side[1] : side[2]);
+                const bool fb = (ks == 0 ? far[0] : ks == 1 ? far[1] : far[2]) != 0;
+                if (fb) accf += x;
+                else acc += x;
+                anyfar |= fb;
+                ++ks;
+            } else {
+                acc += (double)(ki == 0 ? inside[0] : inside[1]);
+                ++ki;
+            }
+        }
+        un = rk_value(fa.stage, un0, us, dt * (-acc / ar));
+        if (anyfar) un = un + rk_weight(fa.stage) * (dt * (-accf / ar));
+    } else {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k < ns) acc += (double)side[k];
+        un = us + rk_weight(fa.stage) * (dt * (-acc / ar));
+    }
+    if (live && q < NV) fa.Uout[i * NV + v] = un;
+    if (fa.dt_part) {
+        double u4[NV], nrm[3][3];
+        quad_state<NV>(un, u4);
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            real nx, ny, len;
+            uint32_t code;
+            face_record<real>(fa.fr, i, f, nx, ny, len, code);
+            nrm[f][0] = (double)nx; nrm[f][1] = (double)ny; nrm[f][2] = (double)len;
+        }
+        double dtc = INFINITY;
+        if (live) dtc = cell_dt_bound<NV, PHYS>(u4, nrm, ar, fa.gamma64, (double)fa.ax, (double)fa.ay);
+        // with a share of part 0's minima, so that the step control has only
+        // these blocks' to reduce
+        const int64_t per = (n_groups + gridDim.x - 1) / gridDim.x;
+        const int64_t p1 = min(n_groups, per * (blockIdx.x + 1));
+        for (int64_t p = per * blockIdx.x + threadIdx.x; p < p1; p += 256) dtc = fmin(dtc, fa.dt_part[fa.part_off + p]);
+        const double bm = block_min(dtc);
+        if (threadIdx.x == 0) fa.dt_part[blockIdx.x] = bm;
+    }
+}
+
 template <typename real, int R, int NV, int VARS, int PHYS>
-static void stage_launch(const DeviceMesh &m, const ReconArgs<real, (R + 1) * (R + 2) / 2 - 1> &ra,
-                         const FluxArgs<real> &fa, unsigned grid, hipStream_t st) {
+static void stage_launch(const DeviceMesh &m, const ReconArgs<real> &ra, const ReconPtrs<real> &rp,
+                         const FluxArgs<real> &fa, hipStream_t st) {
+    const unsigned grid = (unsigned)m.groups();
 #define ST_LAUNCH(SCH, GF) \
-    hipLaunchKernelGGL((k_stage<real, R, NV, SCH, GF, VARS, PHYS>), dim3(grid), dim3(256), 0, st, ra, fa)
+    hipLaunchKernelGGL((k_stage<real, R, NV, SCH, GF, VARS, PHYS>), dim3(grid), dim3(256), m.row_bytes(), st, ra, rp, fa)
     if (m.scheme == CTENO_SCHEME_CTENOZ && m.gamma_form == CTENO_GAMMA_SCALED) ST_LAUNCH(CTENO_SCHEME_CTENOZ, CTENO_GAMMA_SCALED);
     else if (m.scheme == CTENO_SCHEME_CTENOZ) ST_LAUNCH(CTENO_SCHEME_CTENOZ, CTENO_GAMMA_PAPER);
     else if (m.scheme == CTENO_SCHEME_CWENO) ST_LAUNCH(CTENO_SCHEME_CWENO, CTENO_GAMMA_PAPER);
@@ -205,28 +319,27 @@ static void stage_launch(const DeviceMesh &m, const ReconArgs<real, (R + 1) * (R
 template <typename real, int R, int NV, int PHYS>
 static hipError_t stage_t(const DeviceMesh &m, const FluxLaunch &f, const int *done, hipStream_t st,
                           unsigned long long *fb_count) {
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    ReconArgs<real, K> ra;
-    ra.N = m.N;
-    ra.U = f.Us;
-    ra.slot = m.slot;
-    ra.flags = m.flags;
-    if constexpr (std::is_same<real, double>::value) { ra.P = m.P64; ra.fr = m.fr64; }
-    else { ra.P = m.P32; ra.fr = m.fr32; }
-    if (!ra.P || !ra.fr) return hipErrorInvalidValue;
-    ra.FV = nullptr;
-    ra.delta = nullptr;
-    ra.done = done;
-    fill_recon_constants<real, K>(m, ra);
-    ra.fb_count = fb_count;
+    if (m.E != QuadDims<R>::E || m.SP != QuadDims<R>::SP) return hipErrorInvalidValue;
+    ReconArgs<real> ra;
+    fill_recon_constants<real>(m, ra);
+    ReconPtrs<real> rp{};
+    rp.U = f.Us;
+    rp.lslot = m.lslot;
+    rp.desc = m.desc;
+    rp.hlist = m.hlist;
+    rp.flags = m.flags;
+    if constexpr (std::is_same<real, double>::value) { rp.P = m.P64; rp.fr = m.fr64; }
+    else { rp.P = m.P32; rp.fr = m.fr32; }
+    rp.fb = fb_count;
+    rp.done = done;
     FluxArgs<real> fa;
     fill_flux_args<real>(m, f, fa);
-    const unsigned grid = (unsigned)m.blocks();
+    if (!rp.P || !rp.fr || !ra.tab || !fa.frec || !fa.xid || !rp.lslot || !rp.desc || !rp.hlist) return hipErrorInvalidValue;
     if (m.vars == CTENO_VARS_CHARACTERISTIC) {
-        if constexpr (NV == 4) stage_launch<real, R, NV, 1, PHYS>(m, ra, fa, grid, st);
+        if constexpr (NV == 4) stage_launch<real, R, NV, 1, PHYS>(m, ra, rp, fa, st);
         else return hipErrorInvalidValue;
     } else {
-        stage_launch<real, R, NV, 0, PHYS>(m, ra, fa, grid, st);
+        stage_launch<real, R, NV, 0, PHYS>(m, ra, rp, fa, st);
     }
     return hipGetLastError();
 }
@@ -234,18 +347,20 @@ static hipError_t stage_t(const DeviceMesh &m, const FluxLaunch &f, const int *d
 template <typename real>
 hipError_t stage_fused(const DeviceMesh &m, const FluxLaunch &f, const int *done, int part, hipStream_t st,
                        unsigned long long *fb_count) {
-    if (f.mode != 2 || m.r > 3 || m.tab.Nq != 2 || !f.xpart || !f.FV) return hipErrorInvalidValue;
-    const void *xfr = std::is_same<real, double>::value ? (const void *)m.xfr64 : (const void *)m.xfr32;
-    if (m.n_cross && (!m.xcells || !m.xbase || !m.xnb || !m.xarea || !xfr)) return hipErrorInvalidValue;
+    if (f.mode != 2 || m.r > 3 || m.tab.Nq != 2 || !m.fused || !f.FV) return hipErrorInvalidValue;
+    const void *xrec = std::is_same<real, double>::value ? (const void *)m.xrec64 : (const void *)m.xrec32;
+    if (m.n_cross && (!m.xcells || !m.xarea || !xrec ||
+                      (std::is_same<real, float>::value && !f.xterm)))
+        return hipErrorInvalidValue;
     if (part == 1) {
         if (m.n_cross == 0) return hipSuccess;
         FluxArgs<real> fa;
         fill_flux_args<real>(m, f, fa);
         const unsigned grid = (unsigned)m.cross_blocks();
         if (m.physics == CTENO_EULER)
-            hipLaunchKernelGGL((k_stage_cross<real, 4, CTENO_EULER>), dim3(grid), dim3(256), 0, st, fa);
+            hipLaunchKernelGGL((k_stage_cross<real, 4, CTENO_EULER>), dim3(grid), dim3(256), 0, st, fa, m.groups());
         else
-            hipLaunchKernelGGL((k_stage_cross<real, 1, CTENO_ADVECTION>), dim3(grid), dim3(256), 0, st, fa);
+            hipLaunchKernelGGL((k_stage_cross<real, 1, CTENO_ADVECTION>), dim3(grid), dim3(256), 0, st, fa, m.groups());
         return hipGetLastError();
     }
     if (m.physics == CTENO_EULER) {

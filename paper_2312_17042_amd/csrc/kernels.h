@@ -30,6 +30,8 @@
 // one neighbour touches one cache line.
 #pragma once
 
+#include <algorithm>
+
 #include "cteno_internal.h"
 
 namespace cteno {
@@ -40,44 +42,59 @@ struct DeviceMesh {
     int scheme = 0, gamma_form = 0, precision = 0;
     int positivity = 0;            // 1: cell-average fallback for non-physical face states
     int vars = 0;                  // CTENO_VARS_CONSERVED | CTENO_VARS_CHARACTERISTIC
-    int E64 = 0, E32 = 0;          // pseudo-inverse entries per cell (padded to the vector width)
+    int E = 0;                     // pseudo-inverse entries per cell
     int Kd = 0, Md = 0, Nq = 2;    // directional basis size and members, Gauss points per face
     int stile = 64;                // cells per stream tile (r >= 4: 64 / nv)
     double gamma = 1.4, ax = 0, ay = 0, lam1p = 1e4, ct = 1e-6, eps = 1e-12;
     double Lx = 0, Ly = 0;
-    int32_t *slot = nullptr;       // vector-tiled [SP], VW 4
+    int32_t *slot = nullptr;       // vector-tiled [SP], VW 4 (r <= 3: while the mesh is uploaded)
+    // r <= 3: the stencil entries as rows of the cell's group of 64 cells
+    // (lslot_index): row < 64 a cell of the group, row - 64 a place in the
+    // group's list of cells outside it
+    uint16_t *lslot = nullptr;     // [Np][row_entries(r)]
+    int4 *desc = nullptr;          // [groups()] (first place in hlist, its length, first listed face, their number)
+    int32_t *hlist = nullptr;
+    int max_halo = 0;              // the longest list
     uint8_t *flags = nullptr;      // [Np]
     double *fr64 = nullptr;        // face records, vector-tiled [12], VW 2
     float *fr32 = nullptr;         // face records, vector-tiled [12], VW 4
     double *area = nullptr;        // [Np]
-    double *P64 = nullptr;         // pseudo-inverse stream, vector-tiled [E64], VW 2
-    float *P32 = nullptr;          // pseudo-inverse stream, vector-tiled [E32], VW 4
+    double *P64 = nullptr;         // pseudo-inverse stream [Np][E] (r <= 3 quad_index, else hvix; VW 2)
+    float *P32 = nullptr;          // pseudo-inverse stream [Np][E] (VW 4)
     int32_t *perm = nullptr;       // internal -> user [N]
     double *bface = nullptr;       // [n_inflow][4]: first vertex and edge vector of each inflow face
     int64_t n_inflow = 0;
     double bst[2][4] = {};         // inflow states behind / ahead of the moving line
     double bline[3] = {};          // x = bline[0] + bline[1] y + bline[2] t
-    double *htab64 = nullptr;      // r >= 4: Gram matrix [K][K] and face basis [3][Nq][K], FP64
-    float *htab32 = nullptr;       // the same in FP32
+    double *htab64 = nullptr;      // Gram matrix [K][K] and face basis [3][Nq][K], FP64
+    float *htab32 = nullptr;       // the same in FP32 (r <= 3: off-diagonal Gram entries above the diagonal doubled)
     RefTables tab;
-    // fused stage (degree <= 3): cells with a face whose neighbour lies in
-    // another 256-cell block ("cross cells"), ascending; per cross cell (in
-    // that order) the cross index of the neighbour across each face, -1
-    // where the face stays in the block or is a boundary, its area and its
-    // face records (tiled like fr32 / fr64); per block the number of cross
-    // cells in the blocks before it
-    int32_t *xcells = nullptr;
-    int64_t n_cross = 0;
-    int32_t *xbase = nullptr;      // [blocks() + 1]
-    int32_t *xnb = nullptr;        // [n_cross][3]
-    double *xarea = nullptr;       // [n_cross]
-    float *xfr32 = nullptr;        // [pad64(n_cross)][12], VW 4
-    double *xfr64 = nullptr;       // [pad64(n_cross)][12], VW 2
+    // fused stage (degree <= 3), a group of 64 cells per block: the faces that
+    // the block evaluates alone (its boundary faces and the faces between two
+    // of its cells, once, from their owner), and the cells with a face to
+    // another group ("cross cells") with one record per such face ("side")
+    float *frec32 = nullptr;       // [faces][4] normal, length, block face code (kBf*)
+    double *frec64 = nullptr;      // the same in FP64
+    uint32_t *xid = nullptr;       // [Np] the cell's first side | its faces to other groups << 28 (0: none)
+    int2 *xcells = nullptr;        // [n_cross] cross cells, ascending, and their xid
+    double *xarea = nullptr;       // [n_cross] their areas
+    float *xrec32 = nullptr;       // [n_sides][4] normal, length, the other side | kNbOwner | kSideFar
+    double *xrec64 = nullptr;      // the same in FP64
+    int64_t n_cross = 0, n_sides = 0;
+    int64_t n_cross256 = 0;        // cells with a face to another 256-cell block
     bool fused = false;            // the march runs the fused stage kernels
     int64_t blocks() const { return (N + 255) / 256; }
-    int64_t cross_blocks() const { return (n_cross + 255) / 256; }
-    // per-block CFL minima of one march step: both stage kernels' blocks
-    int64_t dt_parts() const { return blocks() + (fused ? cross_blocks() : 0); }
+    int64_t groups() const { return Np / 64; }
+    // LDS rows of one group
+    size_t row_bytes() const { return (size_t)(64 + max_halo) * nv * sizeof(double); }
+    int64_t cross_blocks() const { return (n_cross + 63) / 64; }
+    // Per-block CFL minima of one march step that the control reduces: the
+    // fused stage's second kernel's (which fold in the first kernel's, stored
+    // behind them), or the only kernel's
+    int64_t dt_parts(bool fused_run) const {
+        return !fused_run ? blocks() : n_cross ? cross_blocks() : groups();
+    }
+    int64_t dt_storage() const { return std::max(blocks(), groups() + cross_blocks()); }
     // selection bytes per cell: per variable, or per face and characteristic field
     int delta_bytes() const { return vars == CTENO_VARS_CHARACTERISTIC ? 3 * nv : nv; }
 };
@@ -122,35 +139,48 @@ struct FluxLaunch {
     int *nonphys = nullptr;      // non-physical flag when ctrl is null (may be null)
     double *dt_part = nullptr;   // per-block minima of the CFL bound (stage 2 of a march), or null
     double t_base = 0.0;         // time of the stage input when the march time is not on the device
-    // fused stage: [n_cross][nv] stage states of the cross cells from their
-    // faces inside the block (the faces to other blocks still to add)
-    double *xpart = nullptr;
+    void *xterm = nullptr;       // FP32 fused stage: [2 n_sides][nv] floats, the cross cells' other terms
 };
 hipError_t launch_flux(const DeviceMesh &m, bool fp32, const FluxLaunch &f, hipStream_t st);
 
+// Block data of the fused stage from the face records on the device, in two
+// steps: the counts per group (listed faces, cross cells, sides) and the number
+// of cells with a face to another 256-cell block; then, with the groups'
+// first listed face in desc and their offsets (exclusive sums of the counts),
+// the lists.
+struct BlockCounts {
+    int32_t *faces, *cross, *sides;    // [groups()]
+    int32_t *cross256;                 // one counter
+};
+hipError_t launch_block_counts(const DeviceMesh &m, const BlockCounts &c, hipStream_t st);
+hipError_t launch_block_lists(const DeviceMesh &m, const int32_t *xbase, const int32_t *sbase, hipStream_t st);
+
 // Fused SSP-RK3 stage of degree <= 3 (f.mode 2): part 0 reconstructs each
-// 256-cell block into LDS, evaluates the faces inside the block and updates
-// the cells whose faces all lie inside it; the others store the values of
-// their faces to other blocks (f.FV, by cross index) and their partial stage
-// states (f.xpart), and part 1 finishes them with the faces to other
-// blocks.  The two parts are launched in order, 0 then 1.
+// group of 64 cells into LDS, evaluates the faces inside the group and updates
+// the cells whose faces all lie inside it; part 1 evaluates the faces between
+// groups, whose values part 0 leaves in f.FV ([n_sides][2][nv]), and updates
+// their cells with the other faces' terms (f.xterm).  The two parts are launched in
+// order, 0 then 1.
 hipError_t launch_stage(const DeviceMesh &m, bool fp32, const FluxLaunch &f, const int *done, int part,
                         hipStream_t st, unsigned long long *fb_count);
 template <typename real>
 hipError_t stage_fused(const DeviceMesh &m, const FluxLaunch &f, const int *done, int part, hipStream_t st,
                        unsigned long long *fb_count);     // k_stage_f32.hip, k_stage_f64.hip
 
-// per-block minima of the CFL bound of state U into dt_part[blocks()], from the
-// face records of the stage kernels' precision (fp32) so a march's first step
+// minima of the CFL bound of state U over n_part shares of the cells into
+// dt_part[n_part], from the face records of the stage kernels' precision (fp32) so a march's first step
 // uses the same geometry as its later steps
-hipError_t launch_dt_partials(const DeviceMesh &m, bool fp32, const double *U, double *dt_part, hipStream_t st);
+hipError_t launch_dt_partials(const DeviceMesh &m, bool fp32, const double *U, double *dt_part, int64_t n_part,
+                              hipStream_t st);
 // step control; reduces dt_part[n_part] unless commit_only
 hipError_t launch_control(Ctrl *ctrl, const double *dt_part, int64_t n_part, int commit_only, hipStream_t st);
 
 // device descriptor of one active serving slot (one independent solve)
 struct BatchSlot {
     int64_t N, block0, nblocks;     // cells; first global block; blocks of 256 cells
-    const int32_t *slot;
+    const uint16_t *lslot;
+    const int4 *desc;
+    const int32_t *hlist;
     const uint8_t *flags;
     const float *P;                 // FP32 pseudo-inverse stream
     const float *fr;                // FP32 face records
@@ -163,8 +193,14 @@ struct BatchSlot {
 // one SSP-RK3 step (control + 3 x (reconstruction, flux/RK)) of every slot in
 // tab[0 .. *n_slots); grids of max_slots and max_blocks blocks (blocks past the
 // active range exit at once).  FP32 reconstruction/flux, Euler, r = 2 or 3.
+// proto.max_halo: the longest neighbour list of a group that a slot may have.
 hipError_t launch_batch_step(const DeviceMesh &proto, const BatchSlot *tab, const int *n_slots, int max_slots,
                              int64_t max_blocks, hipStream_t st);
+
+// neighbour lists of the 64-cell groups: their lengths into len[groups()], then
+// (their places set in m.desc) the lists and the stencil entries as rows
+hipError_t launch_halo_counts(const DeviceMesh &m, int32_t *len, hipStream_t st);
+hipError_t launch_halo_lists(const DeviceMesh &m, hipStream_t st);
 
 // layout conversions between caller order/layout and internal order/layout
 hipError_t launch_user_to_state(const DeviceMesh &m, const double *user, double *state, hipStream_t st);
@@ -176,6 +212,7 @@ hipError_t launch_delta_to_user(const DeviceMesh &m, const uint8_t *d, uint8_t *
 hipError_t launch_delta_from_user(const DeviceMesh &m, const uint8_t *user, uint8_t *d, hipStream_t st);
 hipError_t launch_count_diff(const DeviceMesh &m, const uint8_t *a, const uint8_t *b, unsigned long long *count,
                              hipStream_t st);
+hipError_t launch_fill_u32(uint32_t *p, uint32_t v, size_t n, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, size_t n, hipStream_t st);
 
 // Fixed device scratch of the allocation-free entry point (one array per
@@ -188,9 +225,10 @@ constexpr int kMaxDevices = 64;
 hipError_t scratch_init(int device);
 void *scratch_device_ptr(int device);
 hipError_t launch_copy16(void *dst, const void *src, size_t n16, hipStream_t st);
-// dst[a][e] = src[avix(idx[a], e, E, VW)] (ct = 64) or src[hvix(idx[a], e, E, VW, ct)]
-// from exactly one of src64 / src32 / srci
-hipError_t launch_gather_entries(int n, const int32_t *idx, int E, int VW, const double *src64, const float *src32,
-                                 const int32_t *srci, double *dst, hipStream_t st, int ct = 64);
+// dst[a][e] = entry e of cell idx[a] of the pseudo-inverse stream (exactly one of
+// src64 / src32; entries in pinv_offset's order at r <= 3), or of the slot
+// table (srci, E = SP)
+hipError_t launch_gather_entries(const DeviceMesh &m, int n, const int32_t *idx, int E, const double *src64,
+                                 const float *src32, const int32_t *srci, double *dst, hipStream_t st);
 
 }  // namespace cteno

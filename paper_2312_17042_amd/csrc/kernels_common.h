@@ -138,41 +138,6 @@ __device__ __forceinline__ real pow6(real x) {
     return x2 * x2 * x2;
 }
 
-// d[v] = U[m][v] - U0[v], rounded to the working precision
-template <int NV, typename real>
-__device__ __forceinline__ void gather_diff(const double *__restrict__ U, int64_t m, const double *U0, real *d) {
-    if constexpr (NV == 4) {
-        const double2 u01 = reinterpret_cast<const double2 *>(U)[2 * m];
-        const double2 u23 = reinterpret_cast<const double2 *>(U)[2 * m + 1];
-        d[0] = (real)(u01.x - U0[0]); d[1] = (real)(u01.y - U0[1]);
-        d[2] = (real)(u23.x - U0[2]); d[3] = (real)(u23.y - U0[3]);
-    } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) d[v] = (real)(U[m * NV + v] - U0[v]);
-    }
-}
-
-template <typename real, int K>
-struct ReconArgs {
-    int64_t N;
-    const double *U;        // AoS [Np][NV]
-    const int32_t *slot;    // vector-tiled [SP], VW 4
-    const uint8_t *flags;   // [Np]
-    const real *P;          // vector-tiled pseudo-inverse stream
-    real *FV;               // AoS [Np][3][2][NV]
-    uint8_t *delta;         // AoS [Np][NV] (characteristic variables: [Np][3][NV])
-    const int *done;
-    const real *fr;         // face records (characteristic variables)
-    real gram[K][K];
-    real basis[3][2][K];
-    real lam1, ct, eps;
-    real lams[5];           // lambda_s for s_t = 2, 3, 4 (index s_t)
-    real gamma;             // ratio of specific heats (positivity check)
-    real lam_ratio[5];      // lambda_1 / lambda_s (index s_t)
-    int positivity;         // 1: cell-average fallback for non-physical face states
-    unsigned long long *fb_count;   // cells that took the fallback (may be null)
-};
-
 // TENO selection bits for one variable: bit 0 central, bit 1+s directional s.
 // FP64 follows Algorithms 1/2 literally; FP32 evaluates the same chi_s
 // through ratios that cannot overflow (gamma_s reaches 1e72 in FP64 terms).
@@ -317,564 +282,6 @@ __device__ __forceinline__ void cweno_weights(const real si[4], int adm, real la
     }
 }
 
-// per-mesh arrays of one reconstruction (the constants stay in ReconArgs)
-template <typename real>
-struct ReconPtrs {
-    const double *U;
-    const int32_t *slot;
-    const uint8_t *flags;
-    const real *P;
-    real *FV;
-    uint8_t *delta;
-    const real *fr;         // face records (characteristic variables only)
-    unsigned long long *fb; // cells that took the positivity fallback (may be null)
-    const real *tab;        // the block's LDS copy of the Gram matrix [K][K] and face basis [3][2][K]
-    double *lad;            // FP64: the block's LDS space for directional coefficients, [3][2][NV] x 256
-};
-
-// Entries of the reconstruction's constant table (Gram matrix, then face
-// basis values) and its LDS copy: lane 0 of the block writes it from the
-// kernel arguments; the caller synchronises the block before use.  In LDS
-// the FP32 constants cost no scalar registers in the epilogue, where they
-// would not fit beside the kernel's other scalars (FP64 and characteristic
-// variables read them from the arguments: as vector registers they would
-// cost a wave).
-template <int K>
-constexpr int recon_tab_size() { return K * K + 6 * K; }
-template <typename real, int K>
-__device__ __forceinline__ void recon_tab_fill(const ReconArgs<real, K> a, real *tab) {
-    if (std::is_same<real, float>::value && threadIdx.x == 0) {
-#pragma unroll
-        for (int p = 0; p < K; ++p)
-#pragma unroll
-            for (int q = 0; q < K; ++q) tab[p * K + q] = a.gram[p][q];
-#pragma unroll
-        for (int f = 0; f < 3; ++f)
-#pragma unroll
-            for (int q = 0; q < 2; ++q)
-#pragma unroll
-                for (int k = 0; k < K; ++k) tab[K * K + (f * 2 + q) * K + k] = a.basis[f][q][k];
-    }
-}
-
-// selection (or CWENO weights) of NV fields and their final coefficients,
-// in place: c1[K][NV] holds the p_1 coefficients on entry and the final
-// polynomial's on exit, cd[3][2][NV] the degree-1 directional ones; forced
-// (DMODE 2) points at the fields' forced selection bytes
-template <typename real, int K, int NV, int SCHEME, int GFORM, int DMODE, bool LT, typename CD>
-__device__ __forceinline__ void finish_fields(const ReconArgs<real, K> a, const real *tab, real (&c1)[K][NV],
-                                              const CD cd, int fl, int adm, int st, real lams, real lratio,
-                                              const uint8_t *forced, int (&bits)[NV]) {
-    if (DMODE == 2 && SCHEME != CTENO_SCHEME_CWENO) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) bits[v] = forced[v] & adm;
-    } else if (st == 1) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) bits[v] = 1;
-    } else {
-        // smoothness indicators: SI_1 = a1^T G a1, SI_s over the degree-1 block
-        // of G.  FP64 sums the full quadratic form; FP32 its upper triangle,
-        // whose off-diagonal entries the FP32 table holds doubled
-        // (fill_recon_constants), at about half the products.
-        constexpr bool SYM = std::is_same<real, float>::value;
-        real si[NV][4];
-#pragma unroll
-        for (int v = 0; v < NV; ++v) si[v][0] = 0;
-#pragma unroll
-        for (int p = 0; p < K; ++p) {
-            real rowp[NV];
-#pragma unroll
-            for (int v = 0; v < NV; ++v) rowp[v] = 0;
-#pragma unroll
-            for (int q = SYM ? p : 0; q < K; ++q) {
-                const real g = LT ? tab[p * K + q] : a.gram[p][q];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) rowp[v] += g * c1[q][v];
-            }
-#pragma unroll
-            for (int v = 0; v < NV; ++v) si[v][0] += c1[p][v] * rowp[v];
-        }
-        const real g00 = LT ? tab[0] : a.gram[0][0], g01 = LT ? tab[1] : a.gram[0][1];
-        const real g10 = LT ? tab[K] : a.gram[1][0], g11 = LT ? tab[K + 1] : a.gram[1][1];
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                const real x0 = cd(q, 0, v), x1 = cd(q, 1, v);
-                if constexpr (SYM) si[v][q + 1] = x0 * (g00 * x0 + g01 * x1) + g11 * (x1 * x1);
-                else si[v][q + 1] = x0 * (g00 * x0 + g01 * x1) + x1 * (g10 * x0 + g11 * x1);
-            }
-        if constexpr (SCHEME == CTENO_SCHEME_CWENO) {
-            // every admissible stencil contributes; final coefficients, in
-            // place: sum_s omega_s p_s
-#pragma unroll
-            for (int v = 0; v < NV; ++v) {
-                bits[v] = adm;
-                real w[4];
-                cweno_weights<real>(si[v], adm, lams, a.lam1, lratio, a.eps, w);
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    real x = w[0] * c1[k][v];
-                    if (k < 2) {
-#pragma unroll
-                        for (int q = 0; q < 3; ++q)
-                            if ((fl >> q) & 1) x += w[q + 1] * cd(q, k, v);
-                    }
-                    c1[k][v] = x;
-                }
-            }
-        } else {
-            constexpr int SEL = SCHEME == CTENO_SCHEME_TENO ? CTENO_SCHEME_CTENO : SCHEME;
-            constexpr int SGF = SCHEME == CTENO_SCHEME_TENO ? CTENO_GAMMA_PAPER : GFORM;
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                bits[v] = teno_bits<real, SEL, SGF>(si[v], adm, st, a.lam1, lams, lratio, a.ct, a.eps);
-        }
-    }
-    // final coefficients, in place: p_1, or the mean of the selected
-    // directional polynomials
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (SCHEME != CTENO_SCHEME_CWENO && !(bits[v] & 1)) {
-            real s0 = 0, s1 = 0;
-            int cnt = 0;
-#pragma unroll
-            for (int q = 0; q < 3; ++q)
-                if ((bits[v] >> (q + 1)) & 1) { s0 += cd(q, 0, v); s1 += cd(q, 1, v); ++cnt; }
-            c1[0][v] = cnt == 1 ? s0 : cnt == 2 ? (real)0.5 * s0 : fdiv(s0, (real)3);
-            c1[1][v] = cnt == 1 ? s1 : cnt == 2 ? (real)0.5 * s1 : fdiv(s1, (real)3);
-#pragma unroll
-            for (int k = 2; k < K; ++k) c1[k][v] = 0;
-        }
-    }
-}
-
-// the degree-1 directional coefficients cd(q, c, v) of a cell: in registers,
-// or parked in LDS (FP64 reconstruction: the kernel provides [3][2][NV] x
-// 256 doubles of block-shared space, one column per lane)
-template <typename real, int NV>
-struct CdRegs {
-    const real (&a)[3][2][NV];
-    __device__ __forceinline__ real operator()(int q, int c, int v) const { return a[q][c][v]; }
-};
-template <int NV>
-struct CdLds {
-    const double *p;
-    __device__ __forceinline__ double operator()(int q, int c, int v) const {
-        return p[((q * 2 + c) * NV + v) * 256 + threadIdx.x];
-    }
-};
-
-// Reconstruction of cell i: its face Gauss-point values in out (and its
-// selection bytes, DMODE 1); the caller stores them
-template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS>
-__device__ __forceinline__ void recon_body(const ReconArgs<real, (R + 1) * (R + 2) / 2 - 1> a,
-                                           const ReconPtrs<real> ptr, int64_t i, real (&out)[3][2][NV]) {
-    // a and ptr by value: a reference to the kernel-argument struct would make
-    // the compiler copy it to scratch memory
-    constexpr int K = (R + 1) * (R + 2) / 2 - 1;
-    constexpr int M = 2 * K;
-    constexpr int S = M > 12 ? M : 12;
-    constexpr int SP = (S + 3) / 4 * 4;
-    using V = typename Vec<real>::T;
-    constexpr int VW = Vec<real>::W;
-    constexpr int E = (pinv_offset(S, K) + VW - 1) / VW * VW;
-
-    // this cell's streams: vector g of the pseudo-inverse at Pv[g * 64]
-    const V *__restrict__ Pv = reinterpret_cast<const V *>(ptr.P) + (size_t)(i >> 6) * (E / VW) * 64 + (i & 63);
-    const int4 *__restrict__ Sv = reinterpret_cast<const int4 *>(ptr.slot) + (size_t)(i >> 6) * (SP / 4) * 64 + (i & 63);
-
-    double U0[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) U0[v] = ptr.U[i * NV + v];
-
-    real ao[K][NV], ad[3][2][NV];
-    // FP64: the directional coefficients wait in LDS until the epilogue
-    // (registers for two waves per SIMD); 256 lanes per block
-    constexpr bool AD_LDS = std::is_same<real, double>::value;
-    // FP32 in conserved variables reads the scheme constants from the block's
-    // LDS table; the others from the arguments (their epilogues would hold
-    // the loaded constants in vector registers and lose a wave per SIMD)
-    constexpr bool LTAB = std::is_same<real, float>::value && VARS == 0;
-    double *const lad = ptr.lad;
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ao[k][v] = 0;
-#pragma unroll
-    for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-            for (int v = 0; v < NV; ++v) ad[s][c][v] = 0;
-
-    // a_opt = P_c d and a_s = P_s d.  Slots 4s..4s+3 (directional group s)
-    // hold K central and 2 directional entries each: 4 (K + 2) entries, a
-    // whole number of vectors, loaded at once per group; then the remaining
-    // slots with K central entries each.
-    constexpr int GE = 4 * (K + 2);
-    constexpr int GV = GE / VW;
-    // all slot indices up front, so each group's gathers issue with its loads
-    int4 slv[SP / 4];
-#pragma unroll
-    for (int g = 0; g < SP / 4; ++g) slv[g] = Sv[g * 64];
-    constexpr int NVEC = E / VW;
-    if constexpr (AD_LDS) {
-        // FP64: half a group of stream vectors in flight per wave, loaded at
-        // the top of its part, and the directional coefficients parked in
-        // LDS, so that two waves fit on a SIMD
-#pragma unroll 1
-        for (int s = 0; s < 3; ++s) {
-            int4 sl = slv[0];
-#pragma unroll
-            for (int s2 = 1; s2 < 3; ++s2)
-                if (s2 == s) sl = slv[s2];
-            real adt[2][NV];
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) adt[c][v] = 0;
-            // the group in two halves of two slots (whole vectors)
-            constexpr int PARTS = (GE / 2) % VW == 0 ? 2 : 1;
-            constexpr int PVEC = GV / PARTS, PT = 4 / PARTS;
-#pragma unroll
-            for (int h = 0; h < PARTS; ++h) {
-                V cur[PVEC];
-#pragma unroll
-                for (int g = 0; g < PVEC; ++g) cur[g] = Pv[(s * GV + h * PVEC + g) * 64];
-#pragma unroll
-                for (int t = h * PT; t < (h + 1) * PT; ++t) {
-                    const int64_t m = comp(sl, t);
-                    real d[NV];
-                    gather_diff<NV>(ptr.U, m, U0, d);
-#pragma unroll
-                    for (int q = 0; q < K + 2; ++q) {
-                        const int el = t * (K + 2) + q - h * PVEC * VW;
-                        const real p = comp(cur[el / VW], el % VW);
-                        if (q < K) {
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) ao[q][v] += p * d[v];
-                        } else {
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) adt[q - K][v] += p * d[v];
-                        }
-                    }
-                }
-                if (PARTS > 1) __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) lad[((s * 2 + c) * NV + v) * 256 + threadIdx.x] = adt[c][v];
-            __builtin_amdgcn_sched_barrier(0);   // keep the groups apart: bounded live registers
-        }
-        if constexpr (S > 12) {
-            // remaining slots (K central entries each), from stream vector 3 GV
-            // on, in parts of at most three slots
-            constexpr int T0 = 12 * (K + 2);
-            constexpr int NT = S - 12;
-#pragma unroll
-            for (int t0 = 0; t0 < NT; t0 += 3) {
-                constexpr int PV = (3 * K + 2 * VW - 2) / VW;     // vectors that three slots can touch
-                const int v0 = (T0 + t0 * K) / VW;
-                V buf[PV];
-#pragma unroll
-                for (int g = 0; g < PV; ++g)
-                    if (v0 + g < NVEC) buf[g] = Pv[(v0 + g) * 64];
-#pragma unroll
-                for (int t = t0; t < t0 + 3 && t < NT; ++t) {
-                    const int j = 12 + t;
-                    const int64_t m = comp(slv[j / 4], j % 4);
-                    real d[NV];
-                    gather_diff<NV>(ptr.U, m, U0, d);
-#pragma unroll
-                    for (int q = 0; q < K; ++q) {
-                        const int e = T0 + t * K + q;
-                        const real p = comp(buf[e / VW - v0], e % VW);
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) ao[q][v] += p * d[v];
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    } else {
-        // Rolled loop over the three directional groups with a two-deep load
-        // pipeline: the GV vectors that follow group s (group s + 1, or the head
-        // of the remaining slots) are requested before group s is computed, so a
-        // wave keeps two groups of stream loads in flight.  With no remaining
-        // slots (S = 12) the last iteration requests its own group again.
-        static_assert(S == 12 || 4 * GV <= NVEC, "stream shorter than four groups");
-        V cur[GV];
-#pragma unroll
-        for (int g = 0; g < GV; ++g) cur[g] = Pv[g * 64];
-#pragma unroll 1
-        for (int s = 0; s < 3; ++s) {
-            int4 sl = slv[0];
-#pragma unroll
-            for (int s2 = 1; s2 < 3; ++s2)
-                if (s2 == s) sl = slv[s2];
-            const int gn = (S > 12 || s < 2 ? s + 1 : s) * GV;
-            V nxt[GV];
-#pragma unroll
-            for (int g = 0; g < GV; ++g) nxt[g] = Pv[(gn + g) * 64];
-            real adt[2][NV];
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int v = 0; v < NV; ++v) adt[c][v] = 0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int64_t m = comp(sl, t);
-                real d[NV];
-                gather_diff<NV>(ptr.U, m, U0, d);
-#pragma unroll
-                for (int q = 0; q < K + 2; ++q) {
-                    const int el = t * (K + 2) + q;
-                    const real p = comp(cur[el / VW], el % VW);
-                    if (q < K) {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) ao[q][v] += p * d[v];
-                    } else {
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) adt[q - K][v] += p * d[v];
-                    }
-                }
-            }
-#pragma unroll
-            for (int s2 = 0; s2 < 3; ++s2)
-                if (s2 == s)
-#pragma unroll
-                    for (int c = 0; c < 2; ++c)
-#pragma unroll
-                        for (int v = 0; v < NV; ++v) ad[s2][c][v] = adt[c][v];
-#pragma unroll
-            for (int g = 0; g < GV; ++g) cur[g] = nxt[g];
-            __builtin_amdgcn_sched_barrier(0);   // keep the groups apart: bounded live registers
-        }
-        if constexpr (S > 12) {
-            // remaining slots (K central entries each): cur holds stream vectors
-            // [3 GV, 4 GV); the rest of the stream follows
-            constexpr int T0 = 12 * (K + 2);
-            constexpr int NT = S - 12;
-            constexpr int RV = NVEC - 4 * GV;
-            V rest[RV > 0 ? RV : 1];
-#pragma unroll
-            for (int g = 0; g < RV; ++g) rest[g] = Pv[(4 * GV + g) * 64];
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const int j = 12 + t;
-                const int64_t m = comp(slv[j / 4], j % 4);
-                real d[NV];
-                gather_diff<NV>(ptr.U, m, U0, d);
-#pragma unroll
-                for (int q = 0; q < K; ++q) {
-                    const int e = T0 + t * K + q;
-                    const int gv = e / VW - 3 * GV;     // compile-time after unrolling
-                    const real p = gv < GV ? comp(cur[gv < GV ? gv : 0], e % VW)
-                                           : comp(rest[gv < GV ? 0 : gv - GV], e % VW);
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) ao[q][v] += p * d[v];
-                }
-            }
-        }
-    }
-    // the directional coefficients, wherever they wait
-    auto adv = [&](int q, int c, int v) -> real {
-        if constexpr (AD_LDS) return lad[((q * 2 + c) * NV + v) * 256 + threadIdx.x];
-        else return ad[q][c][v];
-    };
-    const int fl = ptr.flags[i] & 7;
-    const int adm = 1 | (fl << 1);
-    const int st = 1 + __popc(fl);
-    // static indices only: a dynamic index into the argument struct would
-    // force it into scratch memory
-    const real lams = st == 2 ? a.lams[2] : (st == 3 ? a.lams[3] : a.lams[4]);
-    const real lratio = st == 2 ? a.lam_ratio[2] : (st == 3 ? a.lam_ratio[3] : a.lam_ratio[4]);
-    // The epilogue works on all variables at once, phase by phase, so each
-    // scheme constant (Gram matrix, face basis values) is used once and
-    // dies, instead of staying live across a per-variable loop.
-    // p_1 = (p_opt - sum_s lambda_s p_s) / lambda_1, in place of a_opt, with
-    // one reciprocal of lambda_1
-    const real ilam1 = frcp(a.lam1);
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            real sm = ao[k][v];
-            if (k < 2 && st > 1) {
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-                    if ((fl >> q) & 1) sm -= lams * adv(q, k, v);
-            }
-            // TENO keeps the central stencil's own polynomial
-            if (SCHEME != CTENO_SCHEME_TENO) ao[k][v] = st > 1 ? sm * ilam1 : sm;
-        }
-    constexpr int NB = VARS ? 3 * NV : NV;       // selection bytes per cell
-    uint8_t dbyte[NB];
-    if constexpr (VARS == 0) {
-        int bits[NV];
-        if constexpr (AD_LDS)
-            finish_fields<real, K, NV, SCHEME, GFORM, DMODE, LTAB>(a, ptr.tab, ao, CdLds<NV>{lad}, fl, adm, st,
-                                                                   lams, lratio, ptr.delta + i * NV, bits);
-        else
-            finish_fields<real, K, NV, SCHEME, GFORM, DMODE, LTAB>(a, ptr.tab, ao, CdRegs<real, NV>{ad}, fl, adm,
-                                                                   st, lams, lratio, ptr.delta + i * NV, bits);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) dbyte[v] = (uint8_t)bits[v];
-        // face Gauss-point values
-#pragma unroll
-        for (int f = 0; f < 3; ++f)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                real val[NV];
-#pragma unroll
-                for (int v = 0; v < NV; ++v) val[v] = 0;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const real b = LTAB ? ptr.tab[K * K + (f * 2 + q) * K + k] : a.basis[f][q][k];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) val[v] += b * ao[k][v];
-                }
-#pragma unroll
-                for (int v = 0; v < NV; ++v) out[f][q][v] = (real)(U0[v] + (double)val[v]);
-            }
-    } else {
-        // characteristic fields per face: the least-squares coefficients are
-        // linear in the data, so projecting them with L_f equals
-        // reconstructing the projected averages W = L_f U; the face values
-        // are U_0 + R_f (W(x_q) - W_0)
-        static_assert(NV == 4, "characteristic variables need the Euler equations");
-        const real rho = (real)U0[0], uu = (real)(U0[1] / U0[0]), vv = (real)(U0[2] / U0[0]);
-        const real q2 = (real)0.5 * (uu * uu + vv * vv);
-        const real pr = (a.gamma - 1) * ((real)U0[3] - rho * q2);
-        const real cs = fsqrt(fdiv(a.gamma * pr, rho)), H = fdiv((real)U0[3] + pr, rho);
-        const real b1 = fdiv(a.gamma - 1, cs * cs), b2 = b1 * q2, ic = frcp(cs);
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
-            real nx, ny, len;
-            uint32_t code;
-            face_record<real>(ptr.fr, i, f, nx, ny, len, code);
-            const real un = uu * nx + vv * ny, ut = -uu * ny + vv * nx;
-            const real L[4][4] = {{(real)0.5 * (b2 + un * ic), (real)-0.5 * (b1 * uu + nx * ic),
-                                   (real)-0.5 * (b1 * vv + ny * ic), (real)0.5 * b1},
-                                  {1 - b2, b1 * uu, b1 * vv, -b1},
-                                  {-ut, -ny, nx, 0},
-                                  {(real)0.5 * (b2 - un * ic), (real)-0.5 * (b1 * uu - nx * ic),
-                                   (real)-0.5 * (b1 * vv - ny * ic), (real)0.5 * b1}};
-            const real Rm[4][4] = {{1, 1, 0, 1},
-                                   {uu - cs * nx, uu, -ny, uu + cs * nx},
-                                   {vv - cs * ny, vv, nx, vv + cs * ny},
-                                   {H - un * cs, q2, ut, H + un * cs}};
-            real c1[K][4], cd[3][2][4];
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    real x = 0;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) x += L[j][v] * ao[k][v];
-                    c1[k][j] = x;
-                }
-#pragma unroll
-            for (int s2 = 0; s2 < 3; ++s2)
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        real x = 0;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) x += L[j][v] * adv(s2, k, v);
-                        cd[s2][k][j] = x;
-                    }
-            int bits[4];
-            finish_fields<real, K, 4, SCHEME, GFORM, DMODE, false>(a, ptr.tab, c1, CdRegs<real, 4>{cd}, fl, adm, st,
-                                                                   lams, lratio, ptr.delta + (i * 3 + f) * 4, bits);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dbyte[f * 4 + j] = (uint8_t)bits[j];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                real w[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) w[j] = 0;
-#pragma unroll
-                for (int k = 0; k < K; ++k) {
-                    const real b = a.basis[f][q][k];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) w[j] += b * c1[k][j];
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    real x = 0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x += Rm[v][j] * w[j];
-                    out[f][q][v] = (real)(U0[v] + (double)x);
-                }
-            }
-        }
-    }
-    if constexpr (NV == 4) if (a.positivity) {
-        // optional positivity fallback (not in the paper): a cell with a
-        // non-physical state (density or pressure <= 0) at any of its Gauss
-        // points uses its cell average at all of them; reported with bit 7
-        // of its selection bytes and counted.  Without it the flux reports
-        // the state.
-        bool bad = false;
-#pragma unroll
-        for (int f = 0; f < 3; ++f)
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const real rho = out[f][q][0];
-                const real pr = euler_pressure(a.gamma, rho, out[f][q][1], out[f][q][2], out[f][q][3]);
-                bad |= !(rho > 0) || !(pr > 0);
-            }
-        if (bad) {
-#pragma unroll
-            for (int f = 0; f < 3; ++f)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) out[f][q][v] = (real)U0[v];
-#pragma unroll
-            for (int k = 0; k < NB; ++k) dbyte[k] |= 0x80;
-            if (ptr.fb) atomicAdd(ptr.fb, 1ull);
-        }
-    }
-    if (DMODE == 1) {
-#pragma unroll
-        for (int k = 0; k < NB; ++k) ptr.delta[i * NB + k] = dbyte[k];
-    }
-}
-
-
-// scheme constants of the reconstruction (tables of the reference triangle,
-// linear weights of eq. e18 for every admissible-stencil count)
-template <typename real, int K>
-inline void fill_recon_constants(const DeviceMesh &m, ReconArgs<real, K> &a) {
-    a.N = m.N;
-    // FP64: the Gram matrix; FP32: its upper triangle with the off-diagonal
-    // entries doubled (finish_fields sums the quadratic form over it), the
-    // lower triangle as is
-    constexpr bool sym = std::is_same<real, float>::value;
-    for (int p = 0; p < K; ++p)
-        for (int q = 0; q < K; ++q) a.gram[p][q] = (real)((sym && q > p ? 2.0 : 1.0) * m.tab.gram[p][q]);
-    for (int f = 0; f < 3; ++f)
-        for (int q = 0; q < 2; ++q)
-            for (int k = 0; k < K; ++k) a.basis[f][q][k] = (real)m.tab.basis[f][q][k];
-    const double lam1 = 1.0 - 1.0 / m.lam1p;
-    a.lam1 = (real)lam1;
-    a.gamma = (real)m.gamma;
-    a.ct = (real)m.ct;
-    a.eps = (real)m.eps;
-    a.positivity = m.positivity;
-    a.fb_count = nullptr;
-    for (int s = 0; s < 5; ++s) {
-        const double ls = s >= 2 ? (1.0 - lam1) / (s - 1) : 0.0;
-        a.lams[s] = (real)ls;
-        a.lam_ratio[s] = s >= 2 ? (real)(lam1 / ls) : (real)1;
-    }
-}
-
 template <int R>
 struct HoDims {
     static constexpr int K = (R + 1) * (R + 2) / 2 - 1;
@@ -900,9 +307,13 @@ struct HoDims {
 // ===========================================================================
 
 // HLLC with Roe-averaged signal speeds (sec. 2.7), in the face-normal frame
-// (u normal, w tangential velocity); F returned in the global frame.
-template <typename real>
-__device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, real nx, real ny, real *F) {
+// (u normal, w tangential velocity); F returned in the global frame.  The sum
+// H_l + H_r D of the Roe average is contracted by hand: ALT 0 leaves H_l
+// unrounded in it, 1 H_r D, 2 decides by `alt` (FP32 marches repeat their
+// results bit for bit only if each face keeps its own).
+template <typename real, int ALT = -1>
+__device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, real nx, real ny, real *F,
+                                     bool alt = false) {
     // one reciprocal per denominator, shared by the quotients over it
     const real rl = UL[0], rr = UR[0];
     const real irl = frcp(rl), irr = frcp(rr);
@@ -919,7 +330,14 @@ __device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, rea
     const real iD = frcp(1 + D);
     const real ut = (ul + ur * D) * iD;
     const real wt = (wl + wr * D) * iD;
-    const real Ht = (Hl + Hr * D) * iD;
+    real Hs;
+    if constexpr (ALT < 0) {
+        Hs = Hl + Hr * D;
+    } else {
+        const real h0 = __builtin_fmaf(irl, El + pl, Hr * D), h1 = __builtin_fmaf(Hr, D, Hl);
+        Hs = ALT == 2 ? (alt ? h1 : h0) : ALT == 1 ? h1 : h0;
+    }
+    const real Ht = Hs * iD;
     const real ct = fsqrt((g - 1) * (Ht - h * (ut * ut + wt * wt)));
     const real SL = fmin(ul - cl, ut - ct);
     const real SR = fmax(ur + cr, ut + ct);
@@ -986,7 +404,7 @@ __device__ __forceinline__ bool wall_flux(real g, const real *UL, real nx, real 
 
 template <typename real>
 struct FluxArgs {
-    int64_t N;
+    int64_t N, Np;
     const real *FV;
     const real *fr;         // face records (nx, ny, |A|, code), vector-tiled
     const double *area;
@@ -1010,17 +428,15 @@ struct FluxArgs {
     double gq[4];           // Gauss nodes on [0, 1]
     double t_base;          // time of the stage input when tctrl is null
     const Ctrl *tctrl;      // time march: the stage input's time is tctrl->t, its step *dt_ptr
-    // fused stage: cells with a face whose neighbour lies in another
-    // 256-cell block (cross cells) finish in a second kernel from their
-    // partial stage states; their data in cross-cell order
-    double *xpart;          // [n_cross][NV] stage states from the faces inside the block
-    const int32_t *xcells;  // the cross cells, ascending
+    // fused stage (DeviceMesh)
+    const real *frec;       // records of the blocks' listed faces
+    const uint32_t *xid;    // [Np] first side | the faces to other groups << 28
+    const int2 *xcells;     // cross cells and their xid
+    const double *xarea;
+    const real *xrec;       // [n_sides] side records
+    real *xterm;            // [2 n_sides][NV] a cross cell's terms from faces inside its group, at its first side
     int64_t n_cross;
-    const int32_t *xbase;   // [blocks + 1] cross cells before each block
-    const int32_t *xnb;     // [n_cross][3] the neighbour's cross index across a face to another block, else -1
-    const double *xarea;    // [n_cross]
-    const real *xfr;        // [n_cross] face records, tiled like fr
-    int64_t part_off;       // offset of the second kernel's block minima in dt_part
+    int64_t part_off;       // the first kernel's minima in dt_part, behind the second kernel's
 };
 
 // the launch arguments of a flux / residual / RK stage (MODE f.mode)
@@ -1028,6 +444,7 @@ template <typename real>
 inline void fill_flux_args(const DeviceMesh &m, const FluxLaunch &f, FluxArgs<real> &a) {
     a = FluxArgs<real>{};
     a.N = m.N;
+    a.Np = m.Np;
     a.FV = (const real *)f.FV;
     if constexpr (std::is_same<real, double>::value) a.fr = m.fr64;
     else a.fr = m.fr32;
@@ -1050,15 +467,14 @@ inline void fill_flux_args(const DeviceMesh &m, const FluxLaunch &f, FluxArgs<re
     for (int q = 0; q < 4; ++q) a.gq[q] = q < m.tab.Nq ? m.tab.gq[q] : 0.0;
     a.t_base = f.t_base;
     a.tctrl = f.ctrl && f.dt_ptr ? f.ctrl : nullptr;
-    a.xpart = f.xpart;
     a.xcells = m.xcells;
     a.n_cross = m.n_cross;
-    a.xbase = m.xbase;
-    a.xnb = m.xnb;
+    a.xid = m.xid;
     a.xarea = m.xarea;
-    if constexpr (std::is_same<real, double>::value) a.xfr = m.xfr64;
-    else a.xfr = m.xfr32;
-    a.part_off = m.blocks();
+    a.xterm = (real *)f.xterm;
+    if constexpr (std::is_same<real, double>::value) { a.xrec = m.xrec64; a.frec = m.frec64; }
+    else { a.xrec = m.xrec32; a.frec = m.frec32; }
+    a.part_off = m.cross_blocks();     // (no cross cells: the first kernel's minima are the last)
 }
 
 template <int NV, int PHYS>
@@ -1134,6 +550,31 @@ __device__ __forceinline__ bool boundary_state(const FluxArgs<real> a, const dou
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
             for (int v = 0; v < NV; ++v) oth[NQ - 1 - q][v] = ownf[q][v];
+    }
+    return false;
+}
+
+// boundary_state for one Gauss point g of local face f of cell i, in an RK
+// stage: the inside state A, the outside state in B
+template <typename real, int NV, int PHYS>
+__device__ __forceinline__ bool boundary_point(const FluxArgs<real> a, double dt, int64_t i, int f, uint32_t kind,
+                                               int g, const real (&A)[NV], real (&B)[NV]) {
+    if (PHYS == CTENO_EULER && kind == CTENO_WALL) return true;
+    if (kind == CTENO_INFLOW) {
+        real nx, ny, len;
+        uint32_t code;
+        face_record<real>(a.fr, i, f, nx, ny, len, code);
+        const double *e = a.bface + 4 * (int64_t)((code >> 2) & kNbInflowMask);
+        const double t0 = a.tctrl ? a.tctrl->t : a.t_base;
+        const double ts = t0 + (a.stage == 1 ? dt : a.stage == 2 ? 0.5 * dt : 0.0);
+        const double gq = g ? a.gq[1] : a.gq[0];
+        const double px = e[0] + gq * e[2], py = e[1] + gq * e[3];
+        const bool behind = px < a.bline[0] + a.bline[1] * py + a.bline[2] * ts;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) B[v] = (real)(behind ? a.bst[0][v] : a.bst[1][v]);
+    } else {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) B[v] = A[v];
     }
     return false;
 }

@@ -256,6 +256,33 @@ static cteno_status check_scheme(const cteno_scheme &s) {
     return CTENO_OK;
 }
 
+// Gram matrix [K][K] and face basis [3][Nq][K] of a degree on the device, in
+// FP64 and FP32.  r <= 3: the FP32 Gram matrix holds its entries above the
+// diagonal doubled (the kernels sum the quadratic form over that triangle).
+template <class Alloc>
+static cteno_status upload_tables(DeviceMesh &dm, Alloc &&alloc_raw, hipStream_t st) {
+    const int K = dm.K, nq = dm.Nq;
+    const size_t n = (size_t)K * K + 3 * nq * K;
+    std::vector<double> t64(n);
+    std::vector<float> t32(n);
+    for (int p = 0; p < K; ++p)
+        for (int q = 0; q < K; ++q) t64[p * K + q] = dm.tab.gram[p][q];
+    for (int f = 0; f < 3; ++f)
+        for (int q = 0; q < nq; ++q)
+            for (int k = 0; k < K; ++k) t64[K * K + (f * nq + q) * K + k] = dm.tab.basis[f][q][k];
+    for (size_t e = 0; e < n; ++e) t32[e] = (float)t64[e];
+    if (dm.r <= 3)
+        for (int p = 0; p < K; ++p)
+            for (int q = p + 1; q < K; ++q) t32[p * K + q] = (float)(2.0 * dm.tab.gram[p][q]);
+    dm.htab64 = (double *)alloc_raw(n * sizeof(double));
+    dm.htab32 = (float *)alloc_raw(n * sizeof(float));
+    if (!dm.htab64 || !dm.htab32) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    HIP_TRY(h2d(dm.htab64, t64, st));
+    HIP_TRY(h2d(dm.htab32, t32, st));
+    HIP_TRY(hipStreamSynchronize(st));     // t64 and t32 end here
+    return CTENO_OK;
+}
+
 // Uploads a host-built mesh: device arrays, FP64 precompute of the
 // pseudo-inverses (plus the FP32 copy for MIXED), admissibility fix-up.
 // Allocations are appended to bufs; their size is added to bytes.
@@ -281,9 +308,11 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     make_ref_tables(hm.r, dm.tab);
     const size_t Np = (size_t)dm.Np, S = hm.S;
     dm.SP = hm.SP;
-    dm.E64 = round_up(pinv_entries(hm.r), 2);
-    dm.E32 = round_up(pinv_entries(hm.r), 4);
-    dm.slot = alloc_T(int32_t, Np * hm.SP);
+    dm.E = pinv_entries(hm.r);
+    // r <= 3: only the row numbers (below) stay
+    DevBuf slots(ctx, Np * hm.SP * sizeof(int32_t));
+    if (!slots.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    dm.slot = slots.as<int32_t>();
     dm.flags = alloc_T(uint8_t, Np);
     dm.fr64 = keep_fr64 ? alloc_T(double, Np * 12) : nullptr;
     dm.area = alloc_T(double, Np);
@@ -299,30 +328,14 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     for (int k = 0; k < 3; ++k) dm.bline[k] = hm.bline[k];
     if (s.precision & CTENO_MIXED) {
         dm.fr32 = alloc_T(float, Np * 12);
-        dm.P32 = alloc_T(float, Np * dm.E32);
+        dm.P32 = alloc_T(float, Np * dm.E);
     }
-    if (!dm.slot || !dm.flags || (keep_fr64 && !dm.fr64) || !dm.area || !dm.perm ||
+    if (!dm.flags || (keep_fr64 && !dm.fr64) || !dm.area || !dm.perm ||
         ((s.precision & CTENO_MIXED) && (!dm.fr32 || !dm.P32)))
         return fail(CTENO_ERR_NOMEM, "device allocation failed");
-    if (hm.r >= 4) {
-        // Gram matrix [K][K] and face basis [3][Nq][K] of the higher-order kernels
-        const int K = hm.K, ntab = K * K + 3 * hm.Nq * K;
-        std::vector<double> t64(ntab);
-        std::vector<float> t32(ntab);
-        for (int p = 0; p < K; ++p)
-            for (int q = 0; q < K; ++q) t64[p * K + q] = dm.tab.gram[p][q];
-        for (int f = 0; f < 3; ++f)
-            for (int q = 0; q < hm.Nq; ++q)
-                for (int k = 0; k < K; ++k) t64[K * K + (f * hm.Nq + q) * K + k] = dm.tab.basis[f][q][k];
-        for (int e = 0; e < ntab; ++e) t32[e] = (float)t64[e];
-        dm.htab64 = alloc_T(double, ntab);
-        dm.htab32 = alloc_T(float, ntab);
-        if (!dm.htab64 || !dm.htab32) return fail(CTENO_ERR_NOMEM, "device allocation failed");
-        HIP_TRY(h2d(dm.htab64, t64, st));
-        HIP_TRY(h2d(dm.htab32, t32, st));
-    }
+    if (cteno_status rc = upload_tables(dm, alloc_raw, st)) return rc;
     // FP64 pseudo-inverses are always computed; kept only when FP64 is resident
-    DevBuf p64(ctx, Np * dm.E64 * sizeof(double));
+    DevBuf p64(ctx, Np * dm.E * sizeof(double));
     DevBuf verts(ctx, Np * 6 * sizeof(double)), sflag(ctx, Np * S), sshift(ctx, Np * 2 * S), rfail(ctx, sizeof(int));
     if (!p64.p || !verts.p || !sflag.p || !sshift.p || !rfail.p)
         return fail(CTENO_ERR_NOMEM, "device allocation failed (precompute)");
@@ -339,8 +352,8 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     HIP_TRY(h2d(sshift.as<int8_t>(), hm.slot_shift, st));
     HIP_TRY(hipMemsetAsync(rfail.p, 0, sizeof(int), st));
     // padding entries of the streams stay zero
-    HIP_TRY(hipMemsetAsync(dm.P64, 0, Np * dm.E64 * sizeof(double), st));
-    if (dm.P32) HIP_TRY(hipMemsetAsync(dm.P32, 0, Np * dm.E32 * sizeof(float), st));
+    HIP_TRY(hipMemsetAsync(dm.P64, 0, Np * dm.E * sizeof(double), st));
+    if (dm.P32) HIP_TRY(hipMemsetAsync(dm.P32, 0, Np * dm.E * sizeof(float), st));
 
     PrecomputeInputs in{verts.as<double>(), sflag.as<uint8_t>(), sshift.as<int8_t>(), dm.flags, rfail.as<int>()};
     // kernel timing belongs to the context's own stream and thread
@@ -370,66 +383,86 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     } else {
         dm.P64 = nullptr;
     }
+    std::vector<int4> desc;
+    if (hm.r <= 3) {
+        const int64_t ng = dm.groups();
+        DevBuf len(ctx, (size_t)ng * sizeof(int32_t));
+        if (!len.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+        HIP_TRY(launch_halo_counts(dm, len.as<int32_t>(), st));
+        std::vector<int32_t> hl((size_t)ng);
+        desc.resize((size_t)ng);
+        HIP_TRY(hipMemcpyAsync(hl.data(), len.p, hl.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        int64_t total = 0;
+        for (int64_t g = 0; g < ng; ++g) {
+            desc[g] = make_int4((int)total, hl[g], 0, 0);
+            total += hl[g];
+            dm.max_halo = std::max(dm.max_halo, (int)hl[g]);
+        }
+        if (total > INT32_MAX) return fail(CTENO_ERR_INVALID, "neighbour lists too long");
+        dm.desc = alloc_T(int4, (size_t)ng);
+        dm.hlist = alloc_T(int32_t, (size_t)total + 1);    // (a group without neighbours reads one entry)
+        dm.lslot = alloc_T(uint16_t, Np * row_entries(hm.r));
+        if (!dm.desc || !dm.hlist || !dm.lslot) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+        HIP_TRY(h2d(dm.desc, desc, st));
+        HIP_TRY(launch_fill_u32((uint32_t *)dm.hlist + total, 0u, 1, st));
+        HIP_TRY(launch_halo_lists(dm, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        dm.slot = nullptr;
+    } else {
+        bytes += (int64_t)slots.bytes;
+        bufs.push_back(std::move(slots));
+    }
     // fused stage (degree <= 3; single meshes -- the batched serving kernels
     // keep the reconstruction + flux pair): the cells with a face whose
     // neighbour lies in another 256-cell block, from the face codes
     dm.fused = keep_fr64 && hm.r <= 3 && hm.Nq == 2;
     if (dm.fused) {
-        std::vector<int32_t> xc;
-        for (int64_t k = 0; k < hm.N; ++k)
-            for (int f = 0; f < 3; ++f) {
-                uint32_t code;
-                std::memcpy(&code, &hm.fr32[avix(k, 4 * f + 3, 12, 4)], sizeof code);
-                if (!(code & kNbBoundary) && ((int64_t)(code & kNbIndexMask) >> 8) != (k >> 8)) {
-                    xc.push_back((int32_t)k);
-                    break;
-                }
-            }
-        dm.n_cross = (int64_t)xc.size();
-        if (dm.n_cross) {
-            // in cross-cell order: the neighbour's cross index across each
-            // face to another block, the area and the face records; per
-            // block the number of cross cells before it
-            const int64_t nx = dm.n_cross, nxp = pad64(nx), nb = dm.blocks();
-            std::vector<int32_t> xbase(nb + 1, 0), xidx(hm.N, -1), xnb(3 * nx, -1);
-            std::vector<double> xar(nx), xf64(keep_fr64 ? nxp * 12 : 0);
-            std::vector<float> xf32(dm.fr32 ? nxp * 12 : 0);
-            for (int64_t t = 0; t < nx; ++t) {
-                xbase[(xc[t] >> 8) + 1]++;
-                xidx[xc[t]] = (int32_t)t;
-            }
-            for (int64_t b = 0; b < nb; ++b) xbase[b + 1] += xbase[b];
-            for (int64_t t = 0; t < nx; ++t) {
-                const int64_t k = xc[t];
-                xar[t] = hm.area[k];
-                for (int f = 0; f < 3; ++f) {
-                    uint32_t code;
-                    std::memcpy(&code, &hm.fr32[avix(k, 4 * f + 3, 12, 4)], sizeof code);
-                    const int64_t j = code & kNbIndexMask;
-                    if (!(code & kNbBoundary) && (j >> 8) != (k >> 8)) xnb[3 * t + f] = xidx[j];
-                }
-                for (int e = 0; e < 12; ++e) {
-                    if (!xf32.empty()) xf32[avix(t, e, 12, 4)] = hm.fr32[avix(k, e, 12, 4)];
-                    if (!xf64.empty()) xf64[avix(t, e, 12, 2)] = hm.fr64[avix(k, e, 12, 2)];
-                }
-            }
-            dm.xcells = alloc_T(int32_t, xc.size());
-            dm.xbase = alloc_T(int32_t, xbase.size());
-            dm.xnb = alloc_T(int32_t, xnb.size());
-            dm.xarea = alloc_T(double, xar.size());
-            if (!xf32.empty()) dm.xfr32 = alloc_T(float, xf32.size());
-            if (!xf64.empty()) dm.xfr64 = alloc_T(double, xf64.size());
-            if (!dm.xcells || !dm.xbase || !dm.xnb || !dm.xarea || (!xf32.empty() && !dm.xfr32) ||
-                (!xf64.empty() && !dm.xfr64))
-                return fail(CTENO_ERR_NOMEM, "device allocation failed");
-            HIP_TRY(h2d(dm.xcells, xc, st));
-            HIP_TRY(h2d(dm.xbase, xbase, st));
-            HIP_TRY(h2d(dm.xnb, xnb, st));
-            HIP_TRY(h2d(dm.xarea, xar, st));
-            if (!xf32.empty()) HIP_TRY(h2d(dm.xfr32, xf32, st));
-            if (!xf64.empty()) HIP_TRY(h2d(dm.xfr64, xf64, st));
-            HIP_TRY(hipStreamSynchronize(st));
+        const int64_t ng = dm.groups();
+        DevBuf cnt(ctx, (size_t)(3 * ng + 1) * sizeof(int32_t)), base(ctx, (size_t)(2 * ng) * sizeof(int32_t));
+        if (!cnt.p || !base.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+        int32_t *c = cnt.as<int32_t>();
+        HIP_TRY(hipMemsetAsync(c + 3 * ng, 0, sizeof(int32_t), st));
+        HIP_TRY(launch_block_counts(dm, BlockCounts{c, c + ng, c + 2 * ng, c + 3 * ng}, st));
+        std::vector<int32_t> hc((size_t)(3 * ng + 1)), hb((size_t)(2 * ng));
+        HIP_TRY(hipMemcpyAsync(hc.data(), c, hc.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        int64_t nf = 0, nx = 0, ns = 0;
+        for (int64_t g = 0; g < ng; ++g) {
+            desc[g].z = (int)nf;
+            desc[g].w = hc[g];
+            hb[g] = (int32_t)nx;
+            hb[ng + g] = (int32_t)ns;
+            nf += hc[g];
+            nx += hc[ng + g];
+            ns += hc[2 * ng + g];
         }
+        if (ns > (int64_t)kNbIndexMask) {
+            dm.fused = false;              // the side numbers do not fit: separate kernels
+        } else {
+            dm.n_cross = nx;
+            dm.n_sides = ns;
+        }
+        dm.n_cross256 = hc[3 * ng];
+        if (dm.fused) {
+            dm.xid = alloc_T(uint32_t, Np);
+            // (a last group without a listed face reads the record past the end)
+            if (dm.fr32) dm.frec32 = alloc_T(float, 4 * (nf + 1));
+            if (dm.fr64) dm.frec64 = alloc_T(double, 4 * (nf + 1));
+            if (nx) {
+                dm.xcells = alloc_T(int2, nx);
+                dm.xarea = alloc_T(double, nx);
+                if (dm.fr32) dm.xrec32 = alloc_T(float, 4 * ns);
+                if (dm.fr64) dm.xrec64 = alloc_T(double, 4 * ns);
+            }
+            if (!dm.xid || (dm.fr32 && !dm.frec32) || (dm.fr64 && !dm.frec64) ||
+                (nx && (!dm.xcells || !dm.xarea || (dm.fr32 && !dm.xrec32) || (dm.fr64 && !dm.xrec64))))
+                return fail(CTENO_ERR_NOMEM, "device allocation failed");
+            HIP_TRY(h2d(dm.desc, desc, st));
+            HIP_TRY(hipMemcpyAsync(base.p, hb.data(), hb.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
+            HIP_TRY(launch_block_lists(dm, base.as<int32_t>(), base.as<int32_t>() + ng, st));
+        }
+        HIP_TRY(hipStreamSynchronize(st));
     }
     // release host-only copies that the device now holds
     hm.slot.clear(); hm.slot.shrink_to_fit();
@@ -474,7 +507,7 @@ extern "C" cteno_status cteno_mesh_info_get(const cteno_mesh *m, cteno_mesh_info
     info->Md = m->host.Md;
     info->n_inadmissible = m->host.n_inadmissible;
     info->device_bytes = m->bytes;
-    info->n_cross_cells = m->dm.n_cross;
+    info->n_cross_cells = m->dm.n_cross256;
     return CTENO_OK;
 }
 
@@ -504,16 +537,17 @@ extern "C" cteno_status cteno_mesh_pinv(cteno_ctx *ctx, const cteno_mesh *m, int
     }
     // slot tables are not kept on the host; rebuild the column maps from the stencils
     const int K = hm.K, S = hm.S, M = hm.M, Kd = hm.Kd, Md = hm.Md;
-    const int E = f32 ? dm.E32 : dm.E64, VW = f32 ? 4 : 2;
+    const int E = dm.E;
     HIP_TRY(hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream();
     DevBuf didx(ctx, n * sizeof(int32_t)), op(ctx, (size_t)n * E * sizeof(double)),
         dslot(ctx, (size_t)n * dm.SP * sizeof(double));
     if (!didx.p || !op.p || !dslot.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     HIP_TRY(hipMemcpyAsync(didx.p, idx.data(), n * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_gather_entries(n, didx.as<int32_t>(), E, VW, f32 ? nullptr : dm.P64, f32 ? dm.P32 : nullptr,
-                                  nullptr, op.as<double>(), st, dm.stile));
-    HIP_TRY(launch_gather_entries(n, didx.as<int32_t>(), dm.SP, 4, nullptr, nullptr, dm.slot, dslot.as<double>(), st));
+    HIP_TRY(launch_gather_entries(dm, n, didx.as<int32_t>(), E, f32 ? nullptr : dm.P64, f32 ? dm.P32 : nullptr,
+                                  nullptr, op.as<double>(), st));
+    HIP_TRY(launch_gather_entries(dm, n, didx.as<int32_t>(), dm.SP, nullptr, nullptr, dm.slot, dslot.as<double>(),
+                                  st));     // (r <= 3: no slot table, the cells come from the row numbers)
     std::vector<double> pe((size_t)n * E), slotd((size_t)n * dm.SP);
     HIP_TRY(hipMemcpyAsync(pe.data(), op.p, pe.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(slotd.data(), dslot.p, slotd.size() * sizeof(double), hipMemcpyDeviceToHost, st));
@@ -586,7 +620,7 @@ struct cteno_sol {
     DevBuf ctrl;              // Ctrl
     DevBuf dt_part;           // per-block minima of the CFL bound
     DevBuf status;            // SolStatus: fallback count, non-physical flag of stage calls
-    DevBuf xpart;             // fused stage: partial stage states of the cross cells
+    DevBuf xterm;             // FP32 fused stage: terms of the cross cells' faces inside their groups
     double t = 0.0;
     Ctrl *h_ctrl = nullptr;   // pinned host mirror
     hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -602,6 +636,14 @@ struct cteno_sol {
             b = DevBuf(ctx, (size_t)dm.Np * 3 * dm.Nq * dm.nv * (f32 ? sizeof(float) : sizeof(double)));
         }
         return b.p;
+    }
+    // the FP32 fused stage's work buffer (null: allocation failed)
+    void *xt() {
+        if (!xterm.p) {
+            const DeviceMesh &dm = mesh->dm;
+            xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.n_sides, 1) * dm.nv * sizeof(float));
+        }
+        return xterm.p;
     }
 };
 
@@ -638,7 +680,7 @@ extern "C" cteno_status cteno_sol_create(cteno_ctx *ctx, const cteno_mesh *m, co
         HIP_TRY(hipMemsetAsync(u.p, 0, bytes, ctx->stream()));
     }
     s->ctrl = DevBuf(ctx, sizeof(Ctrl));
-    s->dt_part = DevBuf(ctx, (size_t)dm.dt_parts() * sizeof(double));
+    s->dt_part = DevBuf(ctx, (size_t)dm.dt_storage() * sizeof(double));
     s->status = DevBuf(ctx, sizeof(SolStatus));
     if (!s->ctrl.p || !s->dt_part.p || !s->status.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     HIP_TRY(hipMemsetAsync(s->ctrl.p, 0, sizeof(Ctrl), ctx->stream()));
@@ -880,7 +922,7 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
     fl.dt_part = dt_part;
     fl.t_base = s->t;
     if (use_fused(ctx, dm, f32)) {
-        fl.xpart = s->xpart.as<double>();
+        if (f32) fl.xterm = s->xt();
         hipError_t e = timed(ctx, 0, [&] { return launch_stage(dm, f32, fl, done, 0, st, &ss->fallbacks); });
         if (e != hipSuccess) return e;
         return timed(ctx, 1, [&] { return launch_stage(dm, f32, fl, done, 1, st, &ss->fallbacks); });
@@ -890,15 +932,9 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
     return timed(ctx, 1, [&] { return launch_flux(dm, f32, fl, st); });
 }
 
-// the work buffers a stage needs: face values, and the fused stage's partial states
+// the work buffers of a stage, allocated before it is issued or captured
 bool stage_buffers(cteno_ctx *ctx, cteno_sol *s, bool f32) {
-    if (!s->fv(f32)) return false;
-    const DeviceMesh &dm = s->mesh->dm;
-    if (use_fused(ctx, dm, f32) && !s->xpart.p) {
-        s->xpart = DevBuf(ctx, (size_t)std::max<int64_t>(dm.n_cross, 1) * dm.nv * sizeof(double));
-        if (!s->xpart.p) return false;
-    }
-    return true;
+    return s->fv(f32) && (!f32 || !use_fused(ctx, s->mesh->dm, f32) || s->xt());
 }
 }  // namespace
 
@@ -924,7 +960,7 @@ hipError_t issue_step(cteno_ctx *ctx, cteno_sol *s, bool f32, hipStream_t st) {
     Ctrl *c = s->ctrl.as<Ctrl>();
     double *part = s->dt_part.as<double>();
     const DeviceMesh &dm = s->mesh->dm;
-    hipError_t e = launch_control(c, part, use_fused(ctx, dm, f32) ? dm.dt_parts() : dm.blocks(), 0, st);
+    hipError_t e = launch_control(c, part, dm.dt_parts(use_fused(ctx, dm, f32)), 0, st);
     for (int stage = 0; stage < 3 && e == hipSuccess; ++stage)
         e = issue_stage(ctx, s, f32, stage, &c->dt, 0.0, c, stage == 2 ? part : nullptr, st);
     return e;
@@ -952,10 +988,8 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
     h.max_steps = max_steps;
     h.dt_cand_bits = 0x7FF0000000000000ull;
     HIP_TRY(hipMemcpyAsync(dc, &h, sizeof(Ctrl), hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_dt_partials(dm, f32, s->U[0].as<double>(), s->dt_part.as<double>(), st));
-    if (use_fused(ctx, dm, f32) && dm.cross_blocks())    // the second stage kernel's minima: none yet
-        HIP_TRY(launch_fill_u64((unsigned long long *)(s->dt_part.as<double>() + dm.blocks()),
-                                0x7FF0000000000000ull, (size_t)dm.cross_blocks(), st));
+    HIP_TRY(launch_dt_partials(dm, f32, s->U[0].as<double>(), s->dt_part.as<double>(),
+                               dm.dt_parts(use_fused(ctx, dm, f32)), st));
 
     // graphs need a capturable stream: the context's own stream when the
     // caller uses the null stream
@@ -1084,6 +1118,9 @@ struct ServerSlot {
 // this many batched steps (a solve that finishes within a tick idles through
 // the rest of it)
 constexpr int kStepsPerTick = 4;
+// neighbour lists of a 64-cell group that the usual batched launch holds in
+// LDS; in Morton order the longest have about 135 cells at degree 3
+constexpr int kHaloUsual = 256;
 
 struct cteno_server {
     cteno_ctx *ctx = nullptr;
@@ -1095,11 +1132,13 @@ struct cteno_server {
     DeviceMesh proto;              // scheme constants shared by every slot
     // device slot table, slot count, control pool
     DevBuf d_table, d_nslots, d_ctrl;
+    std::vector<DevBuf> tables;    // the proto's Gram matrix and face basis
     BatchSlot *h_table = nullptr;
     int *h_nslots = nullptr;
     Ctrl *h_ctrl = nullptr;
-    // one captured tick per grid size (powers of two up to max_blocks)
-    std::map<int64_t, hipGraphExec_t> graphs;
+    // one captured tick per grid size (powers of two up to max_blocks) and LDS
+    // size (neighbour lists of at most kHaloUsual cells, or of any length)
+    std::map<std::pair<int64_t, int>, hipGraphExec_t> graphs;
     // host side
     std::mutex mu;
     std::condition_variable cv_build, cv_upload, cv_sched, cv_done, cv_budget;
@@ -1125,10 +1164,10 @@ namespace {
 void slot_footprint(const cteno_server *sv, int64_t N, int64_t &steady, int64_t &transient) {
     const int r = sv->scheme.degree;
     const int64_t Np = pad64(N);
-    const int64_t E32 = round_up(pinv_entries(r), 4), E64 = round_up(pinv_entries(r), 2);
+    const int64_t E = pinv_entries(r);
     const int S = dims_S(r), SP = round_up(S, 4);
-    steady = Np * (E32 * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 8;
-    transient = Np * (E64 * 8 + 6 * 8 + S + 2 * S) + 64;
+    steady = Np * (E * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 8;
+    transient = Np * (E * 8 + 6 * 8 + S + 2 * S) + 64;
 }
 
 // a request's device state on a builder's stream: mesh arrays and FP64
@@ -1159,7 +1198,7 @@ cteno_status prepare_slot(cteno_server *sv, const std::shared_ptr<ServerRequest>
     if (!tmp.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     HIP_TRY(hipMemcpyAsync(tmp.p, rq->u0.data(), (size_t)dm.N * dm.nv * sizeof(double), hipMemcpyHostToDevice, st));
     HIP_TRY(launch_user_to_state(dm, tmp.as<double>(), sl->U[0].as<double>(), st));
-    HIP_TRY(launch_dt_partials(dm, true, sl->U[0].as<double>(), sl->dt_part.as<double>(), st));
+    HIP_TRY(launch_dt_partials(dm, true, sl->U[0].as<double>(), sl->dt_part.as<double>(), dm.blocks(), st));
     HIP_TRY(hipStreamSynchronize(st));     // tmp and the host u0 are released after this
     rq->u0.clear();
     rq->u0.shrink_to_fit();
@@ -1288,12 +1327,14 @@ void scheduler_fail(cteno_server *sv, const std::string &m) {
 }
 
 // the captured tick for a grid of `blocks` blocks (captured on first use)
-hipGraphExec_t tick_graph(cteno_server *sv, int64_t blocks) {
-    auto it = sv->graphs.find(blocks);
+// whose groups' neighbour lists hold at most `halo` cells
+hipGraphExec_t tick_graph(cteno_server *sv, int64_t blocks, int halo) {
+    auto it = sv->graphs.find({blocks, halo});
     if (it != sv->graphs.end()) return it->second;
     hipGraph_t g = nullptr;
     if (hipStreamBeginCapture(sv->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) return nullptr;
     hipError_t e = hipSuccess;
+    sv->proto.max_halo = halo;
     for (int k = 0; k < kStepsPerTick && e == hipSuccess; ++k)
         e = launch_batch_step(sv->proto, sv->d_table.as<BatchSlot>(), sv->d_nslots.as<int>(), sv->max_slots, blocks,
                               sv->stream);
@@ -1301,7 +1342,7 @@ hipGraphExec_t tick_graph(cteno_server *sv, int64_t blocks) {
     hipGraphExec_t x = nullptr;
     if (e == hipSuccess && e2 == hipSuccess && hipGraphInstantiate(&x, g, nullptr, nullptr, 0) != hipSuccess) x = nullptr;
     if (g) (void)hipGraphDestroy(g);
-    if (x) sv->graphs[blocks] = x;
+    if (x) sv->graphs[{blocks, halo}] = x;
     return x;
 }
 
@@ -1309,6 +1350,7 @@ void scheduler_main(cteno_server *sv) {
     if (hipSetDevice(sv->ctx->device) != hipSuccess) { scheduler_fail(sv, "hipSetDevice failed"); return; }
     bool dirty = true;
     int64_t grid = 0;
+    int halo = kHaloUsual;
     for (;;) {
         // admissions: resident solves, in the order their uploads finished,
         // while slots are free (no device work: the builders did it)
@@ -1345,13 +1387,16 @@ void scheduler_main(cteno_server *sv) {
         if (sv->active.empty()) continue;
         if (dirty) {
             int64_t b0 = 0;
+            halo = kHaloUsual;
             for (size_t k = 0; k < sv->active.size(); ++k) {
                 ServerSlot &sl = *sv->active[k];
                 BatchSlot &t = sv->h_table[k];
                 t.N = sl.dm.N;
                 t.block0 = b0;
                 t.nblocks = sl.dm.blocks();
-                t.slot = sl.dm.slot;
+                t.lslot = sl.dm.lslot;
+                t.desc = sl.dm.desc;
+                t.hlist = sl.dm.hlist;
                 t.flags = sl.dm.flags;
                 t.P = sl.dm.P32;
                 t.fr = sl.dm.fr32;
@@ -1361,6 +1406,7 @@ void scheduler_main(cteno_server *sv) {
                 t.dt_part = sl.dt_part.as<double>();
                 t.ctrl = sv->d_ctrl.as<Ctrl>() + sl.ctrl_index;
                 b0 += t.nblocks;
+                if (sl.dm.max_halo > kHaloUsual) halo = 64 * sl.dm.S;
             }
             *sv->h_nslots = (int)sv->active.size();
             if (b0 > sv->max_blocks) { scheduler_fail(sv, "block budget exceeded"); return; }
@@ -1378,7 +1424,7 @@ void scheduler_main(cteno_server *sv) {
             dirty = false;
         }
         // kStepsPerTick SSP-RK3 steps of every active solve
-        hipGraphExec_t gx = tick_graph(sv, grid);
+        hipGraphExec_t gx = tick_graph(sv, grid, halo);
         if (!gx) { scheduler_fail(sv, "tick capture failed"); return; }
         if (hipGraphLaunch(gx, sv->stream) != hipSuccess) { scheduler_fail(sv, "graph launch failed"); return; }
         sv->ticks += kStepsPerTick;
@@ -1464,7 +1510,13 @@ extern "C" cteno_status cteno_server_create(cteno_ctx *ctx, const cteno_scheme *
     p.scheme = scheme->scheme; p.gamma_form = scheme->gamma_form; p.precision = CTENO_MIXED;
     p.gamma = scheme->gamma; p.lam1p = scheme->lambda1_prime; p.ct = scheme->c_t; p.eps = scheme->eps;
     p.positivity = scheme->positivity;
+    p.Nq = dims_Nq(p.r);
     make_ref_tables(p.r, p.tab);
+    auto table_mem = [&](size_t n) -> void * {
+        sv->tables.emplace_back(ctx, n);
+        return sv->tables.back().p;
+    };
+    if (cteno_status rc = upload_tables(p, table_mem, sv->stream)) return rc;
     HIP_TRY(hipStreamSynchronize(sv->stream));
     // several mesh builders, each with a share of the host threads, and two
     // upload threads, each with a stream of its own (default priority)
@@ -1618,6 +1670,7 @@ extern "C" void cteno_server_destroy(cteno_server *sv) {
     sv->d_table.reset();
     sv->d_nslots.reset();
     sv->d_ctrl.reset();
+    sv->tables.clear();
     (void)hipStreamDestroy(sv->stream);
     delete sv;
 }
