@@ -157,9 +157,9 @@ constexpr uint32_t kNbOwner = 0x40000000u;
 constexpr uint32_t kNbIndexMask = 0x0FFFFFFFu;
 // boundary faces: kind in bits 0-1; an inflow face's row in the inflow table in bits 2-29
 constexpr uint32_t kNbInflowMask = 0x0FFFFFFFu;
-// listed faces of a fused-stage block (64 cells): bits 0..5 the evaluating cell
-// in the block, 6..7 its local face; bits 8..13 the other cell and 14..15 its
-// local face, or bit 31 and the boundary kind in bits 8..9
+// listed faces of a fused-stage block (at most 256 cells): bits 0..7 the
+// evaluating cell in the block, 8..9 its local face; bits 10..17 the other cell
+// and 18..19 its local face, or bit 31 and the boundary kind in bits 10..11
 constexpr uint32_t kBfBoundary = 0x80000000u;
 // side records: the other side's number in bits 0..27, kNbOwner, and whether the
 // other cell lies in another 256-cell block

@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_batch(const ReconArgs<float
     extern __shared__ __align__(16) double rows[];
     double U0;
     float out[3][2];
-    recon_quad<float, R, 4, SCHEME, GFORM, 0, 0>(a, ptr, rows, i, threadIdx.x, i < t.N, [](const int4 &) {}, U0, out);
+    recon_quad<float, R, 4, SCHEME, GFORM, 0, 0>(a, ptr, rows, i, threadIdx.x, i < t.N, [] {}, U0, out);
     if (i >= t.N) return;
 #pragma unroll
     for (int f = 0; f < 3; ++f)
@@ -433,7 +433,7 @@ void *scratch_device_ptr(int device) {
 
 // the cell of slot j of cell i, from the row-number table
 template <int R>
-__device__ __forceinline__ int32_t row_cell(const uint16_t *lslot, const int4 *desc, const int32_t *hlist,
+__device__ __forceinline__ int32_t row_cell(const uint16_t *lslot, const int2 *desc, const int32_t *hlist,
                                             int64_t i, int j) {
     const int r = lslot[lslot_index<R>(i, j)];
     return r < 64 ? (int32_t)((i & ~int64_t(63)) + r) : hlist[desc[i >> 6].x + r - 64];
@@ -452,7 +452,7 @@ __global__ void k_gather_entries(int n, const int32_t *idx, int E, int VW, const
     dst[t] = s64 ? s64[src] : (s32 ? (double)s32[src] : (double)si[src]);
 }
 template <int R>
-__global__ void k_gather_cells(int n, const int32_t *idx, int SP, const uint16_t *lslot, const int4 *desc,
+__global__ void k_gather_cells(int n, const int32_t *idx, int SP, const uint16_t *lslot, const int2 *desc,
                                const int32_t *hlist, double *dst) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)n * SP) return;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void k_halo_counts(const int32_t *slot, int SP
     if (threadIdx.x == 0) len[blockIdx.x] = n;
 }
 template <int R>
-__global__ __launch_bounds__(256) void k_halo_lists(const int32_t *slot, int SP, const int4 *desc,
+__global__ __launch_bounds__(256) void k_halo_lists(const int32_t *slot, int SP, const int2 *desc,
                                                     int32_t *hlist, uint16_t *lslot) {
     __shared__ int key[kHaloSort], uniq[kHaloSort];
     const int n = group_halo(slot, SP, key, uniq);
@@ -580,24 +580,31 @@ hipError_t launch_halo_lists(const DeviceMesh &m, hipStream_t st) {
 
 // the arrays of a DeviceMesh that these kernels read and write
 struct BlockMesh {
-    int64_t N, Np, n_cross;
+    int64_t N, Np;
     const float *fr32;
     const double *fr64, *area;
-    const int4 *desc;
-    float *frec32, *xrec32;
-    double *frec64, *xrec64, *xarea;
-    uint32_t *xid;
-    int2 *xcells;
-    explicit BlockMesh(const DeviceMesh &m)
-        : N(m.N), Np(m.Np), n_cross(m.n_cross), fr32(m.fr32), fr64(m.fr64), area(m.area), desc(m.desc),
-          frec32(m.frec32), xrec32(m.xrec32), frec64(m.frec64), xrec64(m.xrec64), xarea(m.xarea), xid(m.xid),
-          xcells(m.xcells) {}
+    bool f32;
+    StageLists l;
+    BlockMesh(const DeviceMesh &m, bool fp32)
+        : N(m.N), Np(m.Np), fr32(m.fr32), fr64(m.fr64), area(m.area), f32(fp32), l(m.lists[fp32]) {}
 };
 
 // the neighbour code of face f of cell i, from either kind of face record
 __device__ __forceinline__ uint32_t face_code(const BlockMesh &m, int64_t i, int f) {
     if (m.fr32) return (uint32_t)__float_as_int(m.fr32[avix(i, 4 * f + 3, 12, 4)]);
     return (uint32_t)__double_as_longlong(m.fr64[avix(i, 4 * f + 3, 12, 2)]);
+}
+// record k of a list: normal and length of face f of cell i, and a code
+__device__ __forceinline__ void put_record(const BlockMesh &m, void *rec, int64_t k, int64_t i, int f, uint32_t code) {
+    if (m.f32) {
+        float *r = (float *)rec + 4 * k;
+        for (int e = 0; e < 3; ++e) r[e] = m.fr32[avix(i, 4 * f + e, 12, 4)];
+        r[3] = __int_as_float((int)code);
+    } else {
+        double *r = (double *)rec + 4 * k;
+        for (int e = 0; e < 3; ++e) r[e] = m.fr64[avix(i, 4 * f + e, 12, 2)];
+        r[3] = __longlong_as_double((long long)code);
+    }
 }
 
 // exclusive sum over a wave and the total
@@ -633,7 +640,7 @@ __global__ __launch_bounds__(256) void k_block_counts(const BlockMesh m, const B
     uint32_t code[3];
     int listed, cross, cross256, nf, nx, ns, n256;
     cell_faces(m, i, 256, code, listed, cross256);
-    cell_faces(m, i, 64, code, listed, cross);
+    cell_faces(m, i, m.l.bc, code, listed, cross);
     (void)wave_scan(__popc(listed), nf);
     (void)wave_scan(cross ? 1 : 0, nx);
     (void)wave_scan(__popc(cross), ns);
@@ -645,68 +652,57 @@ __global__ __launch_bounds__(256) void k_block_counts(const BlockMesh m, const B
         if (n256) atomicAdd(c.cross256, n256);
     }
 }
-hipError_t launch_block_counts(const DeviceMesh &m, const BlockCounts &c, hipStream_t st) {
-    hipLaunchKernelGGL(k_block_counts, dim3(grid_for(m.Np)), dim3(256), 0, st, BlockMesh(m), c);
+hipError_t launch_block_counts(const DeviceMesh &m, bool f32, const BlockCounts &c, hipStream_t st) {
+    hipLaunchKernelGGL(k_block_counts, dim3(grid_for(m.Np)), dim3(256), 0, st, BlockMesh(m, f32), c);
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_block_lists(const BlockMesh m, const int32_t *xbase, const int32_t *sbase) {
+__global__ __launch_bounds__(256) void k_block_lists(const BlockMesh m, const BlockCounts base) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x, g = i >> 6;
     if (i >= m.Np) return;                    // whole waves
     uint32_t code[3];
     int listed, cross, total;
-    cell_faces(m, i, 64, code, listed, cross);
-    int64_t k = m.desc[g].z + wave_scan(__popc(listed), total);
-    const int64_t t = xbase[g] + wave_scan(cross ? 1 : 0, total);
-    const uint32_t s0 = (uint32_t)(sbase[g] + wave_scan(__popc(cross), total));
+    cell_faces(m, i, m.l.bc, code, listed, cross);
+    int64_t k = base.faces[g] + wave_scan(__popc(listed), total);
+    const int64_t t = base.cross[g] + wave_scan(cross ? 1 : 0, total);
+    const uint32_t s0 = (uint32_t)(base.sides[g] + wave_scan(__popc(cross), total));
     const uint32_t id = cross ? s0 | ((uint32_t)cross << 28) : 0u;
-    m.xid[i] = id;
+    m.l.xid[i] = id;
     if (i >= m.N) return;
+    const uint32_t lm = (uint32_t)m.l.bc - 1u;
 #pragma unroll
     for (int f = 0; f < 3; ++f) {
         if (!((listed >> f) & 1)) continue;
-        uint32_t bf = (uint32_t)(i & 63) | ((uint32_t)f << 6);
-        if (code[f] & kNbBoundary) bf |= kBfBoundary | ((code[f] & 3u) << 8);
-        else bf |= (code[f] & 63u) << 8 | ((code[f] >> 28) & 3u) << 14;
-        for (int e = 0; e < 3; ++e) {
-            if (m.frec32) m.frec32[4 * k + e] = m.fr32[avix(i, 4 * f + e, 12, 4)];
-            if (m.frec64) m.frec64[4 * k + e] = m.fr64[avix(i, 4 * f + e, 12, 2)];
-        }
-        if (m.frec32) m.frec32[4 * k + 3] = __int_as_float((int)bf);
-        if (m.frec64) m.frec64[4 * k + 3] = __longlong_as_double((long long)bf);
-        ++k;
+        uint32_t bf = ((uint32_t)i & lm) | ((uint32_t)f << 8);
+        if (code[f] & kNbBoundary) bf |= kBfBoundary | ((code[f] & 3u) << 10);
+        else bf |= (code[f] & lm) << 10 | ((code[f] >> 28) & 3u) << 18;
+        put_record(m, m.l.frec, k++, i, f, bf);
     }
     if (cross) {
-        m.xcells[t] = make_int2((int)i, (int)id);
-        m.xarea[t] = m.area[i];
+        m.l.xcells[t] = make_int2((int)i, (int)id);
+        m.l.xarea[t] = m.area[i];
     }
 }
 // one thread per cross cell: its side records (every cell's first side is known)
 __global__ __launch_bounds__(256) void k_side_records(const BlockMesh m) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= m.n_cross) return;
-    const int64_t i = m.xcells[t].x;
-    const uint32_t id = m.xid[i];
+    if (t >= m.l.n_cross) return;
+    const int64_t i = m.l.xcells[t].x;
+    const uint32_t id = m.l.xid[i];
     int64_t s = id & kNbIndexMask;
     for (int f = 0; f < 3; ++f) {
         if (!((id >> (28 + f)) & 1)) continue;
-        const uint32_t code = face_code(m, i, f), idj = m.xid[code & kNbIndexMask];
+        const uint32_t code = face_code(m, i, f), idj = m.l.xid[code & kNbIndexMask];
         const int gf = (int)((code >> 28) & 3u);
         const uint32_t other = (idj & kNbIndexMask) + __popc((idj >> 28) & ((1u << gf) - 1u));
         const bool fb = (int64_t)(code & kNbIndexMask) / 256 != i / 256;
-        const uint32_t w = other | (code & kNbOwner) | (fb ? kSideFar : 0u);
-        for (int e = 0; e < 3; ++e) {
-            if (m.xrec32) m.xrec32[4 * s + e] = m.fr32[avix(i, 4 * f + e, 12, 4)];
-            if (m.xrec64) m.xrec64[4 * s + e] = m.fr64[avix(i, 4 * f + e, 12, 2)];
-        }
-        if (m.xrec32) m.xrec32[4 * s + 3] = __int_as_float((int)w);
-        if (m.xrec64) m.xrec64[4 * s + 3] = __longlong_as_double((long long)w);
-        ++s;
+        put_record(m, m.l.xrec, s++, i, f, other | (code & kNbOwner) | (fb ? kSideFar : 0u));
     }
 }
-hipError_t launch_block_lists(const DeviceMesh &m, const int32_t *xbase, const int32_t *sbase, hipStream_t st) {
-    hipLaunchKernelGGL(k_block_lists, dim3(grid_for(m.Np)), dim3(256), 0, st, BlockMesh(m), xbase, sbase);
-    if (m.n_cross) hipLaunchKernelGGL(k_side_records, dim3(grid_for(m.n_cross)), dim3(256), 0, st, BlockMesh(m));
+hipError_t launch_block_lists(const DeviceMesh &m, bool f32, const BlockCounts &base, hipStream_t st) {
+    const BlockMesh b(m, f32);
+    hipLaunchKernelGGL(k_block_lists, dim3(grid_for(m.Np)), dim3(256), 0, st, b, base);
+    if (b.l.n_cross) hipLaunchKernelGGL(k_side_records, dim3(grid_for(b.l.n_cross)), dim3(256), 0, st, b);
     return hipGetLastError();
 }
 

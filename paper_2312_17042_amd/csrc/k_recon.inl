@@ -15,7 +15,7 @@ __global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, co
     extern __shared__ __align__(16) double rows[];
     double U0;
     real out[3][2];
-    if (!recon_quad<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, rows, i, threadIdx.x, live, [](const int4 &) {},
+    if (!recon_quad<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, rows, i, threadIdx.x, live, [] {},
                                                                     U0, out)) return;
     if (!live || q >= NV) return;
 #pragma unroll

@@ -36,6 +36,31 @@
 
 namespace cteno {
 
+// Lists of the fused stage in one precision.  A block is bc cells: the faces
+// that it evaluates alone (its boundary faces and the faces between two of its
+// cells, once, from their owner), and the cells with a face to another block
+// ("cross cells") with one record per such face ("side")
+struct StageLists {
+    int bc = 64;
+    int2 *fdesc = nullptr;         // per block its first listed face and their number
+    void *frec = nullptr;          // [faces][4] normal, length, block face code (kBf*), of the precision type
+    uint32_t *xid = nullptr;       // [Np] the cell's first side | its faces to other blocks << 28 (0: none)
+    int2 *xcells = nullptr;        // [n_cross] cross cells, ascending, and their xid
+    double *xarea = nullptr;       // [n_cross] their areas
+    void *xrec = nullptr;          // [n_sides][4] normal, length, the other side | kNbOwner | kSideFar
+    int64_t n_cross = 0, n_sides = 0;
+    int64_t cross_blocks() const { return (n_cross + 63) / 64; }
+};
+// FP32 meshes from this many cells on take blocks of 256 cells (k_stage_wide):
+// fewer faces lead to other blocks, but the four groups of a block run one
+// after the other.  Both kernels of a stage together, blocks of 64 against 256
+// cells, degree 3: 96 / 102 us at 500k cells, 186 / 189 at 1M, 288 / 283 at
+// 1.4M, 402 / 392 at 2M, 1728 / 1545 at 8M.  Only where two groups' averages leave
+// room for three blocks per CU (the usual lists take 13 KB; scattered numberings up
+// to 90).
+constexpr int64_t kWideCells = 1200000;
+constexpr size_t kWideRowBytes = 28 * 1024;
+
 struct DeviceMesh {
     int64_t N = 0, Np = 0;
     int r = 0, K = 0, S = 0, SP = 0, nv = 0, physics = 0;
@@ -52,7 +77,7 @@ struct DeviceMesh {
     // (lslot_index): row < 64 a cell of the group, row - 64 a place in the
     // group's list of cells outside it
     uint16_t *lslot = nullptr;     // [Np][row_entries(r)]
-    int4 *desc = nullptr;          // [groups()] (first place in hlist, its length, first listed face, their number)
+    int2 *desc = nullptr;          // [groups()] first place in hlist, its length
     int32_t *hlist = nullptr;
     int max_halo = 0;              // the longest list
     uint8_t *flags = nullptr;      // [Np]
@@ -69,32 +94,24 @@ struct DeviceMesh {
     double *htab64 = nullptr;      // Gram matrix [K][K] and face basis [3][Nq][K], FP64
     float *htab32 = nullptr;       // the same in FP32 (r <= 3: off-diagonal Gram entries above the diagonal doubled)
     RefTables tab;
-    // fused stage (degree <= 3), a group of 64 cells per block: the faces that
-    // the block evaluates alone (its boundary faces and the faces between two
-    // of its cells, once, from their owner), and the cells with a face to
-    // another group ("cross cells") with one record per such face ("side")
-    float *frec32 = nullptr;       // [faces][4] normal, length, block face code (kBf*)
-    double *frec64 = nullptr;      // the same in FP64
-    uint32_t *xid = nullptr;       // [Np] the cell's first side | its faces to other groups << 28 (0: none)
-    int2 *xcells = nullptr;        // [n_cross] cross cells, ascending, and their xid
-    double *xarea = nullptr;       // [n_cross] their areas
-    float *xrec32 = nullptr;       // [n_sides][4] normal, length, the other side | kNbOwner | kSideFar
-    double *xrec64 = nullptr;      // the same in FP64
-    int64_t n_cross = 0, n_sides = 0;
+    StageLists lists[2];           // fused stage (degree <= 3): FP64, FP32
     int64_t n_cross256 = 0;        // cells with a face to another 256-cell block
     bool fused = false;            // the march runs the fused stage kernels
     int64_t blocks() const { return (N + 255) / 256; }
     int64_t groups() const { return Np / 64; }
     // LDS rows of one group
     size_t row_bytes() const { return (size_t)(64 + max_halo) * nv * sizeof(double); }
-    int64_t cross_blocks() const { return (n_cross + 63) / 64; }
+    int64_t stage_blocks(bool f32) const { return (N + lists[f32].bc - 1) / lists[f32].bc; }
     // Per-block CFL minima of one march step that the control reduces: the
     // fused stage's second kernel's (which fold in the first kernel's, stored
     // behind them), or the only kernel's
-    int64_t dt_parts(bool fused_run) const {
-        return !fused_run ? blocks() : n_cross ? cross_blocks() : groups();
+    int64_t dt_parts(bool fused_run, bool f32) const {
+        return !fused_run ? blocks() : lists[f32].n_cross ? lists[f32].cross_blocks() : stage_blocks(f32);
     }
-    int64_t dt_storage() const { return std::max(blocks(), groups() + cross_blocks()); }
+    int64_t dt_storage() const {
+        return std::max({blocks(), stage_blocks(false) + lists[0].cross_blocks(),
+                         stage_blocks(true) + lists[1].cross_blocks()});
+    }
     // selection bytes per cell: per variable, or per face and characteristic field
     int delta_bytes() const { return vars == CTENO_VARS_CHARACTERISTIC ? 3 * nv : nv; }
 };
@@ -143,22 +160,21 @@ struct FluxLaunch {
 };
 hipError_t launch_flux(const DeviceMesh &m, bool fp32, const FluxLaunch &f, hipStream_t st);
 
-// Block data of the fused stage from the face records on the device, in two
-// steps: the counts per group (listed faces, cross cells, sides) and the number
-// of cells with a face to another 256-cell block; then, with the groups'
-// first listed face in desc and their offsets (exclusive sums of the counts),
-// the lists.
+// Lists of the fused stage in one precision from the face records on the device,
+// in two steps: the counts per group of 64 cells (listed faces, cross cells,
+// sides) and the number of cells with a face to another 256-cell block; then,
+// with the groups' offsets (exclusive sums of the counts), the lists.
 struct BlockCounts {
     int32_t *faces, *cross, *sides;    // [groups()]
     int32_t *cross256;                 // one counter
 };
-hipError_t launch_block_counts(const DeviceMesh &m, const BlockCounts &c, hipStream_t st);
-hipError_t launch_block_lists(const DeviceMesh &m, const int32_t *xbase, const int32_t *sbase, hipStream_t st);
+hipError_t launch_block_counts(const DeviceMesh &m, bool f32, const BlockCounts &c, hipStream_t st);
+hipError_t launch_block_lists(const DeviceMesh &m, bool f32, const BlockCounts &base, hipStream_t st);
 
 // Fused SSP-RK3 stage of degree <= 3 (f.mode 2): part 0 reconstructs each
-// group of 64 cells into LDS, evaluates the faces inside the group and updates
+// block of cells into LDS, evaluates the faces inside the block and updates
 // the cells whose faces all lie inside it; part 1 evaluates the faces between
-// groups, whose values part 0 leaves in f.FV ([n_sides][2][nv]), and updates
+// blocks, whose values part 0 leaves in f.FV ([n_sides][2][nv]), and updates
 // their cells with the other faces' terms (f.xterm).  The two parts are launched in
 // order, 0 then 1.
 hipError_t launch_stage(const DeviceMesh &m, bool fp32, const FluxLaunch &f, const int *done, int part,
@@ -179,7 +195,7 @@ hipError_t launch_control(Ctrl *ctrl, const double *dt_part, int64_t n_part, int
 struct BatchSlot {
     int64_t N, block0, nblocks;     // cells; first global block; blocks of 256 cells
     const uint16_t *lslot;
-    const int4 *desc;
+    const int2 *desc;
     const int32_t *hlist;
     const uint8_t *flags;
     const float *P;                 // FP32 pseudo-inverse stream

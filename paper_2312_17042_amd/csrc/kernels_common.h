@@ -428,9 +428,10 @@ struct FluxArgs {
     double gq[4];           // Gauss nodes on [0, 1]
     double t_base;          // time of the stage input when tctrl is null
     const Ctrl *tctrl;      // time march: the stage input's time is tctrl->t, its step *dt_ptr
-    // fused stage (DeviceMesh)
+    // fused stage (StageLists)
+    const int2 *fdesc;      // per block its first listed face and their number
     const real *frec;       // records of the blocks' listed faces
-    const uint32_t *xid;    // [Np] first side | the faces to other groups << 28
+    const uint32_t *xid;    // [Np] first side | the faces to other blocks << 28
     const int2 *xcells;     // cross cells and their xid
     const double *xarea;
     const real *xrec;       // [n_sides] side records
@@ -467,14 +468,16 @@ inline void fill_flux_args(const DeviceMesh &m, const FluxLaunch &f, FluxArgs<re
     for (int q = 0; q < 4; ++q) a.gq[q] = q < m.tab.Nq ? m.tab.gq[q] : 0.0;
     a.t_base = f.t_base;
     a.tctrl = f.ctrl && f.dt_ptr ? f.ctrl : nullptr;
-    a.xcells = m.xcells;
-    a.n_cross = m.n_cross;
-    a.xid = m.xid;
-    a.xarea = m.xarea;
+    const StageLists &l = m.lists[std::is_same<real, float>::value ? 1 : 0];
+    a.fdesc = l.fdesc;
+    a.frec = (const real *)l.frec;
+    a.xid = l.xid;
+    a.xcells = l.xcells;
+    a.n_cross = l.n_cross;
+    a.xarea = l.xarea;
+    a.xrec = (const real *)l.xrec;
     a.xterm = (real *)f.xterm;
-    if constexpr (std::is_same<real, double>::value) { a.xrec = m.xrec64; a.frec = m.frec64; }
-    else { a.xrec = m.xrec32; a.frec = m.frec32; }
-    a.part_off = m.cross_blocks();     // (no cross cells: the first kernel's minima are the last)
+    a.part_off = l.cross_blocks();     // (no cross cells: the first kernel's minima are the last)
 }
 
 template <int NV, int PHYS>

@@ -98,12 +98,18 @@ __device__ __forceinline__ void rows_to_lanes(double (&x)[4]) {
 // constants of one reconstruction
 template <typename real>
 struct ReconArgs {
-    const real *tab;        // device table: Gram matrix [K][K], face basis [3][2][K] (uniform loads)
+    const real *tab;        // device table: Gram matrix [K][K], face basis [3][2][K]
     real lam1, ct, eps;
     real lams[5];           // lambda_s for s_t = 2, 3, 4 (index s_t)
     real gamma;             // ratio of specific heats (positivity check)
     real lam_ratio[5];      // lambda_1 / lambda_s (index s_t)
     int positivity;         // 1: cell-average fallback for non-physical face states
+    // entry k of the table, through the constant address space: a scalar load
+    // also behind stores and barriers (as a vector load it would wait for the
+    // stream that is in flight)
+    __device__ __forceinline__ real entry(int k) const {
+        return ((const __attribute__((address_space(4))) real *)tab)[k];
+    }
 };
 
 // arrays of one mesh and state
@@ -111,7 +117,7 @@ template <typename real>
 struct ReconPtrs {
     const double *U;        // AoS [Np][NV]
     const uint16_t *lslot;  // stencil entries as rows of the group (lslot_index)
-    const int4 *desc;       // per group: first place in hlist, length, (fused stage) first listed face, number
+    const int2 *desc;       // per group: first place in hlist, length
     const int32_t *hlist;   // the cells outside a group that its stencils reach
     const uint8_t *flags;   // [Np]
     const real *P;          // pseudo-inverse stream (quad_index)
@@ -144,10 +150,10 @@ __device__ __forceinline__ int finish_field(const ReconArgs<real> a, real (&c1)[
         for (int p = 0; p < K; ++p) {
             real rp = 0;
 #pragma unroll
-            for (int q = SYM ? p : 0; q < K; ++q) rp += a.tab[p * K + q] * c1[q];
+            for (int q = SYM ? p : 0; q < K; ++q) rp += a.entry(p * K + q) * c1[q];
             si[0] += c1[p] * rp;
         }
-        const real g00 = a.tab[0], g01 = a.tab[1], g10 = a.tab[K], g11 = a.tab[K + 1];
+        const real g00 = a.entry(0), g01 = a.entry(1), g10 = a.entry(K), g11 = a.entry(K + 1);
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const real x0 = cd[q][0], x1 = cd[q][1];
@@ -195,129 +201,84 @@ __device__ __forceinline__ int finish_field(const ReconArgs<real> a, real (&c1)[
 // stencil entry is a row number: gathers of single averages from global
 // memory took two of three slots of the address unit and kept it busy 88 % of
 // the stage kernel's time.
+template <int NV>
+struct GroupRows {
+    static constexpr int RL = 256 / NV;   // rows that the group's threads write at once
+    // the list's first HS shares are requested at once (NV = 4: 192 cells; the
+    // usual list at degree 3 has 100, at most 135 in Morton order)
+    static constexpr int HS = NV == 4 ? 3 : 1;
+    int hid[HS];
+    double hu[HS];
+    // the threads' places in the list, t of the group's 256 (a place past the
+    // list reads its first entry, or the pad)
+    __device__ __forceinline__ static int place(int t) { return NV == 4 ? t >> 2 : t; }
+    __device__ __forceinline__ void list(const int32_t *hlist, int2 desc, int t) {
+        const int r = place(t);
+#pragma unroll
+        for (int k = 0; k < HS; ++k) hid[k] = hlist[desc.x + (r + k * RL < desc.y ? r + k * RL : 0)];
+    }
+    __device__ __forceinline__ void averages(const double *U, int v) {
+#pragma unroll
+        for (int k = 0; k < HS; ++k) hu[k] = U[(int64_t)hid[k] * NV + v];
+    }
+    __device__ __forceinline__ void store(double *rows, const double *U, const int32_t *hlist, int2 desc, int t, int v,
+                                          double own) const {
+        const int r0 = place(t);
+        if (NV == 4 || (t & 3) == 0) rows[(t >> 2) * NV + v] = own;
+#pragma unroll
+        for (int k = 0; k < HS; ++k)
+            if (r0 + k * RL < desc.y) rows[(64 + r0 + k * RL) * NV + v] = hu[k];
+        for (int r = r0 + HS * RL; r < desc.y; r += RL)
+            rows[(64 + r) * NV + v] = U[(int64_t)hlist[desc.x + r] * NV + v];
+    }
+};
+
 struct RowIds3 { uint32_t w[3]; };
 struct RowIds2 { uint32_t w[2]; };
 template <int R> struct RowIds;
 template <> struct RowIds<3> { using T = RowIds3; };
 template <> struct RowIds<2> { using T = RowIds2; };
 
-// Central and directional coefficients of the lane's variable v, ao = P_c d
-// and ad = P_s d.  il: the cell (below Np), t: the thread in its group's 256;
-// U0: the cell's own average of variable v.  False (the same for the whole
-// grid) when *done is set: the march is over; the flag is waited for together
-// with the listed neighbours, before the stream is requested.  Holds a block
-// barrier.
-// Everything that is not the neighbours' averages is requested before the
-// first wait; what the group's descriptor leads to (list, then averages) is
-// the only chain.
-template <typename real, int R, int NV>
-__device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double *rows, int64_t il, int t, int4 &desc,
-                                              double &U0, int &fl, real (&ao)[QuadDims<R>::K], real (&ad)[3][2]) {
+// A lane's share of its tile's row numbers and stream (16 cells, one wave).
+// Lanes without an entry read another one's: no more bytes, and what they hold
+// meets unused rows of the result or zero differences.
+template <typename real, int R> struct QuadStream;
+
+template <int R>
+struct QuadStream<float, R> {
     using D = QuadDims<R>;
-    using V = typename StreamVec<real>::T;
-    using Ids = typename RowIds<R>::T;
-    constexpr int S = D::S, MA = D::MA, G = D::G;
-    constexpr bool F32 = std::is_same<real, float>::value;
-    const int lane = t & 63, q = t & 3, v = NV == 4 ? q : 0;
-    desc = ptr.desc[__builtin_amdgcn_readfirstlane((int)(il >> 6))];
-    // (one wait for both: without a march the flag's place is the descriptors')
-    const int stop = *(ptr.done ? ptr.done : &ptr.desc->x);
-    if (ptr.done && stop) return false;
-    const int h0 = desc.x, nh = desc.y;
-    // a wave holds the 16 cells of one tile
-    const int64_t tile = __builtin_amdgcn_readfirstlane((int)(il >> 4));
-    constexpr int RL = 256 / NV;          // rows that the group's threads write at once
-    const int row0 = NV == 4 ? t >> 2 : t;
-    // the list's first HS shares at once (NV = 4: 192 cells; the usual list at
-    // degree 3 has 100, at most 135 in Morton order; a place past the list reads
-    // its first entry, or the pad)
-    constexpr int HS = NV == 4 ? 3 : 1;
-    int hid[HS];
-#pragma unroll
-    for (int k = 0; k < HS; ++k) hid[k] = ptr.hlist[h0 + (row0 + k * RL < nh ? row0 + k * RL : 0)];
-    U0 = ptr.U[il * NV + v];
-    fl = ptr.flags[il] & 7;
-    // row numbers: FP32 those of slots q, q + 4, ... of the lane's cell; FP64
-    // those of slots k, k + 4, ... (k = lane / 16) of cells b, 4 + b, ... (b =
-    // lane / 4 % 4) of the tile
-    const Ids *__restrict__ Sv = reinterpret_cast<const Ids *>(ptr.lslot) + tile * 64;
-    Ids ids[F32 ? 1 : 4];
-    if constexpr (F32) {
-        ids[0] = Sv[lane];
-    } else {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) ids[s] = Sv[(4 * s + ((lane >> 2) & 3)) * 4 + (lane >> 4)];
+    static constexpr int S = D::S, MA = D::MA, NAV = S * MA / 4;
+    typename RowIds<R>::T ids;            // of slots q, q + 4, ... of the lane's cell
+    f32x4 bA[NAV], bB[4];
+    f32x2 tl;
+    __device__ __forceinline__ void request_ids(const uint16_t *lslot, int64_t tile, int lane) {
+        ids = reinterpret_cast<const typename RowIds<R>::T *>(lslot)[tile * 64 + lane];
     }
-    const real *__restrict__ Pt = ptr.P + (size_t)tile * (D::E * 16);
-    auto ldv = [&](int off) { return __builtin_nontemporal_load(reinterpret_cast<const V *>(Pt + off)); };
-    // the whole stream (lanes without an entry read another one's: no more
-    // bytes, and what they hold meets unused rows or zero differences)
-    constexpr int NAV = F32 ? S * MA / 4 : 1;
-    V bA[NAV], bB[F32 ? 4 : 1];
-    f32x2 tl = {0, 0};
-    V dA[F32 ? 1 : 4][5], dB[F32 ? 1 : 4];
-    double dA2[4], dB2[4], dB3[4], dB4[4];
-    // FP64: the four quarters of the tile's cells; two of them are requested at
-    // once, the others when a quarter's products have freed its registers.  At
-    // four waves per SIMD this streams faster than all four quarters at three
-    // (k_stage, 2M cells: 654 against 679 us; three quarters at three waves 690).
-    constexpr int NPRE = 2;
-    auto ld64 = [&](int s) {
-        const int kb = lane >> 2, o2 = q < 2 ? q : 2, s0 = s * (D::E * 4);
-        auto ld1 = [&](int off) { return __builtin_nontemporal_load(Pt + s0 + off); };
-        if constexpr (!F32) {
-            if constexpr (R == 3) {
-#pragma unroll
-                for (int g = 0; g < 4; ++g) dA[s][g] = ldv(s0 + g * 128 + lane * 2);
-                dA[s][4] = ldv(s0 + 512 + (lane & 31) * 2);
-            } else {
-                dA[s][0] = ldv(s0 + lane * 2);
-                dA2[s] = ld1(128 + lane);
-            }
-            constexpr int B0 = R == 3 ? 576 : 192;
-            dB[s] = ldv(s0 + B0 + (kb * 3 + o2) * 2);
-            dB2[s] = ld1(B0 + 96 + kb * 3 + o2);
-            if constexpr (R == 3) {
-                dB3[s] = ld1(B0 + 144 + kb);
-                dB4[s] = ld1(B0 + 160 + (kb & 7));
-            }
-        }
-    };
-    if constexpr (F32) {
-        const int c16 = lane >> 2, o2 = q < 2 ? q : 2;
-#pragma unroll
-        for (int g = 0; g < NAV; ++g) bA[g] = ldv((g * 64 + lane) * 4);
+    __device__ __forceinline__ void request(const float *P, int64_t tile, int lane) {
+        const float *__restrict__ Pt = P + (size_t)tile * (D::E * 16);
+        auto ldv = [&](int off) { return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(Pt + off)); };
+        const int q = lane & 3, c16 = lane >> 2, o2 = q < 2 ? q : 2;
         constexpr int B0 = S * MA * 64;
+        // in the order of their use, so that the products start with the first
 #pragma unroll
-        for (int g = 0; g < 3; ++g) bB[g] = ldv(B0 + ((g * 16 + c16) * 3 + o2) * 4);
-        if constexpr (S > 12) {
-            bB[3] = ldv(B0 + 576 + c16 * 4);
-            tl = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(Pt + B0 + 640 + c16 * 2));
+        for (int g = 0; g < (S + 3) / 4; ++g) {
+#pragma unroll
+            for (int m = 0; m < MA; ++m)
+                if (g * MA + m < NAV) bA[g * MA + m] = ldv(((g * MA + m) * 64 + lane) * 4);
+            if (g < 3) bB[g] = ldv(B0 + ((g * 16 + c16) * 3 + o2) * 4);
+            if (g == 3) bB[3] = ldv(B0 + 576 + c16 * 4);
+            if (g == 4) tl = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(Pt + B0 + 640 + c16 * 2));
         }
-    } else {
-#pragma unroll
-        for (int s = 0; s < NPRE; ++s) ld64(s);
     }
-    __builtin_amdgcn_sched_barrier(0);
-    double hu[HS];
-#pragma unroll
-    for (int k = 0; k < HS; ++k) hu[k] = ptr.U[(int64_t)hid[k] * NV + v];
-    if (NV == 4 || q == 0) rows[(int)(il & 63) * NV + v] = U0;
-#pragma unroll
-    for (int k = 0; k < HS; ++k)
-        if (row0 + k * RL < nh) rows[(64 + row0 + k * RL) * NV + v] = hu[k];
-    for (int r = row0 + HS * RL; r < nh; r += RL)
-        rows[(64 + r) * NV + v] = ptr.U[(int64_t)ptr.hlist[h0 + r] * NV + v];
-    __syncthreads();
-    const char *rv = reinterpret_cast<const char *>(rows) + v * 8;
-    auto row = [&](uint32_t w, int half) -> double {
-        return *reinterpret_cast<const double *>(rv + (half ? w >> 16 : w & 0xFFFFu) * (NV * 8));
-    };
-    if constexpr (F32) {
+    template <int NV>
+    __device__ __forceinline__ void products(const float *, int64_t, const double *rows, int, int v, double U0,
+                                             float (&ao)[D::K], float (&ad)[3][2]) {
+        const char *rv = reinterpret_cast<const char *>(rows) + v * 8;
         f32x4 a[MA], x = {0, 0, 0, 0};
 #pragma unroll
         for (int m = 0; m < MA; ++m) a[m] = f32x4{0, 0, 0, 0};
-        // averages from LDS six slots ahead of their products
+        // averages come from LDS three slots ahead of their products (six would
+        // spill at five waves per SIMD)
         constexpr int LB = 3;
         static_assert(S % LB == 0, "slots in batches");
         double u[2][LB];
@@ -325,7 +286,8 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
 #pragma unroll
             for (int k = 0; k < LB; ++k) {
                 const int j = b * LB + k;
-                u[b & 1][k] = row((uint32_t)quad_bcast_dyn(j & 3, (int)ids[0].w[j / 8]), (j >> 2) & 1);
+                const uint32_t w = (uint32_t)quad_bcast_dyn(j & 3, (int)ids.w[j / 8]);
+                u[b & 1][k] = *reinterpret_cast<const double *>(rv + ((j >> 2) & 1 ? w >> 16 : w & 0xFFFFu) * (NV * 8));
             }
         };
         fetch(0);
@@ -357,7 +319,55 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
 #pragma unroll
             for (int c = 0; c < 4; ++c) ao[4 * m + c] = a[m][c];
         ao[4 * MA] = x[0];
-    } else {
+    }
+};
+
+template <int R>
+struct QuadStream<double, R> {
+    using D = QuadDims<R>;
+    static constexpr int MA = D::MA, G = D::G;
+    // the four quarters of the tile's cells; two of them are requested at once,
+    // the others when a quarter's products have freed its registers.  At four
+    // waves per SIMD this streams faster than all four quarters at three (k_stage,
+    // 2M cells: 654 against 679 us; three quarters at three waves 690).
+    static constexpr int NPRE = 2;
+    typename RowIds<R>::T ids[4];         // of slots k, k + 4, ... (k = lane / 16) of cells 4 s + b (b = lane / 4 % 4)
+    f64x2 dA[4][5], dB[4];
+    double dA2[4], dB2[4], dB3[4], dB4[4];
+    __device__ __forceinline__ void request_ids(const uint16_t *lslot, int64_t tile, int lane) {
+        const auto *Sv = reinterpret_cast<const typename RowIds<R>::T *>(lslot) + tile * 64;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) ids[s] = Sv[(4 * s + ((lane >> 2) & 3)) * 4 + (lane >> 4)];
+    }
+    __device__ __forceinline__ void quarter(const double *P, int64_t tile, int lane, int s) {
+        const double *__restrict__ Pt = P + (size_t)tile * (D::E * 16) + s * (D::E * 4);
+        auto ldv = [&](int off) { return __builtin_nontemporal_load(reinterpret_cast<const f64x2 *>(Pt + off)); };
+        auto ld1 = [&](int off) { return __builtin_nontemporal_load(Pt + off); };
+        const int q = lane & 3, kb = lane >> 2, o2 = q < 2 ? q : 2;
+        constexpr int B0 = R == 3 ? 576 : 192;
+        if constexpr (R == 3) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) dA[s][g] = ldv(g * 128 + lane * 2);
+            dA[s][4] = ldv(512 + (lane & 31) * 2);
+        } else {
+            dA[s][0] = ldv(lane * 2);
+            dA2[s] = ld1(128 + lane);
+        }
+        dB[s] = ldv(B0 + (kb * 3 + o2) * 2);
+        dB2[s] = ld1(B0 + 96 + kb * 3 + o2);
+        if constexpr (R == 3) {
+            dB3[s] = ld1(B0 + 144 + kb);
+            dB4[s] = ld1(B0 + 160 + (kb & 7));
+        }
+    }
+    __device__ __forceinline__ void request(const double *P, int64_t tile, int lane) {
+#pragma unroll
+        for (int s = 0; s < NPRE; ++s) quarter(P, tile, lane, s);
+    }
+    template <int NV>
+    __device__ __forceinline__ void products(const double *P, int64_t tile, const double *rows, int lane, int v, double,
+                                             double (&ao)[D::K], double (&ad)[3][2]) {
+        const char *rv = reinterpret_cast<const char *>(rows) + v * 8;
         // per s: full groups a[m], last group x[g] (row 0 runs on over g, rows
         // 1 and 2 are group g's directional coefficients)
         double a[MA][4], x[4][4];
@@ -367,7 +377,10 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
             const double u0 = rows[((int)(tile & 3) * 16 + 4 * s + ((lane >> 2) & 3)) * NV + v];
             double ug[G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) ug[g] = row(ids[s].w[g / 2], g & 1);
+            for (int g = 0; g < G; ++g) {
+                const uint32_t w = ids[s].w[g / 2];
+                ug[g] = *reinterpret_cast<const double *>(rv + (g & 1 ? w >> 16 : w & 0xFFFFu) * (NV * 8));
+            }
             double am[MA], xg = 0.0;
 #pragma unroll
             for (int m = 0; m < MA; ++m) am[m] = 0.0;
@@ -391,7 +404,7 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
             for (int m = 0; m < MA; ++m) a[m][s] = am[m];
             if (s + NPRE < 4) {
                 __builtin_amdgcn_sched_barrier(0);
-                ld64(s + NPRE);
+                quarter(P, tile, lane, s + NPRE);
             }
         }
         // results have lane 16 i + 4 b + v for row i of cell 4 s + b: swap s and
@@ -411,28 +424,51 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
         rows_to_lanes(x[3]);
         ao[4 * MA] = x[3][0];
     }
+};
+
+// Central and directional coefficients of the lane's variable v, ao = P_c d
+// and ad = P_s d.  il: the cell (below Np), t: the thread in its group's 256;
+// U0: the cell's own average of variable v.  False (the same for the whole
+// grid) when *done is set: the march is over; the flag is waited for together
+// with the descriptor, before anything else is requested.  Holds a block
+// barrier.
+// Everything that is not the neighbours' averages is requested before the
+// first wait; what the group's descriptor leads to (list, then averages) is
+// the only chain.
+template <typename real, int R, int NV>
+__device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double *rows, int64_t il, int t, double &U0,
+                                              int &fl, real (&ao)[QuadDims<R>::K], real (&ad)[3][2]) {
+    const int lane = t & 63, v = NV == 4 ? t & 3 : 0;
+    const int2 desc = ptr.desc[__builtin_amdgcn_readfirstlane((int)(il >> 6))];
+    // (one wait for both: without a march the flag's place is the descriptors')
+    const int stop = *(ptr.done ? ptr.done : &ptr.desc->x);
+    if (ptr.done && stop) return false;
+    const int64_t tile = __builtin_amdgcn_readfirstlane((int)(il >> 4));
+    GroupRows<NV> gr;
+    QuadStream<real, R> qs;
+    gr.list(ptr.hlist, desc, t);
+    U0 = ptr.U[il * NV + v];
+    fl = ptr.flags[il] & 7;
+    qs.request_ids(ptr.lslot, tile, lane);
+    qs.request(ptr.P, tile, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    gr.averages(ptr.U, v);
+    gr.store(rows, ptr.U, ptr.hlist, desc, t, v, U0);
+    __syncthreads();
+    qs.template products<NV>(ptr.P, tile, rows, lane, v, U0, ao, ad);
     return true;
 }
 
-// Reconstruction of cell il by its quad (thread t of its group's 256; rows:
-// the group's LDS rows): the face Gauss-point values of the
-// lane's variable v in out (NV = 1: of the one variable, in every lane), and
-// its selection bytes (DMODE 1).  live: the cell exists (padding cells of the
-// last wave compute on padding data and report nothing).  mid(desc) runs after
-// the products, when the stream's registers are free: the caller's loads for
-// what follows, which the selection's arithmetic then covers.  False when the
-// march is over (out is not set).
-template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS, class Mid>
-__device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconPtrs<real> ptr, double *rows,
-                                           int64_t il, int t, bool live, Mid &&mid, double &U0,
-                                           real (&out)[3][2]) {
+// From the coefficients to the face Gauss-point values of the lane's variable v
+// in out (NV = 1: of the one variable, in every lane), and the cell's selection
+// bytes (DMODE 1).  live: the cell exists (padding cells of the last wave compute
+// on padding data and report nothing).
+template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS>
+__device__ __forceinline__ void recon_finish(const ReconArgs<real> a, const ReconPtrs<real> ptr, int64_t il, int q,
+                                             bool live, double U0, int fl, real (&ao)[QuadDims<R>::K],
+                                             real (&ad)[3][2], real (&out)[3][2]) {
     constexpr int K = QuadDims<R>::K;
-    const int q = t & 3, v = NV == 4 ? q : 0;
-    real ao[K], ad[3][2];
-    int fl;
-    int4 desc;
-    if (!quad_contract<real, R, NV>(ptr, rows, il, t, desc, U0, fl, ao, ad)) return false;
-    mid(desc);
+    const int v = NV == 4 ? q : 0;
     const int adm = 1 | (fl << 1);
     const int st = 1 + __popc(fl);
     // static indices only: a dynamic index into the argument struct would
@@ -452,7 +488,6 @@ __device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconP
         }
         if (SCHEME != CTENO_SCHEME_TENO) ao[k] = st > 1 ? sm * ilam1 : sm;
     }
-    const real *Bt = a.tab + K * K;
     constexpr int NB = VARS ? 3 : 1;      // selection bytes of this lane
     int dbyte[NB];
     if constexpr (VARS == 0) {
@@ -465,7 +500,7 @@ __device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconP
             for (int g = 0; g < 2; ++g) {
                 real val = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) val += Bt[(f * 2 + g) * K + k] * ao[k];
+                for (int k = 0; k < K; ++k) val += a.entry(K * K + (f * 2 + g) * K + k) * ao[k];
                 out[f][g] = (real)(U0 + (double)val);
             }
     } else {
@@ -523,7 +558,7 @@ __device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconP
             for (int g = 0; g < 2; ++g) {
                 real w = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) w += Bt[(f * 2 + g) * K + k] * c1[k];
+                for (int k = 0; k < K; ++k) w += a.entry(K * K + (f * 2 + g) * K + k) * c1[k];
                 real x = 0;
                 x += Rr[0] * quad_bcast<0>(w);
                 x += Rr[1] * quad_bcast<1>(w);
@@ -566,6 +601,22 @@ __device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconP
             for (int f = 0; f < 3; ++f) ptr.delta[(il * 3 + f) * NV + v] = (uint8_t)dbyte[f];
         }
     }
+}
+
+// Reconstruction of cell il by its quad (thread t of its group's 256; rows:
+// the group's LDS rows).  mid() runs after the products, when the stream's
+// registers are free: the caller's loads for what follows, which the
+// selection's arithmetic then covers.  False when the march is over (out is
+// not set).
+template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS, class Mid>
+__device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconPtrs<real> ptr, double *rows,
+                                           int64_t il, int t, bool live, Mid &&mid, double &U0,
+                                           real (&out)[3][2]) {
+    real ao[QuadDims<R>::K], ad[3][2];
+    int fl;
+    if (!quad_contract<real, R, NV>(ptr, rows, il, t, U0, fl, ao, ad)) return false;
+    mid();
+    recon_finish<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, il, t & 3, live, U0, fl, ao, ad, out);
     return true;
 }
 

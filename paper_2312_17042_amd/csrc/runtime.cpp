@@ -283,6 +283,56 @@ static cteno_status upload_tables(DeviceMesh &dm, Alloc &&alloc_raw, hipStream_t
     return CTENO_OK;
 }
 
+// The fused stage's lists in one precision; fits: the side numbers fit
+template <class Alloc>
+static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMesh &dm, bool f32, Alloc &&alloc_raw,
+                                       bool &fits) {
+    StageLists &l = dm.lists[f32];
+    l.bc = f32 && dm.N >= kWideCells && 2 * dm.row_bytes() <= kWideRowBytes ? 256 : 64;
+    const int64_t ng = dm.groups(), nb = dm.stage_blocks(f32);
+    DevBuf cnt(ctx, (size_t)(3 * ng + 1) * sizeof(int32_t));
+    if (!cnt.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    int32_t *c = cnt.as<int32_t>();
+    const BlockCounts bc{c, c + ng, c + 2 * ng, c + 3 * ng};
+    HIP_TRY(hipMemsetAsync(c + 3 * ng, 0, sizeof(int32_t), st));
+    HIP_TRY(launch_block_counts(dm, f32, bc, st));
+    std::vector<int32_t> h((size_t)(3 * ng + 1));
+    HIP_TRY(hipMemcpyAsync(h.data(), c, h.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    dm.n_cross256 = h[3 * ng];
+    std::vector<int2> fd((size_t)nb);
+    int64_t sum[3] = {0, 0, 0};                // faces, cross cells, sides
+    for (int64_t g = 0; g < ng; ++g) {
+        if (g % (l.bc / 64) == 0) fd[g / (l.bc / 64)] = make_int2((int)sum[0], 0);
+        fd[g / (l.bc / 64)].y += h[g];
+        for (int k = 0; k < 3; ++k) {
+            const int32_t n = h[k * ng + g];
+            h[k * ng + g] = (int32_t)sum[k];   // the exclusive sum takes the count's place
+            sum[k] += n;
+        }
+    }
+    l.n_cross = sum[1];
+    l.n_sides = sum[2];
+    fits = sum[2] <= (int64_t)kNbIndexMask;
+    if (!fits) return CTENO_OK;
+    const size_t rs = 4 * (f32 ? sizeof(float) : sizeof(double));
+    l.fdesc = (int2 *)alloc_raw((size_t)nb * sizeof(int2));
+    l.xid = (uint32_t *)alloc_raw((size_t)dm.Np * sizeof(uint32_t));
+    l.frec = alloc_raw((size_t)(sum[0] + 1) * rs);     // (a last block without a listed face reads one past the end)
+    if (sum[1]) {
+        l.xcells = (int2 *)alloc_raw((size_t)sum[1] * sizeof(int2));
+        l.xarea = (double *)alloc_raw((size_t)sum[1] * sizeof(double));
+        l.xrec = alloc_raw((size_t)sum[2] * rs);
+    }
+    if (!l.fdesc || !l.xid || !l.frec || (sum[1] && (!l.xcells || !l.xarea || !l.xrec)))
+        return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    HIP_TRY(h2d(l.fdesc, fd, st));
+    HIP_TRY(hipMemcpyAsync(c, h.data(), (size_t)(3 * ng) * sizeof(int32_t), hipMemcpyHostToDevice, st));
+    HIP_TRY(launch_block_lists(dm, f32, bc, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    return CTENO_OK;
+}
+
 // Uploads a host-built mesh: device arrays, FP64 precompute of the
 // pseudo-inverses (plus the FP32 copy for MIXED), admissibility fix-up.
 // Allocations are appended to bufs; their size is added to bytes.
@@ -383,24 +433,23 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     } else {
         dm.P64 = nullptr;
     }
-    std::vector<int4> desc;
     if (hm.r <= 3) {
         const int64_t ng = dm.groups();
         DevBuf len(ctx, (size_t)ng * sizeof(int32_t));
         if (!len.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
         HIP_TRY(launch_halo_counts(dm, len.as<int32_t>(), st));
         std::vector<int32_t> hl((size_t)ng);
-        desc.resize((size_t)ng);
+        std::vector<int2> desc((size_t)ng);
         HIP_TRY(hipMemcpyAsync(hl.data(), len.p, hl.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         int64_t total = 0;
         for (int64_t g = 0; g < ng; ++g) {
-            desc[g] = make_int4((int)total, hl[g], 0, 0);
+            desc[g] = make_int2((int)total, hl[g]);
             total += hl[g];
             dm.max_halo = std::max(dm.max_halo, (int)hl[g]);
         }
         if (total > INT32_MAX) return fail(CTENO_ERR_INVALID, "neighbour lists too long");
-        dm.desc = alloc_T(int4, (size_t)ng);
+        dm.desc = alloc_T(int2, (size_t)ng);
         dm.hlist = alloc_T(int32_t, (size_t)total + 1);    // (a group without neighbours reads one entry)
         dm.lslot = alloc_T(uint16_t, Np * row_entries(hm.r));
         if (!dm.desc || !dm.hlist || !dm.lslot) return fail(CTENO_ERR_NOMEM, "device allocation failed");
@@ -414,56 +463,15 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
         bufs.push_back(std::move(slots));
     }
     // fused stage (degree <= 3; single meshes -- the batched serving kernels
-    // keep the reconstruction + flux pair): the cells with a face whose
-    // neighbour lies in another 256-cell block, from the face codes
+    // keep the reconstruction + flux pair): its blocks' faces and the cells with
+    // a face to another block, from the face codes
     dm.fused = keep_fr64 && hm.r <= 3 && hm.Nq == 2;
-    if (dm.fused) {
-        const int64_t ng = dm.groups();
-        DevBuf cnt(ctx, (size_t)(3 * ng + 1) * sizeof(int32_t)), base(ctx, (size_t)(2 * ng) * sizeof(int32_t));
-        if (!cnt.p || !base.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
-        int32_t *c = cnt.as<int32_t>();
-        HIP_TRY(hipMemsetAsync(c + 3 * ng, 0, sizeof(int32_t), st));
-        HIP_TRY(launch_block_counts(dm, BlockCounts{c, c + ng, c + 2 * ng, c + 3 * ng}, st));
-        std::vector<int32_t> hc((size_t)(3 * ng + 1)), hb((size_t)(2 * ng));
-        HIP_TRY(hipMemcpyAsync(hc.data(), c, hc.size() * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        int64_t nf = 0, nx = 0, ns = 0;
-        for (int64_t g = 0; g < ng; ++g) {
-            desc[g].z = (int)nf;
-            desc[g].w = hc[g];
-            hb[g] = (int32_t)nx;
-            hb[ng + g] = (int32_t)ns;
-            nf += hc[g];
-            nx += hc[ng + g];
-            ns += hc[2 * ng + g];
+    for (int p = 0; p < 2 && dm.fused; ++p)
+        if (p ? dm.fr32 != nullptr : (s.precision & CTENO_FP64) != 0) {
+            bool fits = true;
+            if (cteno_status rc = upload_stage_lists(ctx, st, dm, p == 1, alloc_raw, fits)) return rc;
+            dm.fused = fits;               // (else the separate kernels)
         }
-        if (ns > (int64_t)kNbIndexMask) {
-            dm.fused = false;              // the side numbers do not fit: separate kernels
-        } else {
-            dm.n_cross = nx;
-            dm.n_sides = ns;
-        }
-        dm.n_cross256 = hc[3 * ng];
-        if (dm.fused) {
-            dm.xid = alloc_T(uint32_t, Np);
-            // (a last group without a listed face reads the record past the end)
-            if (dm.fr32) dm.frec32 = alloc_T(float, 4 * (nf + 1));
-            if (dm.fr64) dm.frec64 = alloc_T(double, 4 * (nf + 1));
-            if (nx) {
-                dm.xcells = alloc_T(int2, nx);
-                dm.xarea = alloc_T(double, nx);
-                if (dm.fr32) dm.xrec32 = alloc_T(float, 4 * ns);
-                if (dm.fr64) dm.xrec64 = alloc_T(double, 4 * ns);
-            }
-            if (!dm.xid || (dm.fr32 && !dm.frec32) || (dm.fr64 && !dm.frec64) ||
-                (nx && (!dm.xcells || !dm.xarea || (dm.fr32 && !dm.xrec32) || (dm.fr64 && !dm.xrec64))))
-                return fail(CTENO_ERR_NOMEM, "device allocation failed");
-            HIP_TRY(h2d(dm.desc, desc, st));
-            HIP_TRY(hipMemcpyAsync(base.p, hb.data(), hb.size() * sizeof(int32_t), hipMemcpyHostToDevice, st));
-            HIP_TRY(launch_block_lists(dm, base.as<int32_t>(), base.as<int32_t>() + ng, st));
-        }
-        HIP_TRY(hipStreamSynchronize(st));
-    }
     // release host-only copies that the device now holds
     hm.slot.clear(); hm.slot.shrink_to_fit();
     hm.slot_flag.clear(); hm.slot_flag.shrink_to_fit();
@@ -641,7 +649,7 @@ struct cteno_sol {
     void *xt() {
         if (!xterm.p) {
             const DeviceMesh &dm = mesh->dm;
-            xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.n_sides, 1) * dm.nv * sizeof(float));
+            xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.lists[1].n_sides, 1) * dm.nv * sizeof(float));
         }
         return xterm.p;
     }
@@ -899,6 +907,12 @@ namespace {
 // asks for the separate reconstruction and flux kernels
 bool use_fused(const cteno_ctx *ctx, const DeviceMesh &dm, bool) { return dm.fused && ctx->fused_stage; }
 
+// whether the second stage kernel sums its cells' faces itself (FP32 in blocks
+// of 64 cells)
+bool needs_terms(const cteno_ctx *ctx, const DeviceMesh &dm, bool f32) {
+    return f32 && use_fused(ctx, dm, f32) && dm.lists[1].bc == 64;
+}
+
 // one SSP-RK3 stage on sol; dt from a device pointer or a host value
 hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const double *dt_ptr, double dt_value,
                        Ctrl *ctrl, double *dt_part, hipStream_t st) {
@@ -922,7 +936,7 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
     fl.dt_part = dt_part;
     fl.t_base = s->t;
     if (use_fused(ctx, dm, f32)) {
-        if (f32) fl.xterm = s->xt();
+        if (needs_terms(ctx, dm, f32)) fl.xterm = s->xt();
         hipError_t e = timed(ctx, 0, [&] { return launch_stage(dm, f32, fl, done, 0, st, &ss->fallbacks); });
         if (e != hipSuccess) return e;
         return timed(ctx, 1, [&] { return launch_stage(dm, f32, fl, done, 1, st, &ss->fallbacks); });
@@ -934,7 +948,7 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
 
 // the work buffers of a stage, allocated before it is issued or captured
 bool stage_buffers(cteno_ctx *ctx, cteno_sol *s, bool f32) {
-    return s->fv(f32) && (!f32 || !use_fused(ctx, s->mesh->dm, f32) || s->xt());
+    return s->fv(f32) && (!needs_terms(ctx, s->mesh->dm, f32) || s->xt());
 }
 }  // namespace
 
@@ -960,7 +974,7 @@ hipError_t issue_step(cteno_ctx *ctx, cteno_sol *s, bool f32, hipStream_t st) {
     Ctrl *c = s->ctrl.as<Ctrl>();
     double *part = s->dt_part.as<double>();
     const DeviceMesh &dm = s->mesh->dm;
-    hipError_t e = launch_control(c, part, dm.dt_parts(use_fused(ctx, dm, f32)), 0, st);
+    hipError_t e = launch_control(c, part, dm.dt_parts(use_fused(ctx, dm, f32), f32), 0, st);
     for (int stage = 0; stage < 3 && e == hipSuccess; ++stage)
         e = issue_stage(ctx, s, f32, stage, &c->dt, 0.0, c, stage == 2 ? part : nullptr, st);
     return e;
@@ -989,7 +1003,7 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
     h.dt_cand_bits = 0x7FF0000000000000ull;
     HIP_TRY(hipMemcpyAsync(dc, &h, sizeof(Ctrl), hipMemcpyHostToDevice, st));
     HIP_TRY(launch_dt_partials(dm, f32, s->U[0].as<double>(), s->dt_part.as<double>(),
-                               dm.dt_parts(use_fused(ctx, dm, f32)), st));
+                               dm.dt_parts(use_fused(ctx, dm, f32), f32), st));
 
     // graphs need a capturable stream: the context's own stream when the
     // caller uses the null stream

@@ -3,7 +3,11 @@ full, one square over and one short; and a caller numbering that scatters
 neighbours, so that a group's neighbour list takes several rounds to load and
 most faces lead to other groups.  Against the FP64 oracle, 1e-12 normwise per
 variable in FP64 (round-off of the same arithmetic in another order), 1e-5 in
-mixed precision (FP32 reconstruction and fluxes)."""
+mixed precision (FP32 reconstruction and fluxes).  Large mixed meshes, whose fused
+stage runs in blocks of four groups, at last blocks of one, three and four
+groups and with a numbering too scattered for them, against the separate
+kernels, which the other tests hold to the oracle: 1e-6, some FP32 roundings of
+the fluxes over two steps."""
 import numpy as np
 import pytest
 
@@ -56,3 +60,28 @@ def test_group_edges(ctx, degree, problem, nx, ny, scatter):
             assert relerr(s.download()[0], uo) < tol
         s.close()
     m.close()
+
+
+@pytest.mark.parametrize("nx,ny,scatter", [(781, 769, False), (800, 751, False), (800, 752, False), (781, 769, True)])
+def test_wide_blocks(ctx, nx, ny, scatter):
+    mesh = W.split_jitter_mesh(nx, ny, (0.0, 10.0, 0.0, 10.0), seed=31)
+    u0 = W.cell_average(mesh, W.isentropic_vortex(0.0, 3.0, (5.0, 5.0), (10.0, 10.0)), n=2)
+    if scatter:
+        order = np.random.default_rng(7).permutation(mesh.n_cells)
+        mesh.tri = np.ascontiguousarray(mesh.tri[order])
+        u0 = np.ascontiguousarray(u0[:, order])
+    m = T.Mesh.from_workload(ctx, mesh, precision=T.MIXED, reorder=0 if scatter else 1, physics=O.EULER,
+                             scheme=O.CTENOZ, degree=3, lambda1_prime=1e4)
+    s = T.Solution(m, u0)
+    got = []
+    try:
+        for fused in (False, True):
+            ctx.set_fused_stage(fused)
+            s.set(u0, 0.0)
+            assert s.solve(max_steps=2, cfl=0.3, precision=T.MIXED) == 2
+            got.append(s.download()[0])
+    finally:
+        ctx.set_fused_stage(True)
+        s.close()
+        m.close()
+    assert relerr(got[1], got[0]) < 1e-6
