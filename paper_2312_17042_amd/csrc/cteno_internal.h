@@ -44,9 +44,13 @@ inline int dims_S(int r) {
     return dims_M(r) > 3 * dims_Md(r) ? dims_M(r) : 3 * dims_Md(r);
 }
 inline int dims_Nq(int r) { return (r + 2) / 2; }
-// r >= 4: every slot carries K central and K_d directional entries, padded
-// to a multiple of 4 so each slot is a whole number of 16-byte vectors
-inline int ho_slot_entries(int r) { return (dims_K(r) + dims_Kd(r) + 3) / 4 * 4; }
+// r >= 4: every slot carries K central and K_d directional entries; scalar
+// physics pads them to a multiple of 4, so that a lane per cell reads each slot
+// as a whole number of 16-byte vectors
+inline int ho_slot_entries(int r, int nv) {
+    const int n = dims_K(r) + dims_Kd(r);
+    return nv == 1 ? (n + 3) / 4 * 4 : n;
+}
 
 // tiled index: per-cell array with E entries, 64-cell tiles, entry-major inside a tile
 __host__ __device__ inline size_t tix(int64_t i, int e, int E) {
@@ -69,8 +73,8 @@ inline int round_up(int a, int b) { return (a + b - 1) / b * b; }
 __host__ __device__ constexpr int pinv_offset(int j, int K) {
     return j <= 12 ? j * (K + 2) : 12 * (K + 2) + (j - 12) * K;
 }
-inline int pinv_entries(int r) {
-    return r <= 3 ? pinv_offset(dims_S(r), dims_K(r)) : dims_S(r) * ho_slot_entries(r);
+inline int pinv_entries(int r, int nv) {
+    return r <= 3 ? pinv_offset(dims_S(r), dims_K(r)) : dims_S(r) * ho_slot_entries(r, nv);
 }
 // r <= 3: the stream feeds 4 x 4 matrix instructions, four coefficients (rows)
 // by the variables (columns).  The K + 2 coefficients of a slot form MA full row
@@ -143,10 +147,42 @@ __host__ __device__ inline size_t quad_index_entry(int64_t i, int e, int VW) {
     const int j = e < 12 * (K + 2) ? e / (K + 2) : 12 + (e - 12 * (K + 2)) / K;
     return quad_index<R>(i, j, e - pinv_offset(j, K), VW);
 }
-// r >= 4: vector-tiled stream with tiles of CT cells (CT = 64 / nv: one lane
-// per cell and variable), VW = 4 (FP32) or 2 (FP64) entries per vector
-__host__ __device__ inline size_t hvix(int64_t i, int e, int E, int VW, int CT) {
-    return ((((size_t)(i / CT) * (E / VW) + e / VW) * CT + (i % CT)) * VW) + (e % VW);
+// Degree 4 to 6, Euler: the K + K_d coefficients of a slot as NF full row groups
+// of four and REM rows more, in tiles of 16 cells.  Coefficient e of slot j:
+//   FP32 (VW 4): by groups of four slots (two in degree 6's last).  Lane 4 c + o
+//   has row o of cell c: per row group a vector of its entries in slot order;
+//   the REM rows likewise without gaps.
+//   FP64 (VW 2): by cells 4 s + b, then groups of four slots.  Lane 16 k + 4 b +
+//   o has slot 4 g + k, row o: row groups in pairs (a vector), then a single one,
+//   then the REM rows without gaps.
+template <int R>
+struct HoRows {
+    static constexpr int K = (R + 1) * (R + 2) / 2 - 1;
+    static constexpr int RD = (R + 1) / 2;
+    static constexpr int C = K + (RD + 1) * (RD + 2) / 2 - 1;
+    static constexpr int S = R == 6 ? 54 : 2 * K;
+    static constexpr int NF = C / 4, REM = C % 4;
+    static constexpr int G = (S + 3) / 4, TAIL = S % 4;    // slots of an incomplete last group
+    static constexpr int E = S * C;
+    static_assert(REM == 0 || TAIL == 0, "an incomplete group of slots has full row groups only");
+};
+template <int R>
+__host__ __device__ inline size_t ho_index(int64_t i, int j, int e, int VW) {
+    using D = HoRows<R>;
+    const int c16 = (int)(i & 15), g = j >> 2, k = j & 3, m = e / 4, o = e % 4;
+    const size_t base = (size_t)(i >> 4) * (D::E * 16);
+    if (VW == 4) {
+        const size_t b = base + (size_t)g * (64 * D::C);
+        if (D::TAIL && g == D::G - 1) return b + (size_t)(m * 64 + 4 * c16 + o) * D::TAIL + k;
+        if (m < D::NF) return b + (size_t)(m * 64 + 4 * c16 + o) * 4 + k;
+        return b + D::NF * 256 + (size_t)(c16 * D::REM + o) * 4 + k;
+    }
+    const int n = D::TAIL && g == D::G - 1 ? 4 * D::TAIL : 16;     // (slot, cell) pairs of the group
+    const int kb = 4 * k + (c16 & 3), lane = 4 * kb + o;
+    const size_t b = base + (size_t)(c16 >> 2) * (D::E * 4) + (size_t)g * (16 * D::C);
+    if (m < (D::NF & ~1)) return b + (size_t)((m / 2) * 4 * n + lane) * 2 + m % 2;
+    if (m < D::NF) return b + (size_t)m * 4 * n + lane;
+    return b + (size_t)D::NF * 4 * n + kb * D::REM + o;
 }
 
 // neighbour code per cell face: bit 31 set = boundary (bits 0..1 = kind),

@@ -438,17 +438,17 @@ __device__ __forceinline__ int32_t row_cell(const uint16_t *lslot, const int2 *d
     const int r = lslot[lslot_index<R>(i, j)];
     return r < 64 ? (int32_t)((i & ~int64_t(63)) + r) : hlist[desc[i >> 6].x + r - 64];
 }
-// RL: the degree at r <= 3, 4 for the higher ones, 0 for the slot table
+// RL: the degree, 0 for the slot table and for one variable above degree 3
 template <int RL>
 __global__ void k_gather_entries(int n, const int32_t *idx, int E, int VW, const double *s64, const float *s32,
-                                 const int32_t *si, double *dst, int ct) {
+                                 const int32_t *si, double *dst) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (int64_t)n * E) return;
     const int a = (int)(t / E), e = (int)(t % E);
     size_t src;
     if constexpr (RL == 0) src = avix(idx[a], e, E, VW);
     else if constexpr (RL <= 3) src = quad_index_entry<RL>(idx[a], e, VW);
-    else src = hvix(idx[a], e, E, VW, ct);
+    else src = ho_index<RL>(idx[a], e / HoRows<RL>::C, e % HoRows<RL>::C, VW);
     dst[t] = s64 ? s64[src] : (s32 ? (double)s32[src] : (double)si[src]);
 }
 template <int R>
@@ -463,14 +463,16 @@ hipError_t launch_gather_entries(const DeviceMesh &m, int n, const int32_t *idx,
     const int VW = src64 ? 2 : 4;
     const dim3 grid(grid_for((int64_t)n * E)), block(256);
 #define GE_LAUNCH(RL) \
-    hipLaunchKernelGGL((k_gather_entries<RL>), grid, block, 0, st, n, idx, E, VW, src64, src32, srci, dst, m.stile)
+    hipLaunchKernelGGL((k_gather_entries<RL>), grid, block, 0, st, n, idx, E, VW, src64, src32, srci, dst)
     if (!src64 && !src32 && !srci) {
         if (m.r == 2) hipLaunchKernelGGL(k_gather_cells<2>, grid, block, 0, st, n, idx, E, m.lslot, m.desc, m.hlist, dst);
         else hipLaunchKernelGGL(k_gather_cells<3>, grid, block, 0, st, n, idx, E, m.lslot, m.desc, m.hlist, dst);
-    } else if (srci) GE_LAUNCH(0);
+    } else if (srci || (m.r >= 4 && m.nv == 1)) GE_LAUNCH(0);
     else if (m.r == 2) GE_LAUNCH(2);
     else if (m.r == 3) GE_LAUNCH(3);
-    else GE_LAUNCH(4);
+    else if (m.r == 4) GE_LAUNCH(4);
+    else if (m.r == 5) GE_LAUNCH(5);
+    else GE_LAUNCH(6);
 #undef GE_LAUNCH
     return hipGetLastError();
 }

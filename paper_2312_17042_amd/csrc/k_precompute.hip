@@ -297,14 +297,13 @@ hipError_t launch_precompute(const DeviceMesh &m, const PrecomputeInputs &in, hi
 // ===========================================================================
 // orders 5 to 7 (r = 4..6)
 // ===========================================================================
-// The pseudo-inverse stream of a cell has S slots of EPS entries: K central,
-// K_d directional (those of the directional stencil that holds the slot's
-// cell; zero for a cell of none), zero padding to a multiple of 4.  At
-// degrees 4 and 5 the slots are exactly the M central cells; at degree 6
-// (M = 3 M_d) three groups of M_d slots, each group's members first.  It is
-// vector-tiled with tiles of CT = 64 / nv cells: the reconstruction runs one
-// lane per (cell, variable), so a wave covers CT cells and its lanes of one
-// cell read the same 16-byte vector.
+// The pseudo-inverse stream of a cell has S slots of K central and K_d
+// directional entries (those of the directional stencil that holds the slot's
+// cell; zero for a cell of none).  At degrees 4 and 5 the slots are exactly the
+// M central cells; at degree 6 (M = 3 M_d) three groups of M_d slots, each
+// group's members first.  Its order in memory is ho_index's, the one the matrix
+// instructions read; for one variable, with a lane per cell, slots padded to a
+// multiple of 4 entries and vector-tiled (avix).
 
 // sum over the wave; the butterfly adds the same pairs in every lane, so all
 // lanes hold bitwise the same result
@@ -326,7 +325,7 @@ struct PreHoArgs {
     int *rank_fail;
     double *P64;
     float *P32;
-    int ct;                  // cells per stream tile
+    int nv;
     double Lx, Ly;
     int ex[D::K][2];
     double mean[D::K];
@@ -349,9 +348,11 @@ __global__ __launch_bounds__(256) void k_precompute_ho(const PreHoArgs<R> a) {
     if (i >= a.N) return;                 // whole waves; a wave only touches its own LDS
     double (*cA)[64] = sA[wv];
     double (*cD)[64] = sD[wv];
-    auto put = [&](int e, double v) {
-        a.P64[hvix(i, e, E, 2, a.ct)] = v;
-        if (a.P32) a.P32[hvix(i, e, E, 4, a.ct)] = (float)v;
+    // coefficient e of slot j
+    auto put = [&](int j, int e, double v) {
+        const int es = j * EPS + e;
+        a.P64[a.nv == 1 ? avix(i, es, E, 2) : ho_index<R>(i, j, e, 2)] = v;
+        if (a.P32) a.P32[a.nv == 1 ? avix(i, es, E, 4) : ho_index<R>(i, j, e, 4)] = (float)v;
     };
 
     // reference map of cell i: v0 and J = [v1 - v0, v2 - v0]
@@ -454,7 +455,7 @@ __global__ __launch_bounds__(256) void k_precompute_ho(const PreHoArgs<R> a) {
             if (lane == k) xo = xk;
             if (lane < k) b -= cA[k][lane] * xk;
         }
-        if (lane < K) put(m * EPS + lane, rank_ok ? xo : 0.0);
+        if (lane < K) put(m, lane, rank_ok ? xo : 0.0);
     }
 
     // directional systems: stencil s owns the contiguous rows [base, base +
@@ -512,7 +513,7 @@ __global__ __launch_bounds__(256) void k_precompute_ho(const PreHoArgs<R> a) {
                 if (lane == base + k) xo = xk;
                 if (lane >= base && lane < base + k) b -= cD[k][lane] * xk;
             }
-            if (lane >= base && lane < base + KD) put(mrow * EPS + K + (lane - base), ok ? xo : 0.0);
+            if (lane >= base && lane < base + KD) put(mrow, K + (lane - base), ok ? xo : 0.0);
         }
     }
     if (lane == 0) a.flags[i] = flg;
@@ -521,12 +522,12 @@ __global__ __launch_bounds__(256) void k_precompute_ho(const PreHoArgs<R> a) {
 template <int R>
 static hipError_t precompute_ho_r(const DeviceMesh &m, const PrecomputeInputs &in, hipStream_t st) {
     using D = HoDims<R>;
-    if (m.S != D::S || m.E != D::E || m.SP != D::SP) return hipErrorInvalidValue;
+    if (m.S != D::S || m.E != (m.nv == 1 ? D::E : HoRows<R>::E) || m.SP != D::SP) return hipErrorInvalidValue;
     PreHoArgs<R> a;
     a.N = m.N;
     a.verts = in.verts; a.slot = m.slot; a.slot_flag = in.slot_flag; a.slot_shift = in.slot_shift;
     a.flags = in.flags; a.rank_fail = in.rank_fail;
-    a.P64 = m.P64; a.P32 = m.P32; a.ct = m.stile;
+    a.P64 = m.P64; a.P32 = m.P32; a.nv = m.nv;
     a.Lx = m.Lx; a.Ly = m.Ly;
     for (int k = 0; k < D::K; ++k) {
         a.ex[k][0] = m.tab.ex[k][0];

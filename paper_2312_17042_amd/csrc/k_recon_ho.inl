@@ -1,6 +1,15 @@
-// Reconstruction of degree 4 to 6 (orders 5 to 7; a quad of lanes per Euler
-// cell, a lane per cell for advection) for one arithmetic type;
+// Reconstruction of degree 4 to 6 (orders 5 to 7) for one arithmetic type;
 // instantiated per type by k_recon_ho_f32.hip and k_recon_ho_f64.hip.
+//
+// A cell streams 532 (degree 4) to 1944 (degree 6) pseudo-inverse entries, which
+// bounds the kernel as long as enough of them are in flight.  For the Euler
+// equations the products run on the matrix cores as at degree 3 (recon_quad.h):
+// rows are coefficients, columns the variables, the inner index the slots, each
+// sum taken slot after slot with one rounding a term.  Against vector sums of
+// four variables a lane, with two slots in flight: FP32, 500k cells of degree 6
+// 870 -> 726 us (3.9 GB, 5.4 TB/s), 7k cells 42 -> 23 us; FP64, 215k cells of
+// degree 4 224 -> 176 us (1.0 GB, 5.7 TB/s), 9.5k cells of degree 5 42 -> 21 us.
+// One variable keeps a lane per cell.
 #pragma once
 #include "recon_quad.h"
 
@@ -25,6 +34,9 @@ struct ReconHoArgs {
     // the p_1 step's factors: (p_opt - p1_ls sum_s lambda_s p_s) / p1_l1,
     // (1, lambda_1) for the CTENO family, (0, 1) for TENO, which keeps p_opt
     real p1_ls, p1_l1;
+    __device__ __forceinline__ real entry(int k) const {
+        return ((const __attribute__((address_space(4))) real *)tab)[k];
+    }
 };
 
 // one lane's field (a conserved variable, or a characteristic field on one
@@ -45,7 +57,7 @@ __device__ __forceinline__ int finish_field_ho(const ReconHoArgs<real> a, real (
         for (int p = 0; p < K; ++p) {
             real rp = 0;
 #pragma unroll
-            for (int q = 0; q < K; ++q) rp += a.tab[p * K + q] * c1[q];
+            for (int q = 0; q < K; ++q) rp += a.entry(p * K + q) * c1[q];
             si[0] += c1[p] * rp;
         }
 #pragma unroll
@@ -55,7 +67,7 @@ __device__ __forceinline__ int finish_field_ho(const ReconHoArgs<real> a, real (
             for (int p = 0; p < KD; ++p) {
                 real rp = 0;
 #pragma unroll
-                for (int q = 0; q < KD; ++q) rp += a.tab[p * K + q] * cd[s][q];
+                for (int q = 0; q < KD; ++q) rp += a.entry(p * K + q) * cd[s][q];
                 sv += cd[s][p] * rp;
             }
             si[s + 1] = sv;
@@ -99,257 +111,288 @@ __device__ __forceinline__ int finish_field_ho(const ReconHoArgs<real> a, real (
     return bits;
 }
 
-// Coefficient e of the slot stream is accumulated by lane (e / VW) % 4 of
-// the quad, in its round (e / VW) / 4, component e % VW, for the GF full
-// rounds of four vectors; the four entries past them (the spread tail) by
-// lane e - 4 GF VW.  These hand coefficients e0, e0 + 1, ... to the variable
-// lanes.
-template <typename real, int VW, int GF, int e>
-__device__ __forceinline__ real ho_take1(const real (&acc)[GF][VW][4], const real (&acs)[4], int v) {
-    if constexpr (e < 4 * GF * VW) return quad_take<(e / VW) % 4>(acc[e / VW / 4][e % VW], v);
-    else return quad_take<e - 4 * GF * VW>(acs, v);
+// Row groups of a slot: NC hold central coefficients, those from D0 on
+// directional ones (degree 4 and 6: group NC - 1 = D0 holds both).
+template <int R>
+struct HoGroups {
+    using D = HoRows<R>;
+    static constexpr int M = D::NF + (D::REM > 0);        // all
+    static constexpr int NC = (D::K + 3) / 4, D0 = D::K / 4, ND = M - D0;
+    static constexpr bool MIXED = D0 < NC;
+};
+
+// With variable groups (degrees 4 and 5) each directional row keeps three sums:
+// a slot's products enter the sum of the stencil that its entry names, and with
+// zero differences the other two.  These are the slot's differences for the
+// three (a difference that is not finite stays so in all of them).
+template <typename real>
+__device__ __forceinline__ void ho_split(real d, uint32_t group, real (&ds)[3]) {
+    const real z = d * 0;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) ds[s] = group == (uint32_t)s ? d : z;
 }
 
-template <typename real, int VW, int GF, int e0, int n, int... k>
-__device__ __forceinline__ void ho_take(const real (&acc)[GF][VW][4], const real (&acs)[4], int v, real (&out)[n],
-                                        std::integer_sequence<int, k...>) {
-    ((out[k] = ho_take1<real, VW, GF, e0 + k>(acc, acs, v)), ...);
-}
-
-// an empty asm statement that takes x and gives it back, so that x is
-// computed here (not volatile: a volatile statement would count as a
-// possible store and turn the uniform table loads after it into vector loads)
-template <typename T>
-__device__ __forceinline__ void opaque(T &x) { asm("" : "+v"(x)); }
-
-// whether some lane of a quad holds a directional entry (e in [K, K + K_d))
-// at component c of its vector in round t
-template <int K, int KD, int VW>
-constexpr bool ho_dir_any(int t, int c) {
-    for (int u = 0; u < 4; ++u) {
-        const int e = (4 * t + u) * VW + c;
-        if (e >= K && e < K + KD) return true;
-    }
-    return false;
-}
-
-// a_opt = P_c d and a_s = P_s d for the four variables of a cell held by a
-// quad of lanes.  The lanes split each slot's stream instead of each reading
-// all of it: lane q loads the stream vectors q, q + 4, ... and accumulates
-// their coefficients for all four variables (the differences d come from
-// the variable lanes by DPP moves); the coefficients go to their variable
-// lanes at the end (and, with fixed groups of M_d slots, at the end of each
-// group).  Every coefficient sums its slots in slot order, as a lane per
-// variable would.  With variable groups (degrees 4 and 5), where a slot's
-// directional stencil comes with its index, the positions that hold a
-// directional entry in some lane keep three sums, one per stencil: a
-// directional entry enters the sum of its slot's stencil only, a central
-// entry enters the first sum at every slot.
-// Where the slot ends in a partial round of four scalars (r = 4 and 6: one
-// float4 or two double2 vectors), lane q reads scalar q of it, so no lane
-// multiplies a vector it does not own.
-template <typename real, int R>
-__device__ __forceinline__ void ho_contract_quad(const ReconHoArgs<real> a, int64_t i, int v, double U0,
-                                                 real (&ao)[HoDims<R>::K], real (&ad)[3][HoDims<R>::KD]) {
-    using D = HoDims<R>;
-    constexpr int K = D::K, KD = D::KD, MD = D::MD, S = D::S, SP = D::SP, EPS = D::EPS, E = D::E;
-    constexpr bool VARG = D::VARG;
-    constexpr int CT = 16;
-    using V = typename Vec<real>::T;
-    constexpr int VW = Vec<real>::W;
-    constexpr int SV = EPS / VW;          // stream vectors per slot
-    constexpr int GF = SV / 4;            // full rounds of four vectors
-    constexpr bool SPREAD = SV % 4 != 0;  // a tail of four scalars follows
-    static_assert(!SPREAD || (SV % 4) * VW == 4, "a partial round must hold four scalars");
-    const V *__restrict__ Pv = reinterpret_cast<const V *>(a.P) + (size_t)(i / CT) * (E / VW) * CT + (i % CT);
-    // this lane's tail scalar of slot j: Pr[j * SV * CT * VW]
-    const real *__restrict__ Pr =
-        reinterpret_cast<const real *>(Pv) + ((4 * GF + v / VW) * CT) * VW + v % VW;
-    const int32_t *__restrict__ Si = a.slot + (size_t)(i >> 6) * (SP / 4) * 256 + (i & 63) * 4;
-    // acc: central sums and (fixed groups) the current group's directional
-    // sums, or (variable groups) those of stencil 0; ag[0], ag[1]: those of
-    // stencils 1 and 2 (variable groups, directional positions only)
-    real acc[GF][VW][4], acs[4], ag[2][GF][VW][4], ags[2][4];
+// FP32: a_opt = P_c d and a_s = P_s d of the lane's cell and variable, 16 cells
+// per wave.  The row groups' results have a lane per variable with four
+// coefficients each.  Two groups of slots are in flight ahead of the products (18
+// KB a wave at degree 6); 160 to 220 registers, two or three waves per SIMD:
+// held to three, degree 6 spills (726 -> 784 us, to four 1206).
+template <int R>
+__device__ __forceinline__ void ho_contract(const ReconHoArgs<float> a, int64_t i, int lane, double U0,
+                                            float (&ao)[HoDims<R>::K], float (&ad)[3][HoDims<R>::KD]) {
+    using D = HoRows<R>;
+    using H = HoGroups<R>;
+    constexpr int K = D::K, KD = D::C - K, NF = D::NF, REM = D::REM, G = D::G, MD = HoDims<R>::MD;
+    constexpr bool VARG = HoDims<R>::VARG;
+    constexpr int L = 2, NB = L + 1;
+    const int q = lane & 3, c16 = lane >> 2;
+    const float *__restrict__ Pt = a.P + (size_t)(i >> 4) * (D::E * 16);
+    const int32_t *__restrict__ Si = a.slot + (size_t)(i >> 6) * (HoDims<R>::SP / 4) * 256 + (i & 63) * 4 + q;
+    const double *__restrict__ Uv = a.U + q;
+    uint32_t ent[G];                      // slot 4 g + q's
 #pragma unroll
-    for (int t = 0; t < GF; ++t)
+    for (int g = 0; g < G; ++g) ent[g] = (uint32_t)Si[g * 256];
+    f32x4 b[NB][H::M];
+    double u[NB][4];
+    auto request = [&](int g) {
+        const float *__restrict__ Pg = Pt + g * (64 * D::C);
+        const bool tail = D::TAIL && g == G - 1;
 #pragma unroll
-        for (int c = 0; c < VW; ++c)
+        for (int k = 0; k < 4; ++k)
+            if (!tail || k < D::TAIL)
+                u[g % NB][k] = Uv[(int64_t)((uint32_t)quad_bcast_dyn(k, (int)ent[g]) & kSlotIndexMask) * 4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[t][c][u] = ag[0][t][c][u] = ag[1][t][c][u] = 0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acs[u] = ags[0][u] = ags[1][u] = 0;
-    // this lane's entries that belong to a directional polynomial
-    bool isdir[GF][VW];
-#pragma unroll
-    for (int t = 0; t < GF; ++t)
-#pragma unroll
-        for (int c = 0; c < VW; ++c) {
-            const int e = (4 * t + v) * VW + c;
-            isdir[t][c] = e >= K && e < K + KD;
+        for (int m = 0; m < NF; ++m) {
+            if (!tail) b[g % NB][m] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(Pg) + m * 64 + lane);
+            else {
+                const f32x2 x = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(Pg) + m * 64 + lane);
+                b[g % NB][m] = f32x4{x[0], x[1], 0, 0};
+            }
         }
-    const int es = 4 * GF * VW + v;
-    const bool isdirs = es >= K && es < K + KD;
-    constexpr bool DIRS = SPREAD && 4 * GF * VW + 3 >= K && 4 * GF * VW < K + KD;
-    // Slot j's stream vectors and neighbour averages are requested when slot
-    // j - 2 has been used and its entry when slot j - 4 has: the loop takes
-    // the slots in pairs with a buffer per slot of the pair, so that no load
-    // is waited for before its slot (a rotating buffer waits at the copy,
-    // and the compiler had turned the earlier rotating version into loads
-    // at the top of each slot, waited for at once).  The scheduling
-    // barriers keep each pair's loads behind the slot that frees the buffer.
-    static_assert(S % 2 == 0, "slots are taken in pairs (or one by one)");
-    auto ld_stream = [&](int j, V (&b)[GF], real &bs) {
-        const int jc = j < S ? j : S - 1;
-#pragma unroll
-        for (int t = 0; t < GF; ++t) b[t] = Pv[(jc * SV + 4 * t + v) * CT];
-        if constexpr (SPREAD) bs = Pr[(size_t)jc * SV * CT * VW];
+        if constexpr (REM > 0)
+            b[g % NB][NF] = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(Pg + NF * 256) + c16 * REM +
+                                                       (q < REM ? q : REM - 1));
     };
-    auto ld_entry = [&](int j) {
-        const int jc = j < S ? j : S - 1;
-        return (uint32_t)Si[(jc >> 2) * 256 + (jc & 3)];
-    };
-    const double *__restrict__ Ug = a.U;
-    auto ld_avg = [Ug, v](uint32_t se) { return Ug[(int64_t)(se & kSlotIndexMask) * 4 + v]; };
-    // one slot: differences of the quad's four variables, products with
-    // this lane's stream vectors (b, bs), group sums (g: the slot's stencil)
-    double uc = U0;                       // the cell's own average, loaded before the loop
-    opaque(uc);                           // (pending at the loop it would cost a full wait per pair)
-    auto slot_step = [&](const V (&b)[GF], real bs, double u, int g, int j) {
-        const real dv = (real)(u - uc);
-        const real d[4] = {quad_bcast<0>(dv), quad_bcast<1>(dv), quad_bcast<2>(dv), quad_bcast<3>(dv)};
+    f32x4 C[H::NC], X[VARG ? 3 : 1][H::ND];
 #pragma unroll
-        for (int t = 0; t < GF; ++t)
+    for (int m = 0; m < H::NC; ++m) C[m] = f32x4{0, 0, 0, 0};
 #pragma unroll
-            for (int c = 0; c < VW; ++c) {
-                const real p = comp(b[t], c);
-                if (VARG && ho_dir_any<K, KD, VW>(t, c)) {
-                    const real p0 = (isdir[t][c] && g != 0) ? (real)0 : p;
-                    const real p1 = g == 1 ? p : (real)0, p2 = g == 2 ? p : (real)0;
+    for (int s = 0; s < (VARG ? 3 : 1); ++s)
 #pragma unroll
-                    for (int u4 = 0; u4 < 4; ++u4) {
-                        acc[t][c][u4] += p0 * d[u4];
-                        ag[0][t][c][u4] += p1 * d[u4];
-                        ag[1][t][c][u4] += p2 * d[u4];
-                    }
-                } else {
+        for (int m = 0; m < H::ND; ++m) X[s][m] = f32x4{0, 0, 0, 0};
+    auto mma = [](float p, float d, f32x4 &x) { x = __builtin_amdgcn_mfma_f32_4x4x1f32(p, d, x, 0, 0, 0); };
 #pragma unroll
-                    for (int u4 = 0; u4 < 4; ++u4) acc[t][c][u4] += p * d[u4];
+    for (int g = 0; g < L; ++g) request(g);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (g + L < G) request(g + L);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j = 4 * g + k;
+            if (j >= D::S) break;
+            const float d = (float)(u[g % NB][k] - U0);
+#pragma unroll
+            for (int m = 0; m < H::NC; ++m) mma(b[g % NB][m][k], d, C[m]);
+            if constexpr (VARG) {
+                float ds[3];
+                ho_split<float>(d, (uint32_t)quad_bcast_dyn(k, (int)ent[g]) >> kSlotGroupShift, ds);
+#pragma unroll
+                for (int m = 0; m < H::ND; ++m)
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) mma(b[g % NB][H::D0 + m][k], ds[s], X[s][m]);
+            } else {
+#pragma unroll
+                for (int m = 0; m < H::ND; ++m) mma(b[g % NB][H::D0 + m][k], d, X[0][m]);
+                if (j % MD == MD - 1) {   // directional group j / MD is complete
+#pragma unroll
+                    for (int e = 0; e < KD; ++e) ad[j / MD][e] = X[0][(K + e) / 4 - H::D0][(K + e) % 4];
+#pragma unroll
+                    for (int m = 0; m < H::ND; ++m) X[0][m] = f32x4{0, 0, 0, 0};
                 }
             }
-        if constexpr (SPREAD) {
-            if constexpr (VARG && DIRS) {
-                const real p0 = (isdirs && g != 0) ? (real)0 : bs;
-                const real p1 = g == 1 ? bs : (real)0, p2 = g == 2 ? bs : (real)0;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 #pragma unroll
-                for (int u4 = 0; u4 < 4; ++u4) {
-                    acs[u4] += p0 * d[u4];
-                    ags[0][u4] += p1 * d[u4];
-                    ags[1][u4] += p2 * d[u4];
+    for (int e = 0; e < K; ++e) ao[e] = C[e / 4][e % 4];
+    if constexpr (VARG)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int e = 0; e < KD; ++e) ad[s][e] = X[s][(K + e) / 4 - H::D0][(K + e) % 4];
+}
+
+// FP64: the four waves of a block take four of its 16 cells each (an instruction
+// takes four slots of four cells; a wave with all 16 would hold 36 to 64 results
+// beside the stream) and leave the coefficients in LDS, where one wave finds
+// those of its lane's cell and variable: row r of lane l at ho_place(r, l).
+// Results have lane 16 i + 4 b + v for row i: the swizzle spreads the rows of a
+// store over the banks.  With characteristic variables three waves find them, one
+// per face: each face has its own fields to select (122k cells of degree 6: 357
+// us a stage; 935 with one wave for the three faces, 825 with vector sums).
+__device__ __forceinline__ int ho_place(int row, int l) { return row * 64 + (l ^ ((row & 3) * 16)); }
+
+template <int R>
+__device__ __forceinline__ bool ho_contract_share(const ReconHoArgs<double> a, int64_t i0, int s, int lane,
+                                                  double *coef) {
+    using D = HoRows<R>;
+    using H = HoGroups<R>;
+    constexpr int K = D::K, KD = D::C - K, NF = D::NF, REM = D::REM, G = D::G, MD = HoDims<R>::MD;
+    constexpr bool VARG = HoDims<R>::VARG;
+    constexpr int NP = NF / 2;            // row groups in pairs
+    // groups of four slots in flight ahead of the products (4, 3, 2: 3.6 to 5 KB
+    // each; one more or less measures the same)
+    constexpr int L = 8 - R, NB = L + 1;
+    const int k = lane >> 4, b = (lane >> 2) & 3, v = lane & 3;
+    const int64_t i = i0 + 4 * s + b;
+    const double *__restrict__ Pt = a.P + (size_t)(i0 >> 4) * (D::E * 16) + s * (D::E * 4);
+    const int32_t *__restrict__ Si = a.slot + (size_t)(i >> 6) * (HoDims<R>::SP / 4) * 256 + (i & 63) * 4 + k;
+    const double *__restrict__ Uv = a.U + v;
+    const int stop = *(a.done ? a.done : a.slot);
+    uint32_t ent[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) ent[g] = (uint32_t)Si[g * 256];
+    const double u0 = Uv[i * 4];
+    f64x2 p2[NB][NP];
+    double p1[NB][NF % 2 + 1], pr[NB];
+    auto request = [&](int g) {
+        const bool tail = D::TAIL && g == G - 1;          // (lanes without a slot: another one's, zero differences)
+        const int n = tail ? 4 * D::TAIL : 16, l = tail ? lane & (4 * n - 1) : lane;
+        const double *__restrict__ Pg = Pt + g * (16 * D::C);
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+            p2[g % NB][p] = __builtin_nontemporal_load(reinterpret_cast<const f64x2 *>(Pg) + p * 4 * n + l);
+        if constexpr (NF % 2 != 0) p1[g % NB][0] = __builtin_nontemporal_load(Pg + (NF - 1) * 4 * n + l);
+        if constexpr (REM > 0)
+            pr[g % NB] = __builtin_nontemporal_load(Pg + NF * 4 * n + (lane >> 2) * REM + (v < REM ? v : REM - 1));
+    };
+#pragma unroll
+    for (int g = 0; g < L; ++g) request(g);
+    __builtin_amdgcn_sched_barrier(0);
+    if (a.done && stop) return false;
+    double u[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) u[g] = Uv[(int64_t)(ent[g] & kSlotIndexMask) * 4];
+    __builtin_amdgcn_sched_barrier(0);
+    double C[H::NC], X[VARG ? 3 : 1][H::ND];
+#pragma unroll
+    for (int m = 0; m < H::NC; ++m) C[m] = 0;
+#pragma unroll
+    for (int t = 0; t < (VARG ? 3 : 1); ++t)
+#pragma unroll
+        for (int m = 0; m < H::ND; ++m) X[t][m] = 0;
+    auto mma = [](double p, double d, double &x) { x = __builtin_amdgcn_mfma_f64_4x4x4f64(p, d, x, 0, 0, 0); };
+    auto put = [&](int row, double x) { coef[ho_place(row + k, 16 * s + (lane & 15))] = x; };
+    auto put_dir = [&](int t, const double (&x)[H::ND]) { // rows of stencil t
+#pragma unroll
+        for (int m = 0; m < H::ND; ++m) {
+            const int e = 4 * (H::D0 + m) + k - K;
+            if (e >= 0 && e < KD) coef[ho_place(K + t * KD + e, 16 * s + (lane & 15))] = x[m];
+        }
+    };
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if (g + L < G) request(g + L);
+        __builtin_amdgcn_sched_barrier(0);
+        const double d = u[g] - u0;
+        double p[H::M];
+#pragma unroll
+        for (int m = 0; m < NF; ++m) p[m] = m < 2 * NP ? p2[g % NB][m / 2][m % 2] : p1[g % NB][0];
+        if constexpr (REM > 0) p[NF] = pr[g % NB];
+#pragma unroll
+        for (int m = 0; m < H::NC; ++m) mma(p[m], d, C[m]);
+        if constexpr (VARG) {
+            double ds[3];
+            ho_split<double>(d, ent[g] >> kSlotGroupShift, ds);
+#pragma unroll
+            for (int m = 0; m < H::ND; ++m)
+#pragma unroll
+                for (int t = 0; t < 3; ++t) mma(p[H::D0 + m], ds[t], X[t][m]);
+        } else {
+            // a directional group may end inside these four slots
+            const int t = 4 * g / MD, e = (t + 1) * MD - 4 * g;   // its slots here: k < e
+            if (e < 4) {
+                const double d0 = k < e ? d : 0.0, d1 = k < e ? 0.0 : d;
+#pragma unroll
+                for (int m = 0; m < H::ND; ++m) mma(p[H::D0 + m], d0, X[0][m]);
+                put_dir(t, X[0]);
+#pragma unroll
+                for (int m = 0; m < H::ND; ++m) {
+                    X[0][m] = 0;
+                    if (t < 2) mma(p[H::D0 + m], d1, X[0][m]);
                 }
             } else {
 #pragma unroll
-                for (int u4 = 0; u4 < 4; ++u4) acs[u4] += bs * d[u4];
+                for (int m = 0; m < H::ND; ++m) mma(p[H::D0 + m], d, X[0][m]);
+                if (e == 4) {
+                    put_dir(t, X[0]);
+#pragma unroll
+                    for (int m = 0; m < H::ND; ++m) X[0][m] = 0;
+                }
             }
         }
-        if (!VARG && j % MD == MD - 1) {  // uniform: group j / MD is complete
-            real x[KD];
-            ho_take<real, VW, GF, K, KD>(acc, acs, v, x, std::make_integer_sequence<int, KD>{});
-            const int s = j / MD;
-            if (s == 0) {
-#pragma unroll
-                for (int k = 0; k < KD; ++k) ad[0][k] = x[k];
-            } else if (s == 1) {
-#pragma unroll
-                for (int k = 0; k < KD; ++k) ad[1][k] = x[k];
-            } else {
-#pragma unroll
-                for (int k = 0; k < KD; ++k) ad[2][k] = x[k];
-            }
-#pragma unroll
-            for (int t = 0; t < GF; ++t)
-#pragma unroll
-                for (int c = 0; c < VW; ++c)
-#pragma unroll
-                    for (int u4 = 0; u4 < 4; ++u4) acc[t][c][u4] = isdir[t][c] ? (real)0 : acc[t][c][u4];
-#pragma unroll
-            for (int u4 = 0; u4 < 4; ++u4) acs[u4] = isdirs ? (real)0 : acs[u4];
-        }
-    };
-    // FP64 at degree 6: one buffer (its second would cost a wave per SIMD)
-    constexpr bool PAIRS = !(sizeof(real) == 8 && R == 6);
-    V bA[GF], bB[GF];
-    real sA = 0, sB = 0;
-    ld_stream(0, bA, sA);
-    uint32_t eA = ld_entry(0), eB = ld_entry(1);
-    double uA = ld_avg(eA), uB = 0;
-    int gA = (int)(eA >> kSlotGroupShift), gB = 0;
-    if constexpr (PAIRS) {
-        ld_stream(1, bB, sB);
-        uB = ld_avg(eB);
-        gB = (int)(eB >> kSlotGroupShift);
-        eA = ld_entry(2);
-        eB = ld_entry(3);
-#pragma unroll 1
-        for (int j = 0; j < S; j += 2) {
-            slot_step(bA, sA, uA, gA, j);
-            __builtin_amdgcn_sched_barrier(0);
-            ld_stream(j + 2, bA, sA);
-            gA = (int)(eA >> kSlotGroupShift);
-            opaque(gA);                   // taken now: eA's register is free for the next entry
-            uA = ld_avg(eA);
-            eA = ld_entry(j + 4);
-            __builtin_amdgcn_sched_barrier(0);
-            slot_step(bB, sB, uB, gB, j + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            ld_stream(j + 3, bB, sB);
-            gB = (int)(eB >> kSlotGroupShift);
-            opaque(gB);
-            uB = ld_avg(eB);
-            eB = ld_entry(j + 5);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    } else {
-        eA = eB;
-#pragma unroll 1
-        for (int j = 0; j < S; ++j) {
-            slot_step(bA, sA, uA, gA, j);
-            __builtin_amdgcn_sched_barrier(0);
-            ld_stream(j + 1, bA, sA);
-            gA = (int)(eA >> kSlotGroupShift);
-            opaque(gA);
-            uA = ld_avg(eA);
-            eA = ld_entry(j + 2);
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (VARG) {
-        ho_take<real, VW, GF, K, KD>(acc, acs, v, ad[0], std::make_integer_sequence<int, KD>{});
-        ho_take<real, VW, GF, K, KD>(ag[0], ags[0], v, ad[1], std::make_integer_sequence<int, KD>{});
-        ho_take<real, VW, GF, K, KD>(ag[1], ags[1], v, ad[2], std::make_integer_sequence<int, KD>{});
-    }
-    ho_take<real, VW, GF, 0, K>(acc, acs, v, ao, std::make_integer_sequence<int, K>{});
+    if constexpr (VARG)
+#pragma unroll
+        for (int t = 0; t < 3; ++t) put_dir(t, X[t]);
+#pragma unroll
+    for (int m = 0; m < H::NC; ++m)
+        if (4 * m + k < K) put(4 * m, C[m]);
+    return true;
 }
+
+// cells of a block: 256 lanes, a quad each (FP32 Euler), four waves for 16
+// (FP64 Euler), or one lane each
+template <typename real, int NV>
+constexpr int ho_block_cells() { return NV == 1 ? 256 : std::is_same<real, float>::value ? 64 : 16; }
 
 template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS>
-__global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> a) {
+__global__ __launch_bounds__(256, (VARS && std::is_same<real, float>::value) || NV == 1 ? 1 : 2) void k_reconstruct_ho(const ReconHoArgs<real> a) {
     using D = HoDims<R>;
-    constexpr int K = D::K, KD = D::KD, MD = D::MD, S = D::S, SP = D::SP, EPS = D::EPS, E = D::E, NQ = D::NQ;
-    constexpr int CT = 64 / NV;
+    constexpr int K = D::K, KD = D::KD, NQ = D::NQ;
+    constexpr int BC = ho_block_cells<real, NV>();
+    const int64_t blk = xcd_block(blockIdx.x, gridDim.x);
+    const int v = threadIdx.x % NV;
+    const int64_t i = blk * BC + (BC == 16 ? (threadIdx.x & 63) : threadIdx.x) / NV;
+    const bool live = i < a.N;            // (padding cells compute on padding data and store nothing)
+    if (NV == 1 && !live) return;
+    const double U0 = a.U[i * NV + v];
+    const int fl = a.flags[i] & 7;
+
+    constexpr bool FACES = VARS && BC == 16;      // a wave per face
+    int face = 0;
+    real ao[K], ad[3][KD];
+    if constexpr (NV == 4 && std::is_same<real, float>::value) {
+        if (a.done && *a.done) return;
+        ho_contract<R>(a, i, threadIdx.x & 63, U0, ao, ad);
+    } else if constexpr (NV == 4) {
+        __shared__ double coef[(K + 3 * KD) * 64];
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        if (!ho_contract_share<R>(a, blk * 16, wave, lane, coef)) return;
+        __syncthreads();
+        // characteristic variables: three of the waves take a face each
+        if constexpr (FACES) face = wave;
+        if (VARS ? wave == 3 : wave != (int)(blk & 3)) {
+            if (VARS && a.positivity) __syncthreads();    // (the cells' flags, below)
+            return;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) ao[k] = coef[ho_place(k, lane)];
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int k = 0; k < KD; ++k) ad[s][k] = coef[ho_place(K + s * KD + k, lane)];
+    } else {
+    constexpr int MD = D::MD, S = D::S, SP = D::SP, EPS = D::EPS, E = D::E, CT = 64;
     using V = typename Vec<real>::T;
     constexpr int VW = Vec<real>::W;
     constexpr int SV = EPS / VW;          // stream vectors per slot
-    const int64_t i = xcd_block(blockIdx.x, gridDim.x) * (256 / NV) + threadIdx.x / NV;
-    const int v = threadIdx.x % NV;
-    if (i >= a.N) return;                 // all lanes of a cell leave together
     if (a.done && *a.done) return;
     const V *__restrict__ Pv = reinterpret_cast<const V *>(a.P) + (size_t)(i / CT) * (E / VW) * CT + (i % CT);
     const int32_t *__restrict__ Si = a.slot + (size_t)(i >> 6) * (SP / 4) * 256 + (i & 63) * 4;
-    const double U0 = a.U[i * NV + v];
-
-    real ao[K], ad[3][KD];
-    if constexpr (NV == 4) {
-        ho_contract_quad<real, R>(a, i, v, U0, ao, ad);
-    } else {
     // a_opt = P_c d and a_s = P_s d, slot by slot (one lane per cell); the
     // next slot's stream vectors and entry are requested before the current
     // slot is used.  Variable groups: a slot's directional entries go to the
@@ -403,7 +446,6 @@ __global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> 
     }
     }
 
-    const int fl = a.flags[i] & 7;
     const int adm = 1 | (fl << 1);
     const int st = 1 + __popc(fl);
     const real lams = st == 2 ? a.lams[2] : (st == 3 ? a.lams[3] : a.lams[4]);
@@ -426,7 +468,6 @@ __global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> 
             ao[k] = st > 1 ? sm * il1 : sm;
         }
     }
-    const real *Bt = a.tab + K * K;
     real out[3][NQ];
     constexpr int NB = VARS ? 3 : 1;              // selection bytes of this lane
     int dbyte[NB];
@@ -440,7 +481,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> 
             for (int q = 0; q < NQ; ++q) {
                 real val = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) val += Bt[(f * NQ + q) * K + k] * ao[k];
+                for (int k = 0; k < K; ++k) val += a.entry(K * K + (f * NQ + q) * K + k) * ao[k];
                 out[f][q] = (real)(U0 + (double)val);
             }
     } else {
@@ -448,16 +489,13 @@ __global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> 
         // coefficients are projected with row v of L_f using the cell's
         // other lanes, the face values come back through row v of R_f
         static_assert(NV == 4, "characteristic variables need the Euler equations");
-        const int l0 = (threadIdx.x & 63) & ~3;
-        const double Ud[4] = {__shfl(U0, l0, 64), __shfl(U0, l0 + 1, 64), __shfl(U0, l0 + 2, 64),
-                              __shfl(U0, l0 + 3, 64)};
+        const double Ud[4] = {quad_bcast<0>(U0), quad_bcast<1>(U0), quad_bcast<2>(U0), quad_bcast<3>(U0)};
         const real rho = (real)Ud[0], uu = (real)(Ud[1] / Ud[0]), vv = (real)(Ud[2] / Ud[0]);
         const real q2 = (real)0.5 * (uu * uu + vv * vv);
         const real pr = (a.gamma - 1) * ((real)Ud[3] - rho * q2);
         const real cs = fsqrt(fdiv(a.gamma * pr, rho)), H = fdiv((real)Ud[3] + pr, rho);
         const real b1 = fdiv(a.gamma - 1, cs * cs), b2 = b1 * q2, ic = frcp(cs);
-#pragma unroll
-        for (int f = 0; f < 3; ++f) {
+        auto char_face = [&](int f, real (&of)[NQ]) -> int {
             real nx, ny, len;
             uint32_t code;
             face_record<real>(a.fr, i, f, nx, ny, len, code);
@@ -478,73 +516,87 @@ __global__ __launch_bounds__(256) void k_reconstruct_ho(const ReconHoArgs<real> 
                 Lr[2] = (real)-0.5 * (b1 * vv - ny * ic); Lr[3] = (real)0.5 * b1;
                 Rr[0] = H - un * cs; Rr[1] = q2; Rr[2] = ut; Rr[3] = H + un * cs;
             }
+            auto project = [](const real (&row)[4], real x) -> real {
+                real y = 0;
+                y += row[0] * quad_bcast<0>(x);
+                y += row[1] * quad_bcast<1>(x);
+                y += row[2] * quad_bcast<2>(x);
+                y += row[3] * quad_bcast<3>(x);
+                return y;
+            };
             real c1[K], cd[3][KD];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                real x = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) x += Lr[u] * __shfl(ao[k], l0 + u, 64);
-                c1[k] = x;
-            }
+            for (int k = 0; k < K; ++k) c1[k] = project(Lr, ao[k]);
 #pragma unroll
             for (int s2 = 0; s2 < 3; ++s2)
 #pragma unroll
-                for (int k = 0; k < KD; ++k) {
-                    real x = 0;
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) x += Lr[u] * __shfl(ad[s2][k], l0 + u, 64);
-                    cd[s2][k] = x;
-                }
-            dbyte[f] = finish_field_ho<real, K, KD, SCHEME, GFORM, DMODE>(
+                for (int k = 0; k < KD; ++k) cd[s2][k] = project(Lr, ad[s2][k]);
+            const int db = finish_field_ho<real, K, KD, SCHEME, GFORM, DMODE>(
                 a, c1, cd, fl, adm, st, lams, lratio, DMODE == 2 ? a.delta[(i * 3 + f) * NV + v] : 0);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 real w = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) w += Bt[(f * NQ + q) * K + k] * c1[k];
-                real x = 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) x += Rr[u] * __shfl(w, l0 + u, 64);
-                out[f][q] = (real)(U0 + (double)x);
+                for (int k = 0; k < K; ++k) w += a.entry(K * K + (f * NQ + q) * K + k) * c1[k];
+                of[q] = (real)(U0 + (double)project(Rr, w));
             }
+            return db;
+        };
+        if constexpr (FACES) {
+            dbyte[0] = char_face(face, out[0]);
+        } else {
+#pragma unroll
+            for (int f = 0; f < 3; ++f) dbyte[f] = char_face(f, out[f]);
         }
     }
     if constexpr (NV == 4) if (a.positivity) {
         // optional positivity fallback (not in the paper; density or
         // pressure <= 0 at a Gauss point): the four lanes of the cell
         // exchange their values
-        const int l0 = (threadIdx.x & 63) & ~3;
         bool bad = false;
 #pragma unroll
-        for (int f = 0; f < 3; ++f)
+        for (int f = 0; f < (FACES ? 1 : 3); ++f)
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                const real r0 = __shfl(out[f][q], l0, 64), r1 = __shfl(out[f][q], l0 + 1, 64);
-                const real r2 = __shfl(out[f][q], l0 + 2, 64), r3 = __shfl(out[f][q], l0 + 3, 64);
+                const real r0 = quad_bcast<0>(out[f][q]), r1 = quad_bcast<1>(out[f][q]);
+                const real r2 = quad_bcast<2>(out[f][q]), r3 = quad_bcast<3>(out[f][q]);
                 const real pr = euler_pressure(a.gamma, r0, r1, r2, r3);
                 bad |= !(r0 > 0) || !(pr > 0);
             }
-        if (bad) {
+        if constexpr (FACES) {
+            __shared__ int badf[3][64];           // of the faces' waves
+            badf[face][threadIdx.x & 63] = bad;
+            __syncthreads();
+            bad = badf[0][threadIdx.x & 63] | badf[1][threadIdx.x & 63] | badf[2][threadIdx.x & 63];
+        }
+        if (bad && live) {
 #pragma unroll
             for (int f = 0; f < 3; ++f)
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) out[f][q] = (real)U0;
 #pragma unroll
             for (int k = 0; k < NB; ++k) dbyte[k] |= 0x80;
-            if (v == 0 && a.fb_count) atomicAdd(a.fb_count, 1ull);
+            if (v == 0 && face == 0 && a.fb_count) atomicAdd(a.fb_count, 1ull);
         }
     }
+    if (!live) return;
     if (DMODE == 1) {
         if constexpr (VARS == 0) a.delta[i * NV + v] = (uint8_t)dbyte[0];
+        else if constexpr (FACES) a.delta[(i * 3 + face) * NV + v] = (uint8_t)dbyte[0];
         else {
 #pragma unroll
             for (int f = 0; f < 3; ++f) a.delta[(i * 3 + f) * NV + v] = (uint8_t)dbyte[f];
         }
     }
+    if constexpr (FACES) {
 #pragma unroll
-    for (int f = 0; f < 3; ++f)
+        for (int q = 0; q < NQ; ++q) a.FV[((i * 3 + face) * NQ + q) * NV + v] = out[0][q];
+    } else {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) a.FV[((i * 3 + f) * NQ + q) * NV + v] = out[f][q];
+        for (int f = 0; f < 3; ++f)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) a.FV[((i * 3 + f) * NQ + q) * NV + v] = out[f][q];
+    }
 }
 
 template <typename real, int R, int NV>
@@ -558,7 +610,7 @@ static hipError_t reconstruct_ho_t(const DeviceMesh &m, const double *U, void *F
     a.flags = m.flags;
     if constexpr (std::is_same<real, double>::value) { a.P = m.P64; a.tab = m.htab64; }
     else { a.P = m.P32; a.tab = m.htab32; }
-    if (!a.P || !a.tab || m.stile != 64 / NV || m.E != D::E) return hipErrorInvalidValue;
+    if (!a.P || !a.tab || m.E != (NV == 1 ? D::E : HoRows<R>::E)) return hipErrorInvalidValue;
     if constexpr (std::is_same<real, double>::value) a.fr = m.fr64;
     else a.fr = m.fr32;
     if (m.vars == CTENO_VARS_CHARACTERISTIC && (NV != 4 || !a.fr)) return hipErrorInvalidValue;
@@ -579,7 +631,8 @@ static hipError_t reconstruct_ho_t(const DeviceMesh &m, const double *U, void *F
     }
     a.p1_ls = m.scheme == CTENO_SCHEME_TENO ? (real)0 : (real)1;
     a.p1_l1 = m.scheme == CTENO_SCHEME_TENO ? (real)1 : a.lam1;
-    const unsigned grid = (unsigned)((m.N * NV + 255) / 256);
+    constexpr int BC = ho_block_cells<real, NV>();
+    const unsigned grid = (unsigned)((m.N + BC - 1) / BC);
 #define HO_LAUNCH(SCH, GF, DM)                                                                               \
     do {                                                                                                     \
         if constexpr (NV == 4)                                                                               \

@@ -69,7 +69,6 @@ struct DeviceMesh {
     int vars = 0;                  // CTENO_VARS_CONSERVED | CTENO_VARS_CHARACTERISTIC
     int E = 0;                     // pseudo-inverse entries per cell
     int Kd = 0, Md = 0, Nq = 2;    // directional basis size and members, Gauss points per face
-    int stile = 64;                // cells per stream tile (r >= 4: 64 / nv)
     double gamma = 1.4, ax = 0, ay = 0, lam1p = 1e4, ct = 1e-6, eps = 1e-12;
     double Lx = 0, Ly = 0;
     int32_t *slot = nullptr;       // vector-tiled [SP], VW 4 (r <= 3: while the mesh is uploaded)
@@ -84,7 +83,7 @@ struct DeviceMesh {
     double *fr64 = nullptr;        // face records, vector-tiled [12], VW 2
     float *fr32 = nullptr;         // face records, vector-tiled [12], VW 4
     double *area = nullptr;        // [Np]
-    double *P64 = nullptr;         // pseudo-inverse stream [Np][E] (r <= 3 quad_index, else hvix; VW 2)
+    double *P64 = nullptr;         // pseudo-inverse stream [Np][E] (r <= 3 quad_index, else ho_index, one variable avix; VW 2)
     float *P32 = nullptr;          // pseudo-inverse stream [Np][E] (VW 4)
     int32_t *perm = nullptr;       // internal -> user [N]
     double *bface = nullptr;       // [n_inflow][4]: first vertex and edge vector of each inflow face

@@ -349,7 +349,6 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     dm.N = hm.N; dm.Np = pad64(hm.N);
     dm.r = hm.r; dm.K = hm.K; dm.S = hm.S; dm.nv = hm.nv;
     dm.Kd = hm.Kd; dm.Md = hm.Md; dm.Nq = hm.Nq;
-    dm.stile = hm.r >= 4 ? kTile / hm.nv : kTile;
     dm.physics = s.physics; dm.scheme = s.scheme; dm.gamma_form = s.gamma_form; dm.precision = s.precision;
     dm.vars = s.variables;
     dm.positivity = s.physics == CTENO_EULER ? s.positivity : 0;
@@ -358,7 +357,7 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     make_ref_tables(hm.r, dm.tab);
     const size_t Np = (size_t)dm.Np, S = hm.S;
     dm.SP = hm.SP;
-    dm.E = pinv_entries(hm.r);
+    dm.E = pinv_entries(hm.r, hm.nv);
     // r <= 3: only the row numbers (below) stay
     DevBuf slots(ctx, Np * hm.SP * sizeof(int32_t));
     if (!slots.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
@@ -578,7 +577,7 @@ extern "C" cteno_status cteno_mesh_pinv(cteno_ctx *ctx, const cteno_mesh *m, int
             for (int q = 0; q < M; ++q) if (cen[q] == src_u) cpos = q;
             if (cpos < 0) return fail(CTENO_ERR_DEVICE, "slot not in stencil");
             // slot j: K central entries, then (slots of the directional groups) K_d directional ones
-            const int off = hm.r >= 4 ? j * ho_slot_entries(hm.r) : pinv_offset(j, K);
+            const int off = hm.r >= 4 ? j * ho_slot_entries(hm.r, hm.nv) : pinv_offset(j, K);
             if (central)
                 for (int k = 0; k < K; ++k) central[((size_t)a * K + k) * M + cpos] = pe[(size_t)a * E + off + k];
             if (grp < 3 && directional) {
@@ -1178,7 +1177,7 @@ namespace {
 void slot_footprint(const cteno_server *sv, int64_t N, int64_t &steady, int64_t &transient) {
     const int r = sv->scheme.degree;
     const int64_t Np = pad64(N);
-    const int64_t E = pinv_entries(r);
+    const int64_t E = pinv_entries(r, 4);
     const int S = dims_S(r), SP = round_up(S, 4);
     steady = Np * (E * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 8;
     transient = Np * (E * 8 + 6 * 8 + S + 2 * S) + 64;

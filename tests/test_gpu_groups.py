@@ -8,6 +8,8 @@ stage runs in blocks of four groups, at last blocks of one, three and four
 groups and with a numbering too scattered for them, against the separate
 kernels, which the other tests hold to the oracle: 1e-6, some FP32 roundings of
 the fluxes over two steps."""
+import math
+
 import numpy as np
 import pytest
 
@@ -85,3 +87,50 @@ def test_wide_blocks(ctx, nx, ny, scatter):
         s.close()
         m.close()
     assert relerr(got[1], got[0]) < 1e-6
+
+
+def gauss_basis(r):
+    """The degree-r basis (monomials less their means over the reference
+    triangle) at the faces' Gauss points, [3][N_q][K]."""
+    ex = [(d - k, k) for d in range(1, r + 1) for k in range(d + 1)]
+    mean = [2.0 * math.factorial(a) * math.factorial(b) / math.factorial(a + b + 2) for a, b in ex]
+    g = 0.5 * (np.polynomial.legendre.leggauss((r + 2) // 2)[0] + 1.0)
+    v = np.array([[0.0, 0.0], [1.0, 0.0], [0.0, 1.0]])
+    x = v[:, None] + g[:, None] * (np.roll(v, -1, 0) - v)[:, None]
+    return np.stack([x[..., 0] ** a * x[..., 1] ** b - m for (a, b), m in zip(ex, mean)], -1)
+
+
+@pytest.mark.parametrize("degree", [4, 5, 6])
+@pytest.mark.parametrize("nx,ny,scatter", [(16, 12, False), (12, 11, False), (15, 9, False), (24, 23, True)])
+def test_high_order_products(ctx, degree, nx, ny, scatter):
+    """Degree 4 to 6 with the last 16 cells of a wave full and cut off: each
+    polynomial in turn, selected by force, against its products with the mesh's
+    own pseudo-inverses, within the rounding bound of sums of that length."""
+    mesh = W.split_jitter_mesh(nx, ny, (0.0, 10.0, 0.0, 10.0), seed=31)
+    u0 = W.cell_average(mesh, W.isentropic_vortex(0.0, 3.0, (5.0, 5.0), (10.0, 10.0)), n=4)
+    if scatter:
+        order = np.random.default_rng(7).permutation(mesh.n_cells)
+        mesh.tri = np.ascontiguousarray(mesh.tri[order])
+        u0 = np.ascontiguousarray(u0[:, order])
+    m = T.Mesh.from_workload(ctx, mesh, precision=T.BOTH, physics=O.EULER, scheme=O.TENO, degree=degree,
+                             lambda1_prime=1e4)
+    s = T.Solution(m, u0)
+    cen, dr, dn = m.stencils()
+    B = gauss_basis(degree)
+    N = mesh.n_cells
+    for prec, eps in ((T.FP64, 2.0**-53), (T.MIXED, 2.0**-24)):
+        Pc, Pd = m.pinv(np.arange(N), prec)
+        for bit in range(4):
+            P, st = (Pc, cen) if bit == 0 else (Pd[:, bit - 1], dr[:, bit - 1])
+            d = np.where(st[:, None] >= 0, u0.T[np.maximum(st, 0)].transpose(0, 2, 1) - u0.T[:, :, None], 0.0)
+            b = B[..., :P.shape[1]]
+            want = u0.T[:, None, None] + np.einsum("fqk,nkj,nvj->nfqv", b, P, d)
+            mag = np.einsum("fqk,nkj,nvj->nfqv", np.abs(b), np.abs(P), np.abs(d))
+            on = np.ones(N, bool) if bit == 0 else dn[:, bit - 1] > 0
+            assert on.any()
+            forced = np.full((N, 4), 1 << bit, np.uint8)
+            got = s.reconstruct(prec, forced=forced)[0].cpu().numpy()
+            bound = 2 * (P.shape[1] + P.shape[2] + 6) * eps * mag + 2 * eps * np.abs(want)
+            assert (np.abs(got - want) <= bound)[on].all(), (prec, bit)
+    s.close()
+    m.close()
