@@ -495,7 +495,9 @@ __global__ __launch_bounds__(256, (VARS && std::is_same<real, float>::value) || 
         const real pr = (a.gamma - 1) * ((real)Ud[3] - rho * q2);
         const real cs = fsqrt(fdiv(a.gamma * pr, rho)), H = fdiv((real)Ud[3] + pr, rho);
         const real b1 = fdiv(a.gamma - 1, cs * cs), b2 = b1 * q2, ic = frcp(cs);
-        auto char_face = [&](int f, real (&of)[NQ]) -> int {
+#pragma unroll
+        for (int w = 0; w < (FACES ? 1 : 3); ++w) {
+            const int f = FACES ? face : w;
             real nx, ny, len;
             uint32_t code;
             face_record<real>(a.fr, i, f, nx, ny, len, code);
@@ -531,22 +533,15 @@ __global__ __launch_bounds__(256, (VARS && std::is_same<real, float>::value) || 
             for (int s2 = 0; s2 < 3; ++s2)
 #pragma unroll
                 for (int k = 0; k < KD; ++k) cd[s2][k] = project(Lr, ad[s2][k]);
-            const int db = finish_field_ho<real, K, KD, SCHEME, GFORM, DMODE>(
+            dbyte[w] = finish_field_ho<real, K, KD, SCHEME, GFORM, DMODE>(
                 a, c1, cd, fl, adm, st, lams, lratio, DMODE == 2 ? a.delta[(i * 3 + f) * NV + v] : 0);
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
-                real w = 0;
+                real x = 0;
 #pragma unroll
-                for (int k = 0; k < K; ++k) w += a.entry(K * K + (f * NQ + q) * K + k) * c1[k];
-                of[q] = (real)(U0 + (double)project(Rr, w));
+                for (int k = 0; k < K; ++k) x += a.entry(K * K + (f * NQ + q) * K + k) * c1[k];
+                out[w][q] = (real)(U0 + (double)project(Rr, x));
             }
-            return db;
-        };
-        if constexpr (FACES) {
-            dbyte[0] = char_face(face, out[0]);
-        } else {
-#pragma unroll
-            for (int f = 0; f < 3; ++f) dbyte[f] = char_face(f, out[f]);
         }
     }
     if constexpr (NV == 4) if (a.positivity) {
