@@ -295,20 +295,21 @@ __global__ void k_state_to_user(int64_t N, int nv, const int32_t *perm, const do
     const int64_t u = perm[k];
     for (int v = 0; v < nv; ++v) user[(int64_t)v * N + u] = state[k * nv + v];
 }
-// rows of `width` elements, internal row k <-> caller row perm[k]
-template <typename T>
-__global__ void k_rows_to_user(int64_t N, int width, const int32_t *perm, const T *src, T *dst) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const int64_t u = perm[k];
-    for (int e = 0; e < width; ++e) dst[u * width + e] = src[k * width + e];
-}
-template <typename T>
-__global__ void k_rows_from_user(int64_t N, int width, const int32_t *perm, const T *src, T *dst) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= N) return;
-    const int64_t u = perm[k];
-    for (int e = 0; e < width; ++e) dst[k * width + e] = src[u * width + e];
+// Rows of `width` units, internal row k <-> caller row perm[k] (TO_USER: to the
+// caller's).  Lanes run over the units of consecutive internal rows, so both
+// sides are touched in whole rows.  A lane per row touched 64 rows with each
+// load: face values of 49k cells at degree 5 in FP32 (144 B rows) 16.6 us, now
+// 5.5.
+template <typename T, bool TO_USER>
+__global__ __launch_bounds__(256) void k_copy_rows(int64_t N, unsigned width, const int32_t *perm, const T *src, T *dst) {
+    const int64_t k0 = (int64_t)blockIdx.x * 64;
+    const unsigned n = (unsigned)min((int64_t)64, N - k0) * width;
+    for (unsigned t = threadIdx.x; t < n; t += 256) {
+        const unsigned r = t / width;
+        const int64_t k = (k0 + r) * width + (t - r * width), u = (int64_t)perm[k0 + r] * width + (t - r * width);
+        if (TO_USER) dst[u] = src[k];
+        else dst[k] = src[u];
+    }
 }
 
 static unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -321,33 +322,36 @@ hipError_t launch_state_to_user(const DeviceMesh &m, const double *state, double
     hipLaunchKernelGGL(k_state_to_user, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, m.nv, m.perm, state, user);
     return hipGetLastError();
 }
-hipError_t launch_fv_to_user(const DeviceMesh &m, bool fp32, const void *fv, void *user, hipStream_t st) {
-    const int w = 3 * m.tab.Nq * m.nv;
-    if (fp32) hipLaunchKernelGGL(k_rows_to_user<float>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const float *)fv, (float *)user);
-    else hipLaunchKernelGGL(k_rows_to_user<double>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const double *)fv, (double *)user);
+// rows of `bytes` bytes in the widest unit that divides them and that both
+// pointers are aligned to (the caller's may be a view of a larger array)
+template <bool TO_USER>
+static hipError_t copy_rows(const DeviceMesh &m, size_t bytes, const void *src, void *dst, hipStream_t st) {
+    const dim3 grid((unsigned)((m.N + 63) / 64)), block(256);
+    const size_t a = bytes | (size_t)(uintptr_t)src | (size_t)(uintptr_t)dst;
+#define CR_LAUNCH(T)                                                                                              \
+    hipLaunchKernelGGL((k_copy_rows<T, TO_USER>), grid, block, 0, st, m.N, (unsigned)(bytes / sizeof(T)), m.perm, \
+                       (const T *)src, (T *)dst)
+    if (a % 16 == 0) CR_LAUNCH(uint4);
+    else if (a % 8 == 0) CR_LAUNCH(uint2);
+    else if (a % 4 == 0) CR_LAUNCH(uint32_t);
+    else CR_LAUNCH(uint8_t);
+#undef CR_LAUNCH
     return hipGetLastError();
+}
+hipError_t launch_fv_to_user(const DeviceMesh &m, bool fp32, const void *fv, void *user, hipStream_t st) {
+    return copy_rows<true>(m, (size_t)3 * m.tab.Nq * m.nv * (fp32 ? 4 : 8), fv, user, st);
 }
 hipError_t launch_fv_from_user(const DeviceMesh &m, bool fp32, const void *user, void *fv, hipStream_t st) {
-    const int w = 3 * m.tab.Nq * m.nv;
-    if (fp32) hipLaunchKernelGGL(k_rows_from_user<float>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const float *)user, (float *)fv);
-    else hipLaunchKernelGGL(k_rows_from_user<double>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const double *)user, (double *)fv);
-    return hipGetLastError();
+    return copy_rows<false>(m, (size_t)3 * m.tab.Nq * m.nv * (fp32 ? 4 : 8), user, fv, st);
 }
 hipError_t launch_flux_to_user(const DeviceMesh &m, bool fp32, const void *fo, void *user, hipStream_t st) {
-    const int w = 3 * m.nv;
-    if (fp32) hipLaunchKernelGGL(k_rows_to_user<float>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const float *)fo, (float *)user);
-    else hipLaunchKernelGGL(k_rows_to_user<double>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, w, m.perm, (const double *)fo, (double *)user);
-    return hipGetLastError();
+    return copy_rows<true>(m, (size_t)3 * m.nv * (fp32 ? 4 : 8), fo, user, st);
 }
 hipError_t launch_delta_to_user(const DeviceMesh &m, const uint8_t *d, uint8_t *user, hipStream_t st) {
-    hipLaunchKernelGGL(k_rows_to_user<uint8_t>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, m.delta_bytes(), m.perm, d,
-                       user);
-    return hipGetLastError();
+    return copy_rows<true>(m, (size_t)m.delta_bytes(), d, user, st);
 }
 hipError_t launch_delta_from_user(const DeviceMesh &m, const uint8_t *user, uint8_t *d, hipStream_t st) {
-    hipLaunchKernelGGL(k_rows_from_user<uint8_t>, dim3(grid_for(m.N)), dim3(256), 0, st, m.N, m.delta_bytes(), m.perm,
-                       user, d);
-    return hipGetLastError();
+    return copy_rows<false>(m, (size_t)m.delta_bytes(), user, d, st);
 }
 
 __global__ void k_count_diff(int64_t n, const uint8_t *a, const uint8_t *b, unsigned long long *count) {

@@ -12,6 +12,7 @@ import math
 
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 from paper_2312_17042_amd import cteno as T
@@ -132,5 +133,34 @@ def test_high_order_products(ctx, degree, nx, ny, scatter):
             got = s.reconstruct(prec, forced=forced)[0].cpu().numpy()
             bound = 2 * (P.shape[1] + P.shape[2] + 6) * eps * mag + 2 * eps * np.abs(want)
             assert (np.abs(got - want) <= bound)[on].all(), (prec, bit)
+    s.close()
+    m.close()
+
+
+@pytest.mark.parametrize("nx,ny", [(8, 16), (13, 5)])
+@pytest.mark.parametrize("problem", ["vortex", "advection"])
+@pytest.mark.parametrize("prec", [T.FP64, T.MIXED])
+def test_face_values_at_any_alignment(ctx, problem, nx, ny, prec):
+    """A caller's face values that start at any element of an array give the
+    fluxes of the same values in an array of their own."""
+    mesh = W.split_jitter_mesh(nx, ny, (0.0, 10.0, 0.0, 10.0), seed=31)
+    if problem == "vortex":
+        u0 = W.cell_average(mesh, W.isentropic_vortex(0.0, 3.0, (5.0, 5.0), (10.0, 10.0)), n=4)
+        kw = dict(physics=O.EULER, scheme=O.CTENOZ, degree=3, lambda1_prime=1e4)
+    else:
+        u0 = W.cell_average(mesh, W.advection_sine(0.0), n=4)
+        kw = dict(physics=O.ADVECTION, scheme=O.CTENO, degree=3, lambda1_prime=1e15, ax=1.0, ay=1.0)
+    m = T.Mesh.from_workload(ctx, mesh, precision=prec, **kw)
+    s = T.Solution(m, u0)
+    values, selected = s.reconstruct(prec)
+    assert torch.equal(s.reconstruct(prec, forced=selected.cpu().numpy())[0], values)
+    want = T.flux(m, values, prec)
+    for off in (1, 2, 3):
+        buf = torch.zeros(values.numel() + off, dtype=values.dtype, device=values.device)
+        view = buf[off:].view(values.shape)
+        view.copy_(values)
+        assert torch.equal(T.flux(m, view, prec), want)
+        out = torch.zeros(want.numel() + off, dtype=want.dtype, device=want.device)
+        assert torch.equal(T.flux(m, values, prec, out=out[off:].view(want.shape)), want)
     s.close()
     m.close()
