@@ -32,17 +32,6 @@ __device__ __forceinline__ void packed_face(const double *rec, int64_t k, double
     code = (uint32_t)__double_as_longlong(r1.y);
 }
 
-// the state of the quad's cell in every lane
-template <int NV>
-__device__ __forceinline__ void quad_state(double un, double (&u)[NV]) {
-    u[0] = quad_bcast<0>(un);
-    if constexpr (NV == 4) {
-        u[1] = quad_bcast<1>(un);
-        u[2] = quad_bcast<2>(un);
-        u[3] = quad_bcast<3>(un);
-    }
-}
-
 // Gauss point g of a listed face of the block that starts at cell i0: its
 // lane pair leaves the face's terms for both of its cells in lterm, the first
 // lane the owner's, the second the other cell's, its exact negation.  True for a

@@ -105,10 +105,10 @@ struct DeviceMesh {
     // fused stage's second kernel's (which fold in the first kernel's, stored
     // behind them), or the only kernel's
     int64_t dt_parts(bool fused_run, bool f32) const {
-        return !fused_run ? blocks() : lists[f32].n_cross ? lists[f32].cross_blocks() : stage_blocks(f32);
+        return !fused_run ? groups() : lists[f32].n_cross ? lists[f32].cross_blocks() : stage_blocks(f32);
     }
     int64_t dt_storage() const {
-        return std::max({blocks(), stage_blocks(false) + lists[0].cross_blocks(),
+        return std::max({groups(), stage_blocks(false) + lists[0].cross_blocks(),
                          stage_blocks(true) + lists[1].cross_blocks()});
     }
     // selection bytes per cell: per variable, or per face and characteristic field
@@ -202,7 +202,7 @@ struct BatchSlot {
     const double *area;
     double *U[3];                   // U^n, U^(1), U^(2)
     float *FV;
-    double *dt_part;                // [nblocks]
+    double *dt_part;                // [4 nblocks]
     Ctrl *ctrl;
 };
 // one SSP-RK3 step (control + 3 x (reconstruction, flux/RK)) of every slot in

@@ -309,8 +309,9 @@ struct HoDims {
 // HLLC with Roe-averaged signal speeds (sec. 2.7), in the face-normal frame
 // (u normal, w tangential velocity); F returned in the global frame.  The sum
 // H_l + H_r D of the Roe average is contracted by hand: ALT 0 leaves H_l
-// unrounded in it, 1 H_r D, 2 decides by `alt` (FP32 marches repeat their
-// results bit for bit only if each face keeps its own).
+// unrounded in it, 1 H_r D, 2 decides by `alt`; 3 is 0 with the other product of
+// u_r unrounded (FP32 marches repeat their results bit for bit only if each face
+// keeps its own).
 template <typename real, int ALT = -1>
 __device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, real nx, real ny, real *F,
                                      bool alt = false) {
@@ -318,7 +319,10 @@ __device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, rea
     const real rl = UL[0], rr = UR[0];
     const real irl = frcp(rl), irr = frcp(rr);
     const real ul = (UL[1] * nx + UL[2] * ny) * irl, wl = (-UL[1] * ny + UL[2] * nx) * irl;
-    const real ur = (UR[1] * nx + UR[2] * ny) * irr, wr = (-UR[1] * ny + UR[2] * nx) * irr;
+    real mr;
+    if constexpr (ALT == 3) mr = __builtin_fmaf(UR[2], ny, UR[1] * nx);
+    else mr = UR[1] * nx + UR[2] * ny;
+    const real ur = mr * irr, wr = (-UR[1] * ny + UR[2] * nx) * irr;
     const real El = UL[3], Er = UR[3];
     const real h = (real)0.5;
     const real pl = euler_pressure(g, rl, UL[1], UL[2], El);
@@ -604,7 +608,7 @@ __device__ __forceinline__ void face_term(const FluxArgs<real> a, const real (&o
         }
         if (PHYS == CTENO_EULER) {
             if (wallf) bad |= !wall_flux<real>(a.gamma, A, fx, fy, F);
-            else bad |= !hllc<real>(a.gamma, A, B, fx, fy, F);
+            else bad |= !hllc<real, std::is_same<real, float>::value ? 3 : -1>(a.gamma, A, B, fx, fy, F);
         } else {
             const real an = a.ax * fx + a.ay * fy;
             F[0] = an * (an >= 0 ? A[0] : B[0]);
@@ -619,23 +623,6 @@ __device__ __forceinline__ void face_term(const FluxArgs<real> a, const real (&o
     }
 }
 
-// U^n, the stage input and the area of cell i (the RK stage's operands)
-template <typename real, int NV>
-__device__ __forceinline__ void rk_load(const FluxPtrs<real> ptr, int64_t i, double (&u0)[NV], double (&us)[NV],
-                                        double &ar) {
-    ar = ptr.area[i];
-    if constexpr (NV == 4) {
-        const double2 *U2 = reinterpret_cast<const double2 *>(ptr.Un);
-        const double2 *S2 = reinterpret_cast<const double2 *>(ptr.Us);
-        const double2 x0 = U2[2 * i], x1 = U2[2 * i + 1], y0 = S2[2 * i], y1 = S2[2 * i + 1];
-        u0[0] = x0.x; u0[1] = x0.y; u0[2] = x1.x; u0[3] = x1.y;
-        us[0] = y0.x; us[1] = y0.y; us[2] = y1.x; us[3] = y1.y;
-    } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) { u0[v] = ptr.Un[i * NV + v]; us[v] = ptr.Us[i * NV + v]; }
-    }
-}
-
 // SSP-RK3 stage value from U^n, the stage input and dt times the residual
 __device__ __forceinline__ double rk_value(int stage, double u0, double us, double dtR) {
     if (stage == 0) return us + dtR;
@@ -644,86 +631,5 @@ __device__ __forceinline__ double rk_value(int stage, double u0, double us, doub
 }
 // the weight of dt times the residual in rk_value
 __device__ __forceinline__ double rk_weight(int stage) { return stage == 0 ? 1.0 : stage == 1 ? 0.25 : 2.0 / 3.0; }
-
-// writes the new state un of cell i; returns its CFL bound when requested, else +inf
-template <typename real, int NV, int PHYS>
-__device__ __forceinline__ double rk_store(const FluxArgs<real> a, const FluxPtrs<real> ptr, int64_t i,
-                                           const double (&un)[NV], const double (&nrm)[3][3], double ar) {
-    if constexpr (NV == 4) {
-        double2 *O2 = reinterpret_cast<double2 *>(ptr.Uout);
-        O2[2 * i] = make_double2(un[0], un[1]);
-        O2[2 * i + 1] = make_double2(un[2], un[3]);
-    } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ptr.Uout[i * NV + v] = un[v];
-    }
-    return ptr.want_dt ? cell_dt_bound<NV, PHYS>(un, nrm, ar, a.gamma64, (double)a.ax, (double)a.ay) : INFINITY;
-}
-
-// SSP-RK3 stage of cell i from the sum acc of its outward face fluxes (the
-// residual is -acc / |V_i|) and its loaded operands: writes the new state;
-// returns its CFL bound when requested, else +inf
-template <typename real, int NV, int PHYS>
-__device__ __forceinline__ double rk_apply(const FluxArgs<real> a, const FluxPtrs<real> ptr, int64_t i,
-                                           const double (&acc)[NV], const double (&nrm)[3][3],
-                                           const double (&u0)[NV], const double (&us)[NV], double ar) {
-    const double dt = ptr.dt_ptr ? *ptr.dt_ptr : a.dt_value;
-    double un[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) un[v] = rk_value(a.stage, u0[v], us[v], dt * (-acc[v] / ar));
-    return rk_store<real, NV, PHYS>(a, ptr, i, un, nrm, ar);
-}
-
-template <typename real, int NV, int PHYS>
-__device__ __forceinline__ double rk_update(const FluxArgs<real> a, const FluxPtrs<real> ptr, int64_t i,
-                                            const double (&acc)[NV], const double (&nrm)[3][3]) {
-    double u0[NV], us[NV], ar;
-    rk_load<real, NV>(ptr, i, u0, us, ar);
-    return rk_apply<real, NV, PHYS>(a, ptr, i, acc, nrm, u0, us, ar);
-}
-
-// one cell's three faces, residual and (MODE 2) RK stage; returns the cell's
-// CFL bound of the new state when requested, else +inf
-template <typename real, int NV, int PHYS, int MODE, int NQ>
-__device__ __forceinline__ double flux_body(const FluxArgs<real> a, const FluxPtrs<real> ptr, int64_t i) {
-    double acc[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    double nrm[3][3];
-    bool bad = false;
-    real own[3][NQ][NV];
-    load_row<real, 3 * NQ * NV>(ptr.FV + i * 3 * NQ * NV, &own[0][0][0]);
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-        real nx, ny, len;
-        uint32_t code;
-        face_record<real>(ptr.fr, i, f, nx, ny, len, code);
-        nrm[f][0] = (double)nx; nrm[f][1] = (double)ny; nrm[f][2] = (double)len;
-        real oth[NQ][NV];
-        bool owner = true, wallf = false;
-        if (code & kNbBoundary) {
-            wallf = boundary_state<real, NV, PHYS, MODE, NQ>(a, ptr.dt_ptr, code, own[f], oth);
-        } else {
-            owner = (code & kNbOwner) != 0;
-            const int64_t j = code & kNbIndexMask;
-            const int g = (code >> 28) & 3;
-            load_row<real, NQ * NV>(ptr.FV + (j * 3 + g) * NQ * NV, &oth[0][0]);
-        }
-        double term[NV];
-        face_term<real, NV, PHYS, NQ>(a, own[f], oth, owner, wallf, nx, ny, len, term, bad);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            acc[v] += term[v];
-            if (MODE == 0) ptr.flux_out[(i * 3 + f) * NV + v] = (real)term[v];
-        }
-    }
-    if (bad && ptr.nonphys) atomicOr(ptr.nonphys, 1);
-    if (MODE == 1) {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) ptr.resid[i * NV + v] = -acc[v] / ptr.area[i];
-    }
-    if (MODE == 2) return rk_update<real, NV, PHYS>(a, ptr, i, acc, nrm);
-    return INFINITY;
-}
 
 }  // namespace cteno

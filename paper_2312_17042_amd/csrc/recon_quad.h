@@ -65,6 +65,17 @@ __device__ __forceinline__ real quad_take(const real (&x)[4], int v) {
 template <int owner, typename real>
 __device__ __forceinline__ real quad_take(const real (&x)[1], int) { return quad_bcast<owner>(x[0]); }
 
+// the state of the quad's cell in every lane
+template <int NV>
+__device__ __forceinline__ void quad_state(double un, double (&u)[NV]) {
+    u[0] = quad_bcast<0>(un);
+    if constexpr (NV == 4) {
+        u[1] = quad_bcast<1>(un);
+        u[2] = quad_bcast<2>(un);
+        u[3] = quad_bcast<3>(un);
+    }
+}
+
 // Transposes x[s] over the register index s and the lane's row of sixteen
 // lanes i: afterwards x[i] holds, in row s, what x[s] held in row i.
 __device__ __forceinline__ void rows_to_lanes(double (&x)[4]) {

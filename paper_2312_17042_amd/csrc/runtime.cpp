@@ -1179,7 +1179,7 @@ void slot_footprint(const cteno_server *sv, int64_t N, int64_t &steady, int64_t 
     const int64_t Np = pad64(N);
     const int64_t E = pinv_entries(r, 4);
     const int S = dims_S(r), SP = round_up(S, 4);
-    steady = Np * (E * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 8;
+    steady = Np * (E * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 32;
     transient = Np * (E * 8 + 6 * 8 + S + 2 * S) + 64;
 }
 
@@ -1203,7 +1203,7 @@ cteno_status prepare_slot(cteno_server *sv, const std::shared_ptr<ServerRequest>
         HIP_TRY(hipMemsetAsync(u.p, 0, sb, st));
     }
     sl->FV = DevBuf(sv->ctx, (size_t)dm.Np * 3 * kNq * dm.nv * sizeof(float));
-    sl->dt_part = DevBuf(sv->ctx, (size_t)dm.blocks() * sizeof(double));
+    sl->dt_part = DevBuf(sv->ctx, (size_t)(4 * dm.blocks()) * sizeof(double));
     if (!sl->FV.p || !sl->dt_part.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     bytes += (int64_t)(3 * sb + sl->FV.bytes + sl->dt_part.bytes);
     // initial state: caller order -> internal order
@@ -1211,7 +1211,7 @@ cteno_status prepare_slot(cteno_server *sv, const std::shared_ptr<ServerRequest>
     if (!tmp.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     HIP_TRY(hipMemcpyAsync(tmp.p, rq->u0.data(), (size_t)dm.N * dm.nv * sizeof(double), hipMemcpyHostToDevice, st));
     HIP_TRY(launch_user_to_state(dm, tmp.as<double>(), sl->U[0].as<double>(), st));
-    HIP_TRY(launch_dt_partials(dm, true, sl->U[0].as<double>(), sl->dt_part.as<double>(), dm.blocks(), st));
+    HIP_TRY(launch_dt_partials(dm, true, sl->U[0].as<double>(), sl->dt_part.as<double>(), 4 * dm.blocks(), st));
     HIP_TRY(hipStreamSynchronize(st));     // tmp and the host u0 are released after this
     rq->u0.clear();
     rq->u0.shrink_to_fit();
