@@ -164,3 +164,22 @@ def test_face_values_at_any_alignment(ctx, problem, nx, ny, prec):
         assert torch.equal(T.flux(m, values, prec, out=out[off:].view(want.shape)), want)
     s.close()
     m.close()
+
+
+@pytest.mark.parametrize("nx", [361, 363, 724, 725])
+@pytest.mark.parametrize("pinned", [False, True])
+def test_large_state_transfers(ctx, nx, pinned):
+    """States on both sides of the sizes from which transfers are staged, with
+    ragged last chunks, come back bit for bit."""
+    mesh = W.split_jitter_mesh(nx, nx, (0.0, 1.0, 0.0, 1.0), seed=31)
+    rng = np.random.default_rng(3)
+    u = [rng.standard_normal((4, mesh.n_cells)) for _ in range(2)]
+    m = T.Mesh.from_workload(ctx, mesh, precision=T.FP64, physics=O.EULER, scheme=O.CTENO, degree=2,
+                             lambda1_prime=1e15)
+    s = T.Solution(m, u[0])
+    assert np.array_equal(s.download()[0], u[0])
+    s.set(torch.from_numpy(u[1]).pin_memory().numpy() if pinned else u[1], 0.5)
+    got, t = s.download()
+    assert t == 0.5 and np.array_equal(got, u[1])
+    s.close()
+    m.close()
