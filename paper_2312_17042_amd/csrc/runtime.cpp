@@ -730,10 +730,18 @@ struct cteno_sol {
     DevBuf xterm;             // FP32 fused stage: terms of the cross cells' faces inside their groups
     double t = 0.0;
     Ctrl *h_ctrl = nullptr;   // pinned host mirror
-    hipGraphExec_t graph[2] = {nullptr, nullptr};
-    bool graph_fused[2] = {false, false};   // stage kernels a captured graph holds
+    // captured steps, FP64 / FP32: one step, and kGraphSteps of them
+    hipGraphExec_t graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
+    bool graph_fused[2] = {false, false};   // stage kernels that the captured graphs hold
+    void drop_graphs(int p) {
+        for (auto &g : graph[p]) {
+            if (g) (void)hipGraphExecDestroy(g);
+            g = nullptr;
+        }
+    }
     ~cteno_sol() {
-        for (auto &g : graph) if (g) (void)hipGraphExecDestroy(g);
+        drop_graphs(0);
+        drop_graphs(1);
         if (h_ctrl) (void)hipHostFree(h_ctrl);
     }
     void *fv(bool f32) {
@@ -1080,6 +1088,12 @@ hipError_t issue_step(cteno_ctx *ctx, cteno_sol *s, bool f32, hipStream_t st) {
 }
 }  // namespace
 
+// Steps of a march in one captured graph.  The device idles some 5 us between two
+// graphs, 1 us between two of a graph's kernels: 100 steps on 800 cells take 3.75
+// ms in graphs of one step, 3.22 of four, 3.10 of 16, but the longer the graph the
+// longer its capture (a new solution's first march 3.75, 3.26, 3.32).
+constexpr int64_t kGraphSteps = 4;
+
 extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_sol *s, int32_t precision,
                                     double t_final, int64_t max_steps, double cfl, int32_t use_graph,
                                     int64_t *steps_done) {
@@ -1115,31 +1129,41 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
         HIP_TRY(hipEventRecord(ev, st));
         HIP_TRY(hipStreamWaitEvent(gs, ev, 0));
     }
-    hipGraphExec_t &gx = s->graph[f32 ? 1 : 0];
-    if (gx && s->graph_fused[f32 ? 1 : 0] != use_fused(ctx, dm, f32)) {   // captured with the other stage kernels
-        (void)hipGraphExecDestroy(gx);
-        gx = nullptr;
-    }
-    if (graph && !gx) {
-        s->graph_fused[f32 ? 1 : 0] = use_fused(ctx, dm, f32);
-        hipGraph_t g = nullptr;
-        HIP_TRY(hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal));
-        hipError_t e = issue_step(ctx, s, f32, gs);
-        hipError_t e2 = hipStreamEndCapture(gs, &g);
-        if (e != hipSuccess) return fail(CTENO_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e));
-        HIP_TRY(e2);
-        HIP_TRY(hipGraphInstantiate(&gx, g, nullptr, nullptr, 0));
-        (void)hipGraphDestroy(g);
-    }
+    const int gp = f32 ? 1 : 0;
+    const bool fused = use_fused(ctx, dm, f32);
+    if (s->graph_fused[gp] != fused) s->drop_graphs(gp);      // captured with the other stage kernels
+    s->graph_fused[gp] = fused;
+    // issues n steps as one graph
+    const auto launch_steps = [&](int64_t n) -> cteno_status {
+        hipGraphExec_t &gx = s->graph[gp][n > 1];
+        if (!gx) {
+            hipGraph_t g = nullptr;
+            HIP_TRY(hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal));
+            hipError_t e = hipSuccess;
+            for (int64_t k = 0; k < n && e == hipSuccess; ++k) e = issue_step(ctx, s, f32, gs);
+            hipError_t e2 = hipStreamEndCapture(gs, &g);
+            if (e != hipSuccess) return fail(CTENO_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e));
+            HIP_TRY(e2);
+            HIP_TRY(hipGraphInstantiate(&gx, g, nullptr, nullptr, 0));
+            (void)hipGraphDestroy(g);
+        }
+        HIP_TRY(hipGraphLaunch(gx, gs));
+        return CTENO_OK;
+    };
     // steps are issued in chunks between host checks of the done flag; a
     // step issued after the march has reached t_final exits at once on the
     // device.  No more steps than the budget are issued.
     int64_t issued = 0;
     while (issued < max_steps) {
         const int64_t chunk = std::min<int64_t>(16, max_steps - issued);
-        for (int64_t k = 0; k < chunk; ++k) {
-            if (graph) HIP_TRY(hipGraphLaunch(gx, gs));
-            else HIP_TRY(issue_step(ctx, s, f32, gs));
+        for (int64_t k = 0; k < chunk;) {
+            const int64_t n = graph && chunk - k >= kGraphSteps ? kGraphSteps : 1;
+            if (graph) {
+                if (cteno_status rc = launch_steps(n)) return rc;
+            } else {
+                HIP_TRY(issue_step(ctx, s, f32, gs));
+            }
+            k += n;
         }
         issued += chunk;
         HIP_TRY(hipMemcpyAsync(&h, dc, sizeof(Ctrl), hipMemcpyDeviceToHost, gs));
