@@ -42,7 +42,7 @@ RECON_BYTES = {"mixed": 162 * 4 + 24 * 4 + 18 * 4 + 12 + 32, "fp64": 162 * 8 + 2
 # the flux / residual / RK kernel's share: U^n, state write, area, geometry
 FLUX_BYTES = {k: STAGE_BYTES[k] - RECON_BYTES[k] for k in STAGE_BYTES}
 # a cross cell's share of the second fused-stage kernel: its state write
-# (k_stage reads its U^n, stage input and area and stores its partial state)
+# (k_stage reads its U^n, stage input and area)
 CROSS_UPDATE_BYTES = 32
 
 # HBM bytes per cell and launch measured with the FETCH_SIZE / WRITE_SIZE
@@ -56,9 +56,9 @@ MEASURED_TRAFFIC = {"kernels_sha256_prefix": "002632cd235042d6",
                                        "k_reconstruct_f64": 1811.3, "k_flux_f64": 554.5}}
 
 
-KERNEL_SOURCES = ("kernels_common.h", "k_recon.inl", "k_recon_ho.inl", "k_stage.inl", "k_recon_f32.hip",
-                  "k_recon_f64.hip", "k_recon_ho_f32.hip", "k_recon_ho_f64.hip", "k_stage_f32.hip",
-                  "k_stage_f64.hip", "k_precompute.hip", "k_flux.hip")
+KERNEL_SOURCES = ("kernels_common.h", "recon_quad.h", "k_recon.inl", "k_recon_ho.inl", "k_stage.inl",
+                  "k_recon_f32.hip", "k_recon_f64.hip", "k_recon_ho_f32.hip", "k_recon_ho_f64.hip",
+                  "k_stage_f32.hip", "k_stage_f64.hip", "k_precompute.hip", "k_flux.hip")
 
 
 def kernels_hash():

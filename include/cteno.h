@@ -158,8 +158,7 @@ typedef struct {
     int32_t n_inadmissible;     /* interior faces whose directional stencil has < K_d + 1 cells */
     int32_t Kd, Md;             /* directional basis size and stencil size (M_d = 2 K_d) */
     int64_t device_bytes;       /* resident device memory of the mesh handle */
-    int64_t n_cross_cells;      /* cells with a face to another 256-cell block (the fused
-                                   stage's second kernel finishes them); 0 above degree 3 */
+    int64_t n_cross_cells;      /* cells with a face to another block of 256 cells; 0 above degree 3 */
 } cteno_mesh_info;
 
 /* ---------------------------------------------------------------------- */
@@ -179,11 +178,11 @@ cteno_status cteno_ctx_synchronize(cteno_ctx *ctx);
 const char *cteno_last_error(void);
 /* Stage kernels of degree 2 and 3, in either precision, for RK stages and
    marches (cteno_rk_stage, cteno_solve): on = 1 (default), one fused
-   kernel per stage reconstructs each block of 256 cells into on-chip
-   memory and evaluates the fluxes of the faces inside the block there, and
-   a second kernel finishes the cells with faces to other blocks; on = 0, a
-   reconstruction kernel writes all face values to device memory and a flux
-   kernel reads them back.  A stage's results agree to FP64 rounding (the
+   kernel per stage reconstructs each block of cells (64, or 256 on large
+   MIXED meshes) into on-chip memory and evaluates the fluxes of the faces
+   inside the block there, and a second kernel finishes the cells with
+   faces to other blocks; on = 0, a reconstruction kernel writes all face
+   values to device memory and a flux kernel reads them back.  A stage's results agree to FP64 rounding (the
    fused path sums a cell's faces inside its block first).  Synchronises. */
 cteno_status cteno_ctx_set_fused_stage(cteno_ctx *ctx, int32_t on);
 /* Per-kernel timing with HIP events on the context stream (off by default).
