@@ -174,8 +174,8 @@ void k_stage(const ReconArgs<real> ra, const ReconPtrs<real> rp, const FluxArgs<
 // GB, 5 TB/s: a wave waits a third of its time for memory and a third for the
 // matrix and vector units' results.  Three waves per SIMD; at four the stream
 // spills (1728 us).
-template <int R, int NV, int SCHEME, int GFORM, int VARS, int PHYS>
-__global__ __launch_bounds__(256, (VARS ? 2 : 3))
+template <int R, int NV, int SCHEME, int GFORM, int PHYS>
+__global__ __launch_bounds__(256, 3)
 void k_stage_wide(const ReconArgs<float> ra, const ReconPtrs<float> rp, const FluxArgs<float> fa, int row_doubles) {
     using real = float;
     constexpr int NQ = 2, ROW = 3 * NQ * NV, K = QuadDims<R>::K;
@@ -223,7 +223,7 @@ void k_stage_wide(const ReconArgs<float> ra, const ReconPtrs<float> rp, const Fl
     auto finish = [&](int p) {
         const int64_t i = (g0 + p) * 64 + cl;
         real out[3][NQ];
-        recon_finish<real, R, NV, SCHEME, GFORM, 0, VARS>(ra, rp, i, q, i < fa.N, U0, fl, ao, ad, out);
+        recon_finish<real, R, NV, SCHEME, GFORM, 0, 0>(ra, rp, i, q, i < fa.N, U0, fl, ao, ad, out);
         const int xmask = i < fa.N ? xid >> 28 : 0, c = p * 64 + cl;
         if (q < NV) {
 #pragma unroll
@@ -459,9 +459,9 @@ static void stage_launch(const DeviceMesh &m, const ReconArgs<real> &ra, const R
     const unsigned grid = (unsigned)m.stage_blocks(F32);
 #define ST_LAUNCH(SCH, GF)                                                                                        \
     do {                                                                                                          \
-        if constexpr (F32)                                                                                        \
+        if constexpr (F32 && !VARS)                                                                               \
             if (m.lists[1].bc == 256) {                                                                           \
-                hipLaunchKernelGGL((k_stage_wide<R, NV, SCH, GF, VARS, PHYS>), dim3(grid), dim3(256),             \
+                hipLaunchKernelGGL((k_stage_wide<R, NV, SCH, GF, PHYS>), dim3(grid), dim3(256),                   \
                                    std::max(2 * m.row_bytes(), 256 * 3 * NV * sizeof(float)), st, ra, rp, fa,     \
                                    (int)(m.row_bytes() / 8));                                                     \
                 break;                                                                                            \

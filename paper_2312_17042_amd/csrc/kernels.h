@@ -57,7 +57,8 @@ struct StageLists {
 // cells, degree 3: 96 / 102 us at 500k cells, 186 / 189 at 1M, 288 / 283 at
 // 1.4M, 402 / 392 at 2M, 1728 / 1545 at 8M.  Only where two groups' averages leave
 // room for three blocks per CU (the usual lists take 13 KB; scattered numberings up
-// to 90).
+// to 90), and not for characteristic variables, whose selection per face leaves
+// room for two waves per SIMD only (448 / 545 us at 1.6M).
 constexpr int64_t kWideCells = 1200000;
 constexpr size_t kWideRowBytes = 28 * 1024;
 

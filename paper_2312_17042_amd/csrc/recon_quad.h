@@ -106,6 +106,13 @@ __device__ __forceinline__ void rows_to_lanes(double (&x)[4]) {
         x[s] = __builtin_bit_cast(double, ((unsigned long long)h[1][s] << 32) | (unsigned long long)h[0][s]);
 }
 
+// a + b with both rounded: not contracted with the product that one of them is
+template <typename real>
+__device__ __forceinline__ real rounded_sum(real a, real b) {
+#pragma clang fp contract(off)
+    return a + b;
+}
+
 // constants of one reconstruction
 template <typename real>
 struct ReconArgs {
@@ -524,7 +531,7 @@ __device__ __forceinline__ void recon_finish(const ReconArgs<real> a, const Reco
         const real rho = (real)Ud[0], uu = (real)(Ud[1] / Ud[0]), vv = (real)(Ud[2] / Ud[0]);
         const real q2 = (real)0.5 * (uu * uu + vv * vv);
         const real pr = (a.gamma - 1) * ((real)Ud[3] - rho * q2);
-        const real cs = fsqrt(fdiv(a.gamma * pr, rho)), H = fdiv((real)Ud[3] + pr, rho);
+        const real cs = fsqrt(fdiv(a.gamma * pr, rho)), H = fdiv(rounded_sum((real)Ud[3], pr), rho);
         const real b1 = fdiv(a.gamma - 1, cs * cs), b2 = b1 * q2, ic = frcp(cs);
 #pragma unroll
         for (int f = 0; f < 3; ++f) {

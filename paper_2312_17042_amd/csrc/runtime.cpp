@@ -388,7 +388,8 @@ template <class Alloc>
 static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMesh &dm, bool f32, Alloc &&alloc_raw,
                                        bool &fits) {
     StageLists &l = dm.lists[f32];
-    l.bc = f32 && dm.N >= kWideCells && 2 * dm.row_bytes() <= kWideRowBytes ? 256 : 64;
+    l.bc = f32 && dm.vars != CTENO_VARS_CHARACTERISTIC && dm.N >= kWideCells && 2 * dm.row_bytes() <= kWideRowBytes
+               ? 256 : 64;
     const int64_t ng = dm.groups(), nb = dm.stage_blocks(f32);
     DevBuf cnt(ctx, (size_t)(3 * ng + 1) * sizeof(int32_t));
     if (!cnt.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
