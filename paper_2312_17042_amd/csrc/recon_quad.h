@@ -147,8 +147,10 @@ struct ReconPtrs {
 
 // The lane's field (a conserved variable, or a characteristic field on one
 // face): selection or CWENO weights, and the final coefficients in place in
-// c1[K] (p_1 on entry); cd[3][2] the degree-1 directional coefficients.
-template <typename real, int K, int SCHEME, int GFORM, int DMODE>
+// c1[K] (p_1 on entry); cd[3][2] the degree-1 directional coefficients.  VARS
+// only decides which product of a directional indicator is rounded in FP32 (a
+// march repeats its results only if that stays).
+template <typename real, int K, int SCHEME, int GFORM, int DMODE, int VARS>
 __device__ __forceinline__ int finish_field(const ReconArgs<real> a, real (&c1)[K], const real (&cd)[3][2], int fl,
                                             int adm, int st, real lams, real lratio, int forced) {
     int bits;
@@ -175,7 +177,8 @@ __device__ __forceinline__ int finish_field(const ReconArgs<real> a, real (&c1)[
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const real x0 = cd[q][0], x1 = cd[q][1];
-            if constexpr (SYM) si[q + 1] = x0 * (g00 * x0 + g01 * x1) + g11 * (x1 * x1);
+            if constexpr (SYM && VARS) si[q + 1] = __builtin_fmaf(g11, x1 * x1, x0 * (g00 * x0 + g01 * x1));
+            else if constexpr (SYM) si[q + 1] = x0 * (g00 * x0 + g01 * x1) + g11 * (x1 * x1);
             else si[q + 1] = x0 * (g00 * x0 + g01 * x1) + x1 * (g10 * x0 + g11 * x1);
         }
         if constexpr (SCHEME == CTENO_SCHEME_CWENO) {
@@ -509,7 +512,7 @@ __device__ __forceinline__ void recon_finish(const ReconArgs<real> a, const Reco
     constexpr int NB = VARS ? 3 : 1;      // selection bytes of this lane
     int dbyte[NB];
     if constexpr (VARS == 0) {
-        dbyte[0] = finish_field<real, K, SCHEME, GFORM, DMODE>(a, ao, ad, fl, adm, st, lams, lratio,
+        dbyte[0] = finish_field<real, K, SCHEME, GFORM, DMODE, VARS>(a, ao, ad, fl, adm, st, lams, lratio,
                                                                DMODE == 2 ? ptr.delta[il * NV + v] : 0);
         // face Gauss-point values
 #pragma unroll
@@ -570,7 +573,7 @@ __device__ __forceinline__ void recon_finish(const ReconArgs<real> a, const Reco
             for (int s = 0; s < 3; ++s)
 #pragma unroll
                 for (int k = 0; k < 2; ++k) cd[s][k] = project(ad[s][k]);
-            dbyte[f] = finish_field<real, K, SCHEME, GFORM, DMODE>(
+            dbyte[f] = finish_field<real, K, SCHEME, GFORM, DMODE, VARS>(
                 a, c1, cd, fl, adm, st, lams, lratio, DMODE == 2 ? ptr.delta[(il * 3 + f) * NV + v] : 0);
 #pragma unroll
             for (int g = 0; g < 2; ++g) {
