@@ -1298,14 +1298,20 @@ struct cteno_server {
 
 namespace {
 
-// steady and transient device bytes of a slot with N cells
-void slot_footprint(const cteno_server *sv, int64_t N, int64_t &steady, int64_t &transient) {
+// Device bytes of a slot with N cells: what it holds at least while it runs
+// (its neighbour lists empty; the batched grid is sized by this), and a bound of
+// what its upload takes.  The bound counts the FP64 precompute's buffers and the
+// slot table beside the state and the face values, which are allocated when the
+// former are gone: that leaves 192 B a cell for the neighbour lists, at most 4 S
+// B, and the row numbers, 2 row_entries B (degree 3: 120 B, degree 2: 80 B).
+void slot_footprint(const cteno_server *sv, int64_t N, int64_t &least, int64_t &reserve) {
     const int r = sv->scheme.degree;
     const int64_t Np = pad64(N);
     const int64_t E = pinv_entries(r, 4);
     const int S = dims_S(r), SP = round_up(S, 4);
-    steady = Np * (E * 4 + SP * 4 + 1 + 12 * 4 + 8 + 3 * 32 + 3 * kNq * 4 * 4) + N * 4 + ((N + 255) / 256) * 32;
-    transient = Np * (E * 8 + 6 * 8 + S + 2 * S) + 64;
+    const int64_t mesh = Np * (E * 4 + 1 + 12 * 4 + 8) + N * 4, state = Np * (3 * 32 + 3 * kNq * 4 * 4);
+    least = mesh + Np * row_entries(r) * 2 + state;
+    reserve = mesh + Np * (SP * 4 + E * 8 + 6 * 8 + S + 2 * S) + state + ((N + 255) / 256) * 32 + 64;
 }
 
 // a request's device state on a builder's stream: mesh arrays and FP64
@@ -1370,9 +1376,9 @@ void builder_main(cteno_server *sv, int threads_each) {
         std::string err;
         cteno_status rc = build_host_mesh(rq->desc, sv->scheme, rq->hm, err);
         if (rc == CTENO_OK) {
-            int64_t steady = 0, transient = 0;
-            slot_footprint(sv, rq->hm.N, steady, transient);
-            if (steady + transient > sv->budget) { rc = CTENO_ERR_BUSY; err = "request exceeds the HBM budget"; }
+            int64_t least = 0, reserve = 0;
+            slot_footprint(sv, rq->hm.N, least, reserve);
+            if (reserve > sv->budget) { rc = CTENO_ERR_BUSY; err = "request exceeds the HBM budget"; }
         }
         std::lock_guard<std::mutex> lk(sv->mu);
         rq->t_built = Clock::now();
@@ -1384,10 +1390,9 @@ void builder_main(cteno_server *sv, int threads_each) {
 }
 
 // An upload thread takes built requests in the order they were built, waits
-// until the device budget holds the request's steady plus transient
-// footprint beside the resident solves, uploads it and runs its FP64
-// precompute on its own stream (overlapping the batched ticks), and hands the
-// resident solve to the scheduler.
+// until the device budget holds the request's upload beside the resident
+// solves, uploads it and runs its FP64 precompute on its own stream (overlapping
+// the batched ticks), and hands the resident solve to the scheduler.
 void uploader_main(cteno_server *sv, int index) {
     const bool dev_ok = hipSetDevice(sv->ctx->device) == hipSuccess;
     const hipStream_t st = sv->upload_streams[index];
@@ -1401,9 +1406,8 @@ void uploader_main(cteno_server *sv, int index) {
             rq = sv->built.front();
             sv->built.pop_front();
             if (!dev_ok) { fail_request(sv, *rq, CTENO_ERR_DEVICE, "hipSetDevice failed"); continue; }
-            int64_t steady = 0, transient = 0;
-            slot_footprint(sv, rq->hm.N, steady, transient);
-            reserve = steady + transient;
+            int64_t least = 0;
+            slot_footprint(sv, rq->hm.N, least, reserve);
             sv->cv_budget.wait(lk, [&] { return sv->stop || sv->bytes_used + reserve <= sv->budget; });
             if (sv->stop) return;
             sv->bytes_used += reserve;
@@ -1627,9 +1631,9 @@ extern "C" cteno_status cteno_server_create(cteno_ctx *ctx, const cteno_scheme *
     sv->max_slots = max_slots;
     // the batched grid covers the most cells the budget can hold, plus one
     // partial block per slot
-    int64_t steady, transient;
-    slot_footprint(sv.get(), 1 << 20, steady, transient);
-    const double per_cell = (double)steady / (1 << 20);
+    int64_t least, reserve;
+    slot_footprint(sv.get(), 1 << 20, least, reserve);
+    const double per_cell = (double)least / (1 << 20);
     sv->max_blocks = (int64_t)(sv->budget / per_cell) / 256 + max_slots + 1;
     HIP_TRY(hipStreamCreateWithFlags(&sv->stream, hipStreamNonBlocking));
     sv->d_table = DevBuf(ctx, sizeof(BatchSlot) * max_slots);

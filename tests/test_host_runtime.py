@@ -1,0 +1,107 @@
+"""The C entry points' host code on a stand-in for the HIP runtime
+(host/hip_standin.cpp: device memory in host memory, kernels that do nothing):
+what is allocated, captured, launched and copied, and in which order.  Each
+test runs in a process of its own, which loads the stand-in before the library."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+PRELUDE = """
+import ctypes as C, os, sys
+sys.path.insert(0, {root!r})
+standin = C.CDLL({so!r}, mode=C.RTLD_GLOBAL)
+standin.standin_count.restype = C.c_int64
+count = lambda what: standin.standin_count(what.encode())
+standin.standin_caller()
+import numpy as np
+from paper_2312_17042_amd import cteno as T, workloads as W
+L = T.lib()
+
+def ok(rc, want=T.OK):
+    assert rc == want, (rc, L.cteno_last_error())
+
+def context(stream=None):
+    h = C.c_void_p()
+    ok(L.cteno_ctx_create(0, C.c_void_p(stream), None, None, None, C.byref(h)))
+    return h
+
+def upload(ctx, m, scheme):
+    h, d = C.c_void_p(), T.mesh_desc(m.xy, m.tri, m.box, m.bc)
+    ok(L.cteno_mesh_upload(ctx, C.byref(d), C.byref(scheme), C.byref(h)))
+    return h
+
+def solution(ctx, mesh, u):
+    h = C.c_void_p()
+    ok(L.cteno_sol_create(ctx, mesh, T._np_ptr(u), 0.0, C.byref(h)))
+    return h
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    """Runs a script on the stand-in."""
+    so = str(tmp_path_factory.mktemp("standin") / "libhip_standin.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-isystem",
+                    os.path.join(ROCM, "include"), os.path.join(HERE, "host", "hip_standin.cpp"), "-o", so], check=True)
+
+    def run(script, *args, timeout=120):
+        code = PRELUDE.format(root=ROOT, so=so) + textwrap.dedent(script) + "\nprint('done', flush=True)\nos._exit(0)\n"
+        r = subprocess.run([sys.executable, "-c", code, *map(str, args)], capture_output=True, text=True,
+                           timeout=timeout)
+        assert r.returncode == 0 and r.stdout.endswith("done\n"), r.stdout + r.stderr
+
+    return run
+
+
+@pytest.mark.parametrize("degree,requests", [(2, 176), (3, 120)])
+def test_server_runs_every_solve_that_the_budget_admits(host, degree, requests):
+    """Solves of whole 256-cell blocks, as many as the device budget holds, all
+    run at once: the batched grid covers them."""
+    host("""
+    degree, n = map(int, sys.argv[1:])
+    m = W.split_jitter_mesh(128, 64, (0.0, 10.0, 0.0, 5.0), seed=5)
+    u = np.ascontiguousarray(np.tile([[1.0], [0.5], [0.0], [3.0]], (1, m.n_cells)))
+    scheme = T.make_scheme(degree=degree, precision=T.MIXED)
+    ctx = context()
+    import time
+    def server(budget, slots):
+        h = C.c_void_p()
+        ok(L.cteno_server_create(ctx, C.byref(scheme), budget, slots, C.byref(h)))
+        return h
+    def submit(sv):
+        d, t = T.mesh_desc(m.xy, m.tri, m.box, m.bc), C.c_uint64()
+        ok(L.cteno_server_submit(sv, C.byref(d), T._np_ptr(u), 1 << 30, 0.3, C.byref(t)))
+        return t.value
+    def stats(sv):
+        s = T.ServerStats()
+        ok(L.cteno_server_get_stats(sv, C.byref(s)))
+        return s
+    def wait(sv, tickets, what):
+        info = T.RequestInfo()
+        for _ in range(6000):
+            s = stats(sv)
+            for t in tickets:
+                ok(L.cteno_server_request_info(sv, t, C.byref(info)))
+                if info.state == T.REQ_FAILED:
+                    ok(L.cteno_server_poll(sv, t, None, None, None, None))
+            if what(s):
+                return s
+            time.sleep(0.01)
+        raise SystemExit(f"{s.active} of {len(tickets)} solves run")
+    one = server(1 << 30, 1)
+    s = wait(one, [submit(one)], lambda s: s.active == 1)
+    resident, reserve = s.bytes_in_use, s.peak_bytes
+    assert resident < reserve
+    many = server((n - 1) * resident + reserve, n)
+    tickets = [submit(many) for _ in range(n)]
+    s = wait(many, tickets, lambda s: s.active == n)
+    # ticks with all of them do not stop the server
+    wait(many, tickets, lambda t: t.active == n and t.ticks > s.ticks + 8)
+    """, degree, requests)
