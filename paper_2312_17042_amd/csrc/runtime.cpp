@@ -1109,6 +1109,33 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
     hipStream_t st = ctx->stream();
     Ctrl *dc = s->ctrl.as<Ctrl>();
     Ctrl &h = *s->h_ctrl;
+    const bool graph = use_graph && !ctx->timing;
+    const int gp = f32 ? 1 : 0;
+    const bool fused = use_fused(ctx, dm, f32);
+    if (s->graph_fused[gp] != fused) s->drop_graphs(gp);      // captured with the other stage kernels
+    s->graph_fused[gp] = fused;
+    // n steps as one graph
+    const auto capture = [&](int64_t n) -> cteno_status {
+        hipGraphExec_t &gx = s->graph[gp][n > 1];
+        if (gx) return CTENO_OK;
+        hipGraph_t g = nullptr;
+        HIP_TRY(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
+        hipError_t e = hipSuccess;
+        for (int64_t k = 0; k < n && e == hipSuccess; ++k) e = issue_step(ctx, s, f32, st);
+        const hipError_t e2 = hipStreamEndCapture(st, &g);
+        if (e == hipSuccess) e = e2;
+        if (e == hipSuccess) e = hipGraphInstantiate(&gx, g, nullptr, nullptr, 0);
+        if (g) (void)hipGraphDestroy(g);
+        if (e == hipSuccess) return CTENO_OK;
+        gx = nullptr;
+        return fail(CTENO_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e));
+    };
+    // every graph that the budget can need, before a step runs: a capture that
+    // fails leaves the solution as it was
+    if (graph && max_steps >= kGraphSteps)
+        if (cteno_status rc = capture(kGraphSteps)) return rc;
+    if (graph && max_steps % kGraphSteps)
+        if (cteno_status rc = capture(1)) return rc;
     std::memset(&h, 0, sizeof(Ctrl));
     h.t = s->t;
     h.t_final = t_final;
@@ -1118,68 +1145,36 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
     HIP_TRY(hipMemcpyAsync(dc, &h, sizeof(Ctrl), hipMemcpyHostToDevice, st));
     HIP_TRY(launch_dt_partials(dm, f32, s->U[0].as<double>(), s->dt_part.as<double>(),
                                dm.dt_parts(use_fused(ctx, dm, f32), f32), st));
-
-    // graphs need a capturable stream: the context's own stream when the
-    // caller uses the null stream
-    const bool graph = use_graph && !ctx->timing;
-    hipStream_t gs = st;
-    hipEvent_t ev = nullptr;
-    if (graph && st == nullptr) {
-        gs = ctx->own_stream;
-        HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        HIP_TRY(hipEventRecord(ev, st));
-        HIP_TRY(hipStreamWaitEvent(gs, ev, 0));
-    }
-    const int gp = f32 ? 1 : 0;
-    const bool fused = use_fused(ctx, dm, f32);
-    if (s->graph_fused[gp] != fused) s->drop_graphs(gp);      // captured with the other stage kernels
-    s->graph_fused[gp] = fused;
-    // issues n steps as one graph
-    const auto launch_steps = [&](int64_t n) -> cteno_status {
-        hipGraphExec_t &gx = s->graph[gp][n > 1];
-        if (!gx) {
-            hipGraph_t g = nullptr;
-            HIP_TRY(hipStreamBeginCapture(gs, hipStreamCaptureModeThreadLocal));
-            hipError_t e = hipSuccess;
-            for (int64_t k = 0; k < n && e == hipSuccess; ++k) e = issue_step(ctx, s, f32, gs);
-            hipError_t e2 = hipStreamEndCapture(gs, &g);
-            if (e != hipSuccess) return fail(CTENO_ERR_DEVICE, std::string("capture: ") + hipGetErrorString(e));
-            HIP_TRY(e2);
-            HIP_TRY(hipGraphInstantiate(&gx, g, nullptr, nullptr, 0));
-            (void)hipGraphDestroy(g);
-        }
-        HIP_TRY(hipGraphLaunch(gx, gs));
-        return CTENO_OK;
-    };
     // steps are issued in chunks between host checks of the done flag; a
     // step issued after the march has reached t_final exits at once on the
     // device.  No more steps than the budget are issued.
-    int64_t issued = 0;
-    while (issued < max_steps) {
-        const int64_t chunk = std::min<int64_t>(16, max_steps - issued);
-        for (int64_t k = 0; k < chunk;) {
-            const int64_t n = graph && chunk - k >= kGraphSteps ? kGraphSteps : 1;
-            if (graph) {
-                if (cteno_status rc = launch_steps(n)) return rc;
-            } else {
-                HIP_TRY(issue_step(ctx, s, f32, gs));
+    const auto march = [&]() -> cteno_status {
+        int64_t issued = 0;
+        while (issued < max_steps) {
+            const int64_t chunk = std::min<int64_t>(16, max_steps - issued);
+            for (int64_t k = 0; k < chunk;) {
+                const int64_t n = graph && chunk - k >= kGraphSteps ? kGraphSteps : 1;
+                if (graph) HIP_TRY(hipGraphLaunch(s->graph[gp][n > 1], st));
+                else HIP_TRY(issue_step(ctx, s, f32, st));
+                k += n;
             }
-            k += n;
+            issued += chunk;
+            HIP_TRY(hipMemcpyAsync(&h, dc, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            collect_timing(ctx);
+            if (h.done) break;
         }
-        issued += chunk;
-        HIP_TRY(hipMemcpyAsync(&h, dc, sizeof(Ctrl), hipMemcpyDeviceToHost, gs));
-        HIP_TRY(hipStreamSynchronize(gs));
-        collect_timing(ctx);
-        if (h.done) break;
-    }
-    HIP_TRY(launch_control(dc, nullptr, 0, 1, gs));
-    HIP_TRY(hipMemcpyAsync(&h, dc, sizeof(Ctrl), hipMemcpyDeviceToHost, gs));
-    HIP_TRY(hipStreamSynchronize(gs));
-    if (ev) {
-        (void)hipEventDestroy(ev);
-    }
+        return CTENO_OK;
+    };
+    const cteno_status rc = march();
+    const std::string msg = g_err;
+    // also after a failed launch: the steps before it have advanced the state
+    HIP_TRY(launch_control(dc, nullptr, 0, 1, st));
+    HIP_TRY(hipMemcpyAsync(&h, dc, sizeof(Ctrl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
     s->t = h.t;
     if (steps_done) *steps_done = h.step;
+    if (rc != CTENO_OK) return fail(rc, msg);
     if (h.nonphysical) return fail(CTENO_ERR_NONPHYSICAL, "non-physical state (density or pressure <= 0, or NaN)");
     return CTENO_OK;
 }

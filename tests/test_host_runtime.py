@@ -105,3 +105,31 @@ def test_server_runs_every_solve_that_the_budget_admits(host, degree, requests):
     # ticks with all of them do not stop the server
     wait(many, tickets, lambda t: t.active == n and t.ticks > s.ticks + 8)
     """, degree, requests)
+
+
+@pytest.mark.parametrize("steps,captures", [(1, 1), (3, 1), (4, 1), (5, 2), (16, 1), (18, 2), (40, 1)])
+def test_march_captures_before_it_launches(host, steps, captures):
+    """The graphs that a march needs are captured before its first step: when one
+    cannot be made the call fails with nothing launched, and the next call marches."""
+    host("""
+    steps, captures = map(int, sys.argv[1:])
+    m = W.split_jitter_mesh(16, 16, (0.0, 10.0, 0.0, 10.0), seed=5)
+    u = np.ascontiguousarray(np.tile([[1.0], [0.5], [0.0], [3.0]], (1, m.n_cells)))
+    ctx = context()
+    mesh = upload(ctx, m, T.make_scheme(degree=3, precision=T.BOTH))
+    for prec in (T.FP64, T.MIXED):
+        for failing in range(1, captures + 1):
+            sol, n = solution(ctx, mesh, u), C.c_int64(-7)
+            march = lambda: L.cteno_solve(ctx, mesh, sol, prec, 1e30, steps, 0.3, 1, C.byref(n))
+            launched, made = count("graph_launch"), count("instantiate")
+            kernels, events = count("kernel"), count("event_alive")
+            standin.standin_fail_instantiate(failing)
+            ok(march(), T.ERR_DEVICE)
+            assert count("graph_launch") == launched and count("kernel") == kernels and n.value == -7
+            assert count("graph_alive") == 0 and count("event_alive") == events
+            ok(march())
+            assert count("graph_launch") - launched == steps // 4 + steps % 4
+            # (the one that failed is made again, those before it are kept)
+            assert count("instantiate") - made == captures + 1 and count("graph_alive") == 0
+            L.cteno_sol_destroy(sol)
+    """, steps, captures)
