@@ -152,7 +152,9 @@ constexpr size_t kStageChunk = 2u << 20;
 // 6.7 ms instead of 9.1 and down in 7.1 instead of 25.2; 64 MB in 1.9 and 1.9
 // instead of 2.5 and 4.0; 23 MB in 0.9 and 0.95 instead of 0.8 and 1.45, so
 // uploads start larger.  Memory that the runtime knows (pinned, managed, device)
-// goes directly, and so does a transfer while another thread's holds the buffers.
+// goes directly, and so does a transfer while another thread's holds the buffers,
+// and one on the per-thread stream, whose handle would mean another stream in each
+// of the threads.
 constexpr size_t kStageMinUp = 32u << 20, kStageMinDown = 8u << 20;
 
 hipError_t host_copy(cteno_ctx *c, void *dev, void *host, size_t n, bool up, hipStream_t st) {
@@ -160,7 +162,7 @@ hipError_t host_copy(cteno_ctx *c, void *dev, void *host, size_t n, bool up, hip
         return up ? hipMemcpyAsync(dev, host, n, hipMemcpyHostToDevice, st)
                   : hipMemcpyAsync(host, dev, n, hipMemcpyDeviceToHost, st);
     };
-    if (n < (up ? kStageMinUp : kStageMinDown)) return direct();
+    if (n < (up ? kStageMinUp : kStageMinDown) || st == hipStreamPerThread) return direct();
     hipPointerAttribute_t at{};
     if (hipPointerGetAttributes(&at, host) != hipSuccess) (void)hipGetLastError();
     else if (at.type != hipMemoryTypeUnregistered) return direct();

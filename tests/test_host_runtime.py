@@ -133,3 +133,25 @@ def test_march_captures_before_it_launches(host, steps, captures):
             assert count("instantiate") - made == captures + 1 and count("graph_alive") == 0
             L.cteno_sol_destroy(sol)
     """, steps, captures)
+
+
+@pytest.mark.parametrize("stream,staged", [(None, True), (1, True), (2, False)])
+def test_staged_transfers_keep_the_caller_s_stream(host, stream, staged):
+    """Large states are staged by several threads, except on the per-thread
+    stream (2), whose handle means another stream in each of them: there every
+    copy comes from the calling thread.  (1: the legacy null stream.)"""
+    host("""
+    stream, staged = eval(sys.argv[1]), eval(sys.argv[2])
+    m = W.split_jitter_mesh(820, 660, (0.0, 10.0, 0.0, 10.0), seed=5)    # 34.6 MB of Euler states
+    u = np.random.default_rng(1).random((4, m.n_cells)) + 1.0
+    ctx = context(stream)
+    mesh = upload(ctx, m, T.make_scheme(degree=2, precision=T.MIXED))
+    sol = solution(ctx, mesh, u)
+    got, t = np.empty_like(u), C.c_double()
+    before = count("foreign_copy")
+    for k in range(4):
+        ok(L.cteno_sol_set(sol, T._np_ptr(u), 0.25))
+        ok(L.cteno_sol_download(sol, T._np_ptr(got), C.byref(t)))
+        assert t.value == 0.25
+    assert (count("foreign_copy") > before) == staged
+    """, stream, staged, timeout=240)
