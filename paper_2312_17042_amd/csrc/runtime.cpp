@@ -747,21 +747,18 @@ struct cteno_sol {
         drop_graphs(1);
         if (h_ctrl) (void)hipHostFree(h_ctrl);
     }
+    // face-point values (null: allocation failed).  The FP32 fused stage's terms
+    // come with them: a stage after a reconstruction allocates nothing, so that a
+    // caller can capture it
     void *fv(bool f32) {
+        const DeviceMesh &dm = mesh->dm;
         DevBuf &b = FV[f32 ? 1 : 0];
-        if (!b.p) {
-            const DeviceMesh &dm = mesh->dm;
-            b = DevBuf(ctx, (size_t)dm.Np * 3 * dm.Nq * dm.nv * (f32 ? sizeof(float) : sizeof(double)));
+        if (!b.p) b = DevBuf(ctx, (size_t)dm.Np * 3 * dm.Nq * dm.nv * (f32 ? sizeof(float) : sizeof(double)));
+        if (f32 && dm.fused && dm.lists[1].bc == 64 && !xterm.p) {
+            xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.lists[1].n_sides, 1) * dm.nv * sizeof(float));
+            if (!xterm.p) return nullptr;
         }
         return b.p;
-    }
-    // the FP32 fused stage's work buffer (null: allocation failed)
-    void *xt() {
-        if (!xterm.p) {
-            const DeviceMesh &dm = mesh->dm;
-            xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.lists[1].n_sides, 1) * dm.nv * sizeof(float));
-        }
-        return xterm.p;
     }
 };
 
@@ -1017,12 +1014,6 @@ namespace {
 // asks for the separate reconstruction and flux kernels
 bool use_fused(const cteno_ctx *ctx, const DeviceMesh &dm, bool) { return dm.fused && ctx->fused_stage; }
 
-// whether the second stage kernel sums its cells' faces itself (FP32 in blocks
-// of 64 cells)
-bool needs_terms(const cteno_ctx *ctx, const DeviceMesh &dm, bool f32) {
-    return f32 && use_fused(ctx, dm, f32) && dm.lists[1].bc == 64;
-}
-
 // one SSP-RK3 stage on sol; dt from a device pointer or a host value
 hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const double *dt_ptr, double dt_value,
                        Ctrl *ctrl, double *dt_part, hipStream_t st) {
@@ -1046,7 +1037,7 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
     fl.dt_part = dt_part;
     fl.t_base = s->t;
     if (use_fused(ctx, dm, f32)) {
-        if (needs_terms(ctx, dm, f32)) fl.xterm = s->xt();
+        if (f32) fl.xterm = s->xterm.p;
         hipError_t e = timed(ctx, 0, [&] { return launch_stage(dm, f32, fl, done, 0, st, &ss->fallbacks); });
         if (e != hipSuccess) return e;
         return timed(ctx, 1, [&] { return launch_stage(dm, f32, fl, done, 1, st, &ss->fallbacks); });
@@ -1056,10 +1047,6 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
     return timed(ctx, 1, [&] { return launch_flux(dm, f32, fl, st); });
 }
 
-// the work buffers of a stage, allocated before it is issued or captured
-bool stage_buffers(cteno_ctx *ctx, cteno_sol *s, bool f32) {
-    return s->fv(f32) && (!needs_terms(ctx, s->mesh->dm, f32) || s->xt());
-}
 }  // namespace
 
 extern "C" cteno_status cteno_rk_stage(cteno_ctx *ctx, const cteno_mesh *m, cteno_sol *sol, int32_t precision,
@@ -1070,7 +1057,7 @@ extern "C" cteno_status cteno_rk_stage(cteno_ctx *ctx, const cteno_mesh *m, cten
     bool f32;
     if (cteno_status rc = check_precision(m, precision, f32)) return rc;
     HIP_TRY(hipSetDevice(ctx->device));
-    if (!stage_buffers(ctx, sol, f32)) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    if (!sol->fv(f32)) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     HIP_TRY(issue_stage(ctx, sol, f32, stage, nullptr, dt, nullptr, nullptr, ctx->stream()));
     if (stage == 2) sol->t += dt;
     return CTENO_OK;
@@ -1106,7 +1093,7 @@ extern "C" cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *m, cteno_s
     bool f32;
     if (cteno_status rc = check_precision(m, precision, f32)) return rc;
     HIP_TRY(hipSetDevice(ctx->device));
-    if (!stage_buffers(ctx, s, f32)) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+    if (!s->fv(f32)) return fail(CTENO_ERR_NOMEM, "device allocation failed");
     const DeviceMesh &dm = m->dm;
     hipStream_t st = ctx->stream();
     Ctrl *dc = s->ctrl.as<Ctrl>();

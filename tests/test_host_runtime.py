@@ -155,3 +155,26 @@ def test_staged_transfers_keep_the_caller_s_stream(host, stream, staged):
         assert t.value == 0.25
     assert (count("foreign_copy") > before) == staged
     """, stream, staged, timeout=240)
+
+
+@pytest.mark.parametrize("degree", [2, 3, 4])
+@pytest.mark.parametrize("precision", ["FP64", "MIXED"])
+def test_stages_after_a_reconstruction_allocate_nothing(host, degree, precision):
+    """A program that has reconstructed once may capture its RK stages."""
+    host("""
+    degree, prec = int(sys.argv[1]), getattr(T, sys.argv[2])
+    m = W.split_jitter_mesh(20, 16, (0.0, 10.0, 0.0, 10.0), seed=5)
+    u = np.ascontiguousarray(np.tile([[1.0], [0.5], [0.0], [3.0]], (1, m.n_cells)))
+    ctx = context()
+    for fused in (1, 0):
+        ok(L.cteno_ctx_set_fused_stage(ctx, fused))
+        mesh = upload(ctx, m, T.make_scheme(degree=degree, precision=T.BOTH))
+        sol = solution(ctx, mesh, u)
+        values = np.empty((m.n_cells, 3, 4, 4))
+        ok(L.cteno_reconstruct(ctx, mesh, sol, prec, T._np_ptr(values), None, None))
+        ok(L.cteno_ctx_set_fused_stage(ctx, 1))
+        before = count("malloc")
+        for stage in range(3):
+            ok(L.cteno_rk_stage(ctx, mesh, sol, prec, stage, 1e-3))
+        assert count("malloc") == before
+    """, degree, precision)
