@@ -14,7 +14,6 @@
 #include <cstring>
 #include <memory>
 #include <string>
-#include <system_error>
 #include <vector>
 
 #include "cteno_internal.h"
@@ -55,9 +54,10 @@ struct cteno_ctx {
     struct Pending { int kernel; hipEvent_t a, b; };
     std::vector<Pending> pending;
     std::vector<hipEvent_t> event_pool;
-    // pinned staging for large transfers (host_copy): made by the first one, given
-    // back with the context, used by one transfer at a time
+    // pinned staging for large transfers (host_copy): given back with the context,
+    // used by one transfer at a time
     std::mutex stage_mu;
+    size_t unstaged = 0;        // bytes of large transfers before there was any
     char *stage_buf = nullptr;
     std::vector<hipEvent_t> stage_ev;
     hipStream_t stream() const { return user_stream ? user_stream : own_stream; }
@@ -141,21 +141,24 @@ struct DevBuf {
     template <class T> T *as() const { return (T *)p; }
 };
 
-constexpr int kStageThreads = 8;
+constexpr int kStageThreads = 6;
 constexpr size_t kStageChunk = 2u << 20;
 
 // n bytes between host memory and the device, on stream st (complete when the
 // caller has synchronised it).  From kStageMin* bytes on, several threads copy
-// chunks through pinned buffers of their own (two each, 32 MB in all) while the
-// others' are in flight: one thread's copies, and on the way back its first touch
-// of the caller's pages, are what bounds the runtime's own path.  256 MB go up in
-// 6.7 ms instead of 9.1 and down in 7.1 instead of 25.2; 64 MB in 1.9 and 1.9
-// instead of 2.5 and 4.0; 23 MB in 0.9 and 0.95 instead of 0.8 and 1.45, so
-// uploads start larger.  Memory that the runtime knows (pinned, managed, device)
-// goes directly, and so does a transfer while another thread's holds the buffers,
-// and one on the per-thread stream, whose handle would mean another stream in each
-// of the threads.
-constexpr size_t kStageMinUp = 32u << 20, kStageMinDown = 8u << 20;
+// chunks through a pinned buffer each (12 MB in all) while the others' are in
+// flight: one thread's copies, and on the way back its first touch of the caller's
+// pages, are what bounds the runtime's own path.  256 MB go up in 6.6 ms instead of
+// 9.1 and down in 6.6 instead of 25; 64 MB in 1.8 and 1.75 instead of 2.4 and 3.8;
+// 23 MB down in 0.8 instead of 1.4, up in no less, so uploads start larger.  (Eight
+// threads with two buffers each: 6.7, 7.1; 1.85, 1.87; 0.9.)
+// The buffers' own first touch takes 0.4 ms a MB and thread, once: 64 MB pay for it
+// at once (2.2 ms), 23 MB do not (2.0).  So the buffers are made by the transfer
+// with which kStageFirst bytes have met none; those before it go directly.
+// Memory that the runtime knows (pinned, managed, device) goes directly too, and so
+// does a transfer while another thread's holds the buffers, and one on the
+// per-thread stream, whose handle would mean another stream in each of the threads.
+constexpr size_t kStageMinUp = 32u << 20, kStageMinDown = 8u << 20, kStageFirst = 32u << 20;
 
 hipError_t host_copy(cteno_ctx *c, void *dev, void *host, size_t n, bool up, hipStream_t st) {
     const auto direct = [&] {
@@ -169,12 +172,14 @@ hipError_t host_copy(cteno_ctx *c, void *dev, void *host, size_t n, bool up, hip
     std::unique_lock<std::mutex> lk(c->stage_mu, std::try_to_lock);
     if (!lk.owns_lock()) return direct();
     if (!c->stage_buf) {
-        while (c->stage_ev.size() < 2 * kStageThreads) {
+        c->unstaged += n;
+        if (c->unstaged < kStageFirst) return direct();
+        while (c->stage_ev.size() < kStageThreads) {
             hipEvent_t e = nullptr;
             if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); return direct(); }
             c->stage_ev.push_back(e);
         }
-        if (hipHostMalloc((void **)&c->stage_buf, 2 * kStageThreads * kStageChunk, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc((void **)&c->stage_buf, kStageThreads * kStageChunk, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             c->stage_buf = nullptr;
             return direct();
@@ -185,42 +190,42 @@ hipError_t host_copy(cteno_ctx *c, void *dev, void *host, size_t n, bool up, hip
     std::atomic<int> err{(int)hipSuccess};
     const auto work = [&](int t) {
         hipError_t e = hipSetDevice(c->device);
-        int64_t held[2] = {-1, -1};      // the chunk that a buffer's copy belongs to
-        const auto buf = [&](int k) { return c->stage_buf + (size_t)(2 * t + k) * kStageChunk; };
+        char *const buf = c->stage_buf + (size_t)t * kStageChunk;
+        const hipEvent_t ev = c->stage_ev[t];
+        int64_t held = -1;               // the chunk that the buffer's copy belongs to
         const auto off = [&](int64_t j) { return (size_t)j * kStageChunk; };
         const auto len = [&](int64_t j) { return std::min(kStageChunk, n - off(j)); };
         // waits for the buffer's copy; on the way down hands its data over
-        const auto finish = [&](int k) {
-            if (held[k] < 0) return;
-            const hipError_t w = hipEventSynchronize(c->stage_ev[2 * t + k]);
+        const auto finish = [&] {
+            if (held < 0) return;
+            const hipError_t w = hipEventSynchronize(ev);
             if (e == hipSuccess) e = w;
-            if (!up && e == hipSuccess) std::memcpy((char *)host + off(held[k]), buf(k), len(held[k]));
-            held[k] = -1;
+            if (!up && e == hipSuccess) std::memcpy((char *)host + off(held), buf, len(held));
+            held = -1;
         };
-        for (int k = 0; e == hipSuccess && err.load() == (int)hipSuccess; k ^= 1) {
+        while (e == hipSuccess && err.load() == (int)hipSuccess) {
             const int64_t j = next.fetch_add(1);
             if (j >= chunks) break;
-            finish(k);
+            finish();
             if (e != hipSuccess) break;
-            if (up) std::memcpy(buf(k), (const char *)host + off(j), len(j));
-            e = up ? hipMemcpyAsync((char *)dev + off(j), buf(k), len(j), hipMemcpyHostToDevice, st)
-                   : hipMemcpyAsync(buf(k), (const char *)dev + off(j), len(j), hipMemcpyDeviceToHost, st);
+            if (up) std::memcpy(buf, (const char *)host + off(j), len(j));
+            e = up ? hipMemcpyAsync((char *)dev + off(j), buf, len(j), hipMemcpyHostToDevice, st)
+                   : hipMemcpyAsync(buf, (const char *)dev + off(j), len(j), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) {
-                held[k] = j;
-                e = hipEventRecord(c->stage_ev[2 * t + k], st);
+                held = j;
+                e = hipEventRecord(ev, st);
             }
         }
-        finish(0);
-        finish(1);
+        finish();
         if (e != hipSuccess) err.store((int)e);
     };
     // (threads that cannot be started leave their chunks to the others)
     std::thread th[kStageThreads];
-    const int nt = (int)std::min<int64_t>({kStageThreads, std::max(1u, std::thread::hardware_concurrency()), (chunks + 1) / 2});
+    const int nt = (int)std::min<int64_t>({kStageThreads, std::max(1u, std::thread::hardware_concurrency()), chunks});
     for (int t = 1; t < nt; ++t) {
         try {
             th[t] = std::thread(work, t);
-        } catch (const std::system_error &) {
+        } catch (...) {
             break;
         }
     }

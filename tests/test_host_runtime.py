@@ -178,3 +178,22 @@ def test_stages_after_a_reconstruction_allocate_nothing(host, degree, precision)
             ok(L.cteno_rk_stage(ctx, mesh, sol, prec, stage, 1e-3))
         assert count("malloc") == before
     """, degree, precision)
+
+
+def test_staging_is_made_when_transfers_pay_for_it(host):
+    """A program that takes one smaller state back makes no pinned buffers; they
+    come with the transfer that completes 32 MB, once, and bounded."""
+    host("""
+    m = W.split_jitter_mesh(520, 350, (0.0, 10.0, 0.0, 10.0), seed=5)     # 11.6 MB of Euler states
+    u = np.random.default_rng(1).random((4, m.n_cells)) + 1.0
+    got, t = np.empty_like(u), C.c_double()
+    ctx = context()
+    mesh = upload(ctx, m, T.make_scheme(degree=2, precision=T.MIXED))
+    sol = solution(ctx, mesh, u)
+    before, made = count("pinned"), []
+    for k in range(5):
+        ok(L.cteno_sol_set(sol, T._np_ptr(u), 0.0))
+        ok(L.cteno_sol_download(sol, T._np_ptr(got), C.byref(t)))
+        made.append(count("pinned") - before)
+    assert made == [0, 0, 1, 1, 1], made
+    """)
