@@ -181,9 +181,12 @@ const char *cteno_last_error(void);
    kernel per stage reconstructs each block of cells (64, or 256 on large
    MIXED meshes) into on-chip memory and evaluates the fluxes of the faces
    inside the block there, and a second kernel finishes the cells with
-   faces to other blocks; on = 0, a reconstruction kernel writes all face
-   values to device memory and a flux kernel reads them back.  A stage's results agree to FP64 rounding (the
-   fused path sums a cell's faces inside its block first).  Synchronises. */
+   faces to other blocks; on = 0, and where a numbering (scheme.reorder = 0)
+   scatters neighbours so that more than half of the faces lead to other
+   blocks, a reconstruction kernel writes all face values to device memory
+   and a flux kernel reads them back.  A stage's results agree to FP64
+   rounding in FP64 (the fused path sums a cell's faces inside its block
+   first) and to the FP32 rounding of the fluxes in MIXED.  Synchronises. */
 cteno_status cteno_ctx_set_fused_stage(cteno_ctx *ctx, int32_t on);
 /* Per-kernel timing with HIP events on the context stream (off by default).
    kernel: 0 = reconstruction (the fused stage kernel when it runs), 1 =

@@ -509,9 +509,9 @@ static hipError_t stage_t(const DeviceMesh &m, const FluxLaunch &f, const int *d
 template <typename real>
 hipError_t stage_fused(const DeviceMesh &m, const FluxLaunch &f, const int *done, int part, hipStream_t st,
                        unsigned long long *fb_count) {
-    if (f.mode != 2 || m.r > 3 || m.tab.Nq != 2 || !m.fused || !f.FV) return hipErrorInvalidValue;
     constexpr bool F32 = std::is_same<real, float>::value;
     const StageLists &l = m.lists[F32];
+    if (f.mode != 2 || m.r > 3 || m.tab.Nq != 2 || !l.fused || !f.FV) return hipErrorInvalidValue;
     const bool sum = F32 && l.bc == 64;
     if (l.n_cross && (!l.xcells || !l.xarea || !l.xrec || (sum && !f.xterm))) return hipErrorInvalidValue;
     if (part == 1) {

@@ -41,6 +41,7 @@ namespace cteno {
 // cells, once, from their owner), and the cells with a face to another block
 // ("cross cells") with one record per such face ("side")
 struct StageLists {
+    bool fused = false;            // marches and stages run the fused kernels
     int bc = 64;
     int2 *fdesc = nullptr;         // per block its first listed face and their number
     void *frec = nullptr;          // [faces][4] normal, length, block face code (kBf*), of the precision type
@@ -60,6 +61,16 @@ struct StageLists {
 // to 90), and not for characteristic variables, whose selection per face leaves
 // room for two waves per SIMD only (448 / 545 us at 1.6M).
 constexpr int64_t kWideCells = 1200000;
+// The fused stage runs where at most half of the cells' faces lead to other
+// blocks: what it saves are the values of the others.  Morton order has 0.5 such
+// faces a cell, a mesh numbered row by row 1.0, a random numbering 3.0.  20 steps
+// at degree 3, fused / separate kernels, at 1.0, 1.4, 1.6, 2.4 and 3.0: 2M cells
+// FP64 47.8 / 53.3, 53.4 / 54.4, 55.7 / 54.9, 62.5 / 58.4, 98.4 / 79.5 ms; mixed
+// 26.9 / 27.1, 29.3 / 28.7, 30.4 / 29.2, 39.6 / 33.6, 70.3 / 59.0; 500k FP64 11.5 /
+// 13.0, 13.0 / 13.2, 13.3 / 13.3, 15.2 / 13.9, 24.3 / 18.6.  FP64 with
+// characteristic variables spends more on the selection and the line lies higher:
+// 2M cells at 1.6, 2.4 and 3.0 65.5 / 67.2, 71.0 / 75.1, 112.1 / 104.1.
+constexpr double kFusedFaces = 1.5, kFusedFacesChar64 = 2.75;
 constexpr size_t kWideRowBytes = 28 * 1024;
 
 struct DeviceMesh {
@@ -96,7 +107,6 @@ struct DeviceMesh {
     RefTables tab;
     StageLists lists[2];           // fused stage (degree <= 3): FP64, FP32
     int64_t n_cross256 = 0;        // cells with a face to another 256-cell block
-    bool fused = false;            // the march runs the fused stage kernels
     int64_t blocks() const { return (N + 255) / 256; }
     int64_t groups() const { return Np / 64; }
     // LDS rows of one group

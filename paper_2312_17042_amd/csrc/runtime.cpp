@@ -390,10 +390,10 @@ static cteno_status upload_tables(DeviceMesh &dm, Alloc &&alloc_raw, hipStream_t
     return CTENO_OK;
 }
 
-// The fused stage's lists in one precision; fits: the side numbers fit
+// The fused stage's lists in one precision, where it runs (else l.fused stays
+// false and the separate kernels do)
 template <class Alloc>
-static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMesh &dm, bool f32, Alloc &&alloc_raw,
-                                       bool &fits) {
+static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMesh &dm, bool f32, Alloc &&alloc_raw) {
     StageLists &l = dm.lists[f32];
     l.bc = f32 && dm.vars != CTENO_VARS_CHARACTERISTIC && dm.N >= kWideCells && 2 * dm.row_bytes() <= kWideRowBytes
                ? 256 : 64;
@@ -419,10 +419,11 @@ static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMes
             sum[k] += n;
         }
     }
+    const double most = !f32 && dm.vars == CTENO_VARS_CHARACTERISTIC ? kFusedFacesChar64 : kFusedFaces;
+    if (sum[2] > (int64_t)kNbIndexMask || (double)sum[2] > most * (double)dm.N) return CTENO_OK;
+    l.fused = true;
     l.n_cross = sum[1];
     l.n_sides = sum[2];
-    fits = sum[2] <= (int64_t)kNbIndexMask;
-    if (!fits) return CTENO_OK;
     const size_t rs = 4 * (f32 ? sizeof(float) : sizeof(double));
     l.fdesc = (int2 *)alloc_raw((size_t)nb * sizeof(int2));
     l.xid = (uint32_t *)alloc_raw((size_t)dm.Np * sizeof(uint32_t));
@@ -572,13 +573,9 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
     // fused stage (degree <= 3; single meshes -- the batched serving kernels
     // keep the reconstruction + flux pair): its blocks' faces and the cells with
     // a face to another block, from the face codes
-    dm.fused = keep_fr64 && hm.r <= 3 && hm.Nq == 2;
-    for (int p = 0; p < 2 && dm.fused; ++p)
-        if (p ? dm.fr32 != nullptr : (s.precision & CTENO_FP64) != 0) {
-            bool fits = true;
-            if (cteno_status rc = upload_stage_lists(ctx, st, dm, p == 1, alloc_raw, fits)) return rc;
-            dm.fused = fits;               // (else the separate kernels)
-        }
+    for (int p = 0; p < 2 && keep_fr64 && hm.r <= 3; ++p)
+        if (p ? dm.fr32 != nullptr : (s.precision & CTENO_FP64) != 0)
+            if (cteno_status rc = upload_stage_lists(ctx, st, dm, p == 1, alloc_raw)) return rc;
     // release host-only copies that the device now holds
     hm.slot.clear(); hm.slot.shrink_to_fit();
     hm.slot_flag.clear(); hm.slot_flag.shrink_to_fit();
@@ -759,7 +756,7 @@ struct cteno_sol {
         const DeviceMesh &dm = mesh->dm;
         DevBuf &b = FV[f32 ? 1 : 0];
         if (!b.p) b = DevBuf(ctx, (size_t)dm.Np * 3 * dm.Nq * dm.nv * (f32 ? sizeof(float) : sizeof(double)));
-        if (f32 && dm.fused && dm.lists[1].bc == 64 && !xterm.p) {
+        if (f32 && dm.lists[1].fused && dm.lists[1].bc == 64 && !xterm.p) {
             xterm = DevBuf(ctx, (size_t)std::max<int64_t>(2 * dm.lists[1].n_sides, 1) * dm.nv * sizeof(float));
             if (!xterm.p) return nullptr;
         }
@@ -1015,9 +1012,9 @@ extern "C" cteno_status cteno_residual(cteno_ctx *ctx, const cteno_mesh *m, cons
 }
 
 namespace {
-// the fused stage kernels (degree <= 3, both precisions) unless the context
+// the fused stage kernels where the mesh has their lists, unless the context
 // asks for the separate reconstruction and flux kernels
-bool use_fused(const cteno_ctx *ctx, const DeviceMesh &dm, bool) { return dm.fused && ctx->fused_stage; }
+bool use_fused(const cteno_ctx *ctx, const DeviceMesh &dm, bool f32) { return dm.lists[f32].fused && ctx->fused_stage; }
 
 // one SSP-RK3 stage on sol; dt from a device pointer or a host value
 hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const double *dt_ptr, double dt_value,
