@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_reconstruct_batch(const ReconArgs<float
     extern __shared__ __align__(16) double rows[];
     double U0;
     float out[3][2];
-    recon_quad<float, R, 4, SCHEME, GFORM, 0, 0>(a, ptr, rows, i, threadIdx.x, i < t.N, [] {}, U0, out);
+    recon_quad<float, R, 4, SCHEME, GFORM, 0, 0, true>(a, ptr, rows, i, threadIdx.x, i < t.N, [] {}, U0, out);
     if (i >= t.N) return;
 #pragma unroll
     for (int f = 0; f < 3; ++f)

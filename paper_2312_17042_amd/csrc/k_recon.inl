@@ -6,7 +6,7 @@
 
 namespace cteno {
 
-template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS>
+template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS, bool NT>
 __global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, const ReconPtrs<real> ptr, int64_t N,
                                                      real *FV) {
     const int64_t i = xcd_block(blockIdx.x, gridDim.x) * 64 + (threadIdx.x >> 2);
@@ -15,8 +15,8 @@ __global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, co
     extern __shared__ __align__(16) double rows[];
     double U0;
     real out[3][2];
-    if (!recon_quad<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, rows, i, threadIdx.x, live, [] {},
-                                                                    U0, out)) return;
+    if (!recon_quad<real, R, NV, SCHEME, GFORM, DMODE, VARS, NT>(a, ptr, rows, i, threadIdx.x, live, [] {}, U0, out))
+        return;
     if (!live || q >= NV) return;
 #pragma unroll
     for (int f = 0; f < 3; ++f)
@@ -27,8 +27,15 @@ __global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, co
 template <typename real, int R, int NV, int VARS>
 static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real> &a, const ReconPtrs<real> &p, real *FV,
                                int dmode, unsigned grid, hipStream_t st) {
-#define CT_LAUNCH(SCH, GF, DM) \
-    hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS>), dim3(grid), dim3(256), m.row_bytes(), st, a, p, m.N, FV)
+#define CT_LAUNCH(SCH, GF, DM)                                                                                    \
+    do {                                                                                                          \
+        if (m.stream_nontemporal(std::is_same<real, float>::value))                                               \
+            hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, true>), dim3(grid), dim3(256),      \
+                               m.row_bytes(), st, a, p, m.N, FV);                                                 \
+        else                                                                                                      \
+            hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, false>), dim3(grid), dim3(256),     \
+                               m.row_bytes(), st, a, p, m.N, FV);                                                 \
+    } while (0)
 #define CT_DM(SCH, GF)                        \
     switch (dmode) {                          \
         case 0: CT_LAUNCH(SCH, GF, 0); break; \

@@ -73,7 +73,7 @@ __device__ __forceinline__ bool listed_face(const FluxArgs<real> fa, double dt, 
 
 // The registers are held to five waves per SIMD in FP32 and four in FP64; FP64
 // with characteristic variables would spill at four (128 B a lane) and runs three
-template <typename real, int R, int NV, int SCHEME, int GFORM, int VARS, int PHYS>
+template <typename real, int R, int NV, int SCHEME, int GFORM, int VARS, int PHYS, bool NT>
 __global__ __launch_bounds__(256, (std::is_same<real, double>::value ? (VARS ? 3 : 4) : 5))
 void k_stage(const ReconArgs<real> ra, const ReconPtrs<real> rp, const FluxArgs<real> fa) {
     constexpr int NQ = 2, ROW = 3 * NQ * NV;
@@ -100,7 +100,7 @@ void k_stage(const ReconArgs<real> ra, const ReconPtrs<real> rp, const FluxArgs<
         // (a place past the list reads the list's last entry)
         packed_face(fa.frec, f0 + max(min((int)(threadIdx.x >> 1), nf - 1), 0), nx, ny, len, code);
     };
-    if (!recon_quad<real, R, NV, SCHEME, GFORM, 0, VARS>(ra, rp, rows, i, threadIdx.x, live, mid, U0, out)) return;
+    if (!recon_quad<real, R, NV, SCHEME, GFORM, 0, VARS, NT>(ra, rp, rows, i, threadIdx.x, live, mid, U0, out)) return;
     const int xmask = xid >> 28;                         // the cell's faces to other groups
     if (q < NV) {
 #pragma unroll
@@ -196,7 +196,7 @@ void k_stage_wide(const ReconArgs<float> ra, const ReconPtrs<float> rp, const Fl
     const int stop = *(rp.done ? rp.done : &rp.desc->x);
     if (rp.done && stop) return;
     GroupRows<NV> gr;
-    QuadStream<real, R> qs;
+    QuadStream<real, R, true> qs;
     double U0, Un0;
     int fl, fln;
     uint32_t xid, xidn;
@@ -466,8 +466,12 @@ static void stage_launch(const DeviceMesh &m, const ReconArgs<real> &ra, const R
                                    (int)(m.row_bytes() / 8));                                                     \
                 break;                                                                                            \
             }                                                                                                     \
-        hipLaunchKernelGGL((k_stage<real, R, NV, SCH, GF, VARS, PHYS>), dim3(grid), dim3(256), m.row_bytes(), st, \
-                           ra, rp, fa);                                                                           \
+        if (m.stream_nontemporal(F32))                                                                            \
+            hipLaunchKernelGGL((k_stage<real, R, NV, SCH, GF, VARS, PHYS, true>), dim3(grid), dim3(256),          \
+                               m.row_bytes(), st, ra, rp, fa);                                                    \
+        else                                                                                                      \
+            hipLaunchKernelGGL((k_stage<real, R, NV, SCH, GF, VARS, PHYS, false>), dim3(grid), dim3(256),         \
+                               m.row_bytes(), st, ra, rp, fa);                                                    \
     } while (0)
     if (m.scheme == CTENO_SCHEME_CTENOZ && m.gamma_form == CTENO_GAMMA_SCALED) ST_LAUNCH(CTENO_SCHEME_CTENOZ, CTENO_GAMMA_SCALED);
     else if (m.scheme == CTENO_SCHEME_CTENOZ) ST_LAUNCH(CTENO_SCHEME_CTENOZ, CTENO_GAMMA_PAPER);

@@ -71,6 +71,15 @@ constexpr int64_t kWideCells = 1200000;
 // characteristic variables spends more on the selection and the line lies higher:
 // 2M cells at 1.6, 2.4 and 3.0 65.5 / 67.2, 71.0 / 75.1, 112.1 / 104.1.
 constexpr double kFusedFaces = 1.5, kFusedFacesChar64 = 2.75;
+// Degree 2 and 3: what a stage reads and writes, of which the 256 MB memory-side
+// cache keeps a stream that fits, but not one that is loaded nontemporally.  20
+// steps, nontemporal / plain loads: one variable, degree 2, mixed 2677 / 2502 us at
+// 400k cells (200 MB), 3100 / 2924 at 500k (250 MB), 4191 / 4710 at 700k (350 MB);
+// degree 3 mixed 2967 / 2787 at 200k (204 MB), 4523 / 5048 at 353k (360 MB); FP64
+// 3845 / 3621 at 150k (264 MB), 4888 / 5270 at 200k.  Below, nontemporal streams
+// stay in it too and leave the L2s to the averages: one variable, degree 2, mixed
+// 1117 / 1183 at 100k (50 MB), 1395 / 1434 at 150k (75 MB).
+constexpr double kCachedStream[2] = {128e6, 268e6};
 constexpr size_t kWideRowBytes = 28 * 1024;
 
 struct DeviceMesh {
@@ -111,6 +120,10 @@ struct DeviceMesh {
     int64_t groups() const { return Np / 64; }
     // LDS rows of one group
     size_t row_bytes() const { return (size_t)(64 + max_halo) * nv * sizeof(double); }
+    bool stream_nontemporal(bool f32) const {
+        const double cell = (double)E * (f32 ? 4 : 8) + 2.0 * row_entries(r) + 32.0 * nv + 100.0;
+        return (double)N * cell < kCachedStream[0] || (double)N * cell > kCachedStream[1];
+    }
     int64_t stage_blocks(bool f32) const { return (N + lists[f32].bc - 1) / lists[f32].bc; }
     // Per-block CFL minima of one march step that the control reduces: the
     // fused stage's second kernel's (which fold in the first kernel's, stored

@@ -260,13 +260,20 @@ template <int R> struct RowIds;
 template <> struct RowIds<3> { using T = RowIds3; };
 template <> struct RowIds<2> { using T = RowIds2; };
 
+// a vector of the stream: nontemporal, or kept by the caches (stream_nontemporal)
+template <bool NT, typename V>
+__device__ __forceinline__ V stream_load(const V *p) {
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
+
 // A lane's share of its tile's row numbers and stream (16 cells, one wave).
 // Lanes without an entry read another one's: no more bytes, and what they hold
 // meets unused rows of the result or zero differences.
-template <typename real, int R> struct QuadStream;
+template <typename real, int R, bool NT> struct QuadStream;
 
-template <int R>
-struct QuadStream<float, R> {
+template <int R, bool NT>
+struct QuadStream<float, R, NT> {
     using D = QuadDims<R>;
     static constexpr int S = D::S, MA = D::MA, NAV = S * MA / 4;
     typename RowIds<R>::T ids;            // of slots q, q + 4, ... of the lane's cell
@@ -277,7 +284,7 @@ struct QuadStream<float, R> {
     }
     __device__ __forceinline__ void request(const float *P, int64_t tile, int lane) {
         const float *__restrict__ Pt = P + (size_t)tile * (D::E * 16);
-        auto ldv = [&](int off) { return __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(Pt + off)); };
+        auto ldv = [&](int off) { return stream_load<NT>(reinterpret_cast<const f32x4 *>(Pt + off)); };
         const int q = lane & 3, c16 = lane >> 2, o2 = q < 2 ? q : 2;
         constexpr int B0 = S * MA * 64;
         // in the order of their use, so that the products start with the first
@@ -288,7 +295,7 @@ struct QuadStream<float, R> {
                 if (g * MA + m < NAV) bA[g * MA + m] = ldv(((g * MA + m) * 64 + lane) * 4);
             if (g < 3) bB[g] = ldv(B0 + ((g * 16 + c16) * 3 + o2) * 4);
             if (g == 3) bB[3] = ldv(B0 + 576 + c16 * 4);
-            if (g == 4) tl = __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(Pt + B0 + 640 + c16 * 2));
+            if (g == 4) tl = stream_load<NT>(reinterpret_cast<const f32x2 *>(Pt + B0 + 640 + c16 * 2));
         }
     }
     template <int NV>
@@ -343,8 +350,8 @@ struct QuadStream<float, R> {
     }
 };
 
-template <int R>
-struct QuadStream<double, R> {
+template <int R, bool NT>
+struct QuadStream<double, R, NT> {
     using D = QuadDims<R>;
     static constexpr int MA = D::MA, G = D::G;
     // the four quarters of the tile's cells; two of them are requested at once,
@@ -362,8 +369,8 @@ struct QuadStream<double, R> {
     }
     __device__ __forceinline__ void quarter(const double *P, int64_t tile, int lane, int s) {
         const double *__restrict__ Pt = P + (size_t)tile * (D::E * 16) + s * (D::E * 4);
-        auto ldv = [&](int off) { return __builtin_nontemporal_load(reinterpret_cast<const f64x2 *>(Pt + off)); };
-        auto ld1 = [&](int off) { return __builtin_nontemporal_load(Pt + off); };
+        auto ldv = [&](int off) { return stream_load<NT>(reinterpret_cast<const f64x2 *>(Pt + off)); };
+        auto ld1 = [&](int off) { return stream_load<NT>(Pt + off); };
         const int q = lane & 3, kb = lane >> 2, o2 = q < 2 ? q : 2;
         constexpr int B0 = R == 3 ? 576 : 192;
         if constexpr (R == 3) {
@@ -456,7 +463,7 @@ struct QuadStream<double, R> {
 // Everything that is not the neighbours' averages is requested before the
 // first wait; what the group's descriptor leads to (list, then averages) is
 // the only chain.
-template <typename real, int R, int NV>
+template <typename real, int R, int NV, bool NT>
 __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double *rows, int64_t il, int t, double &U0,
                                               int &fl, real (&ao)[QuadDims<R>::K], real (&ad)[3][2]) {
     const int lane = t & 63, v = NV == 4 ? t & 3 : 0;
@@ -466,7 +473,7 @@ __device__ __forceinline__ bool quad_contract(const ReconPtrs<real> ptr, double 
     if (ptr.done && stop) return false;
     const int64_t tile = __builtin_amdgcn_readfirstlane((int)(il >> 4));
     GroupRows<NV> gr;
-    QuadStream<real, R> qs;
+    QuadStream<real, R, NT> qs;
     gr.list(ptr.hlist, desc, t);
     U0 = ptr.U[il * NV + v];
     fl = ptr.flags[il] & 7;
@@ -629,13 +636,13 @@ __device__ __forceinline__ void recon_finish(const ReconArgs<real> a, const Reco
 // registers are free: the caller's loads for what follows, which the
 // selection's arithmetic then covers.  False when the march is over (out is
 // not set).
-template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS, class Mid>
+template <typename real, int R, int NV, int SCHEME, int GFORM, int DMODE, int VARS, bool NT, class Mid>
 __device__ __forceinline__ bool recon_quad(const ReconArgs<real> a, const ReconPtrs<real> ptr, double *rows,
                                            int64_t il, int t, bool live, Mid &&mid, double &U0,
                                            real (&out)[3][2]) {
     real ao[QuadDims<R>::K], ad[3][2];
     int fl;
-    if (!quad_contract<real, R, NV>(ptr, rows, il, t, U0, fl, ao, ad)) return false;
+    if (!quad_contract<real, R, NV, NT>(ptr, rows, il, t, U0, fl, ao, ad)) return false;
     mid();
     recon_finish<real, R, NV, SCHEME, GFORM, DMODE, VARS>(a, ptr, il, t & 3, live, U0, fl, ao, ad, out);
     return true;

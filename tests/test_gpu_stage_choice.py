@@ -58,3 +58,43 @@ def test_scattered_numberings_take_the_separate_kernels(ctx, degree, variables, 
         ctx.set_fused_stage(True)
         s.close()
         m.close()
+
+
+@pytest.mark.parametrize("problem,degree,n", [("advection", 2, 380), ("advection", 3, 274), ("vortex", 2, 350),
+                                              ("vortex", 3, 264)])
+def test_streams_that_the_cache_keeps(ctx, problem, degree, n):
+    """Meshes whose pseudo-inverse streams are loaded through the caches in both
+    precisions: face values of sampled cells against the oracle (1e-12; mixed with
+    the selections of FP64 5e-6), and the fused stage against the separate kernels
+    over two steps (1e-12; mixed 1e-6, some FP32 roundings of the fluxes)."""
+    if problem == "vortex":
+        mesh = W.split_jitter_mesh(n, n, (0.0, 10.0, 0.0, 10.0), seed=31)
+        u0 = W.cell_average(mesh, W.isentropic_vortex(0.0, 3.0, (5.0, 5.0), (10.0, 10.0)), n=2)
+        kw = dict(physics=O.EULER, scheme=O.CTENOZ, degree=degree, lambda1_prime=1e4)
+    else:
+        mesh = W.split_jitter_mesh(n, n, (0.0, 1.0, 0.0, 1.0), seed=31)
+        u0 = W.cell_average(mesh, W.advection_sine(0.0), n=2)
+        kw = dict(physics=O.ADVECTION, scheme=O.CTENO, degree=degree, lambda1_prime=1e15, ax=1.0, ay=1.0)
+    cells = np.unique(np.r_[np.arange(70), np.random.default_rng(5).integers(0, mesh.n_cells, 400),
+                            np.arange(mesh.n_cells - 70, mesh.n_cells)])
+    values, selected = O.Oracle.from_mesh(mesh, **kw).reconstruct_cells(u0, cells)
+    m = T.Mesh.from_workload(ctx, mesh, precision=T.BOTH, **kw)
+    s = T.Solution(m, u0)
+    try:
+        fv, own = s.reconstruct(T.FP64)
+        assert np.array_equal(own.cpu().numpy()[cells], selected)
+        for got, tol in ((fv, 1e-12), (s.reconstruct(T.MIXED, forced=own.cpu().numpy())[0], 5e-6)):
+            got = got.cpu().numpy()[cells].reshape(-1, m.nv)
+            assert relerr(got.T, values.reshape(-1, m.nv).T) < tol
+        for prec, tol in ((T.FP64, 1e-12), (T.MIXED, 1e-6)):
+            ends = []
+            for fused in (True, False):
+                ctx.set_fused_stage(fused)
+                s.set(u0, 0.0)
+                assert s.solve(max_steps=2, cfl=0.3, precision=prec) == 2
+                ends.append(s.download()[0])
+            assert relerr(ends[0], ends[1]) < tol
+    finally:
+        ctx.set_fused_stage(True)
+        s.close()
+        m.close()
