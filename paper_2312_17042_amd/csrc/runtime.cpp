@@ -552,11 +552,11 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
         HIP_TRY(hipStreamSynchronize(st));
         int64_t total = 0;
         for (int64_t g = 0; g < ng; ++g) {
-            desc[g] = make_int2((int)total, hl[g]);
+            desc[g] = make_int2((int)(uint32_t)total, hl[g]);
             total += hl[g];
             dm.max_halo = std::max(dm.max_halo, (int)hl[g]);
         }
-        if (total > INT32_MAX) return fail(CTENO_ERR_INVALID, "neighbour lists too long");
+        if (total > (int64_t)UINT32_MAX) return fail(CTENO_ERR_INVALID, "neighbour lists too long");
         dm.desc = alloc_T(int2, (size_t)ng);
         dm.hlist = alloc_T(int32_t, (size_t)total + 1);    // (a group without neighbours reads one entry)
         dm.lslot = alloc_T(uint16_t, Np * row_entries(hm.r));

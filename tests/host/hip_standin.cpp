@@ -17,6 +17,8 @@ std::unordered_map<void *, size_t> blocks;
 int64_t live = 0, peak = 0;
 std::atomic<int64_t> n_malloc{0}, n_pinned{0}, n_capture{0}, n_instantiate{0}, n_graph{0}, n_graph_destroy{0},
     n_event{0}, n_event_destroy{0}, n_kernel{0}, n_foreign{0};
+size_t fill_size = 0;
+int32_t fill_value = 0;
 std::atomic<int> fail_instantiate{0};     // this instantiation from now fails (0: none)
 std::thread::id caller;
 thread_local bool capturing = false;
@@ -44,6 +46,8 @@ int64_t standin_count(const char *what) {
 }
 void standin_caller() { caller = std::this_thread::get_id(); }
 void standin_fail_instantiate(int nth) { fail_instantiate = nth; }
+// device allocations of this size hold that value instead of zeros
+void standin_fill(size_t bytes, int32_t value) { fill_size = bytes; fill_value = value; }
 
 void **__hipRegisterFatBinary(const void *) { static void *h = nullptr; return &h; }
 void __hipUnregisterFatBinary(void **) {}
@@ -75,6 +79,7 @@ hipError_t hipGetSymbolAddress(void **p, const void *) {
 hipError_t hipMalloc(void **p, size_t n) {
     *p = std::calloc(1, n);
     if (!*p) return hipErrorOutOfMemory;
+    for (size_t k = 0; n == fill_size && k < n / 4; ++k) ((int32_t *)*p)[k] = fill_value;
     ++n_malloc;
     std::lock_guard<std::mutex> lk(mu);
     blocks[*p] = n;

@@ -197,3 +197,18 @@ def test_staging_is_made_when_transfers_pay_for_it(host):
         made.append(count("pinned") - before)
     assert made == [0, 0, 1, 1, 1], made
     """)
+
+
+def test_long_neighbour_lists_are_accepted(host):
+    """Lists of more than 2^31 cells in all (some 120M cells of degree 3 in a
+    numbering that scatters every stencil), which a slot table had no limit for."""
+    host("""
+    m = W.split_jitter_mesh(15, 10, (0.0, 10.0, 0.0, 10.0), seed=5)      # five groups
+    ctx = context()
+    for each, want in (((1 << 29) - 1, T.OK), ((1 << 30) - 1, T.ERR_INVALID)):
+        standin.standin_fill(C.c_size_t(5 * 4), C.c_int32(each))         # the groups' lengths
+        d, h, scheme = T.mesh_desc(m.xy, m.tri, m.box, m.bc), C.c_void_p(), T.make_scheme(degree=3, reorder=0)
+        ok(L.cteno_mesh_upload(ctx, C.byref(d), C.byref(scheme), C.byref(h)), want)
+        if want == T.OK:
+            L.cteno_mesh_destroy(h)
+    """)
