@@ -188,6 +188,11 @@ const char *cteno_last_error(void);
    rounding in FP64 (the fused path sums a cell's faces inside its block
    first) and to the FP32 rounding of the fluxes in MIXED.  Synchronises. */
 cteno_status cteno_ctx_set_fused_stage(cteno_ctx *ctx, int32_t on);
+/* Cells per block of the fused stage in MIXED, for meshes uploaded after the
+   call: 0 (default) by the mesh's size, 64, or 256 (which meshes with
+   characteristic variables and meshes whose numbering scatters neighbours
+   do not take).  A stage's results are the same to the bit either way. */
+cteno_status cteno_ctx_set_stage_block(cteno_ctx *ctx, int32_t cells);
 /* Per-kernel timing with HIP events on the context stream (off by default).
    kernel: 0 = reconstruction (the fused stage kernel when it runs), 1 =
    flux + residual + RK update (the fused stage's second kernel), 2 =
@@ -210,6 +215,9 @@ cteno_status cteno_ctx_reset_stats(cteno_ctx *ctx);
 cteno_status cteno_mesh_upload(cteno_ctx *ctx, const cteno_mesh_desc *desc, const cteno_scheme *scheme,
                                cteno_mesh **out);
 cteno_status cteno_mesh_info_get(const cteno_mesh *mesh, cteno_mesh_info *info);
+/* Cells per block of the fused stage (64 or 256) in a precision of the mesh; 0:
+   its stages run the reconstruction and the flux kernel. */
+cteno_status cteno_mesh_stage_block(const cteno_mesh *mesh, int32_t precision, int32_t *cells);
 /* Host copies of the stencils: central [n_cells][M] cell ids (ascending),
    directional [n_cells][3][M_d] (face neighbour first, -1 padded) and the
    directional sizes [n_cells][3] (0 = inadmissible).  Any output may be NULL. */

@@ -49,6 +49,7 @@ struct cteno_ctx {
     void *user = nullptr;
     bool timing = false;
     bool fused_stage = true;    // degree <= 3: the fused stage kernels (else reconstruction + flux)
+    int stage_block = 0;        // their FP32 blocks' cells; 0: by size
     int64_t launches[3] = {0, 0, 0};
     double total_ms[3] = {0, 0, 0};
     struct Pending { int kernel; hipEvent_t a, b; };
@@ -295,6 +296,13 @@ extern "C" cteno_status cteno_ctx_set_fused_stage(cteno_ctx *c, int32_t on) {
     return CTENO_OK;
 }
 
+extern "C" cteno_status cteno_ctx_set_stage_block(cteno_ctx *c, int32_t cells) {
+    if (!c) return fail(CTENO_ERR_INVALID, "ctx is NULL");
+    if (cells != 0 && cells != 64 && cells != 256) return fail(CTENO_ERR_INVALID, "blocks have 64 or 256 cells");
+    c->stage_block = cells;
+    return CTENO_OK;
+}
+
 extern "C" cteno_status cteno_ctx_set_timing(cteno_ctx *c, int32_t on) {
     if (!c) return fail(CTENO_ERR_INVALID, "ctx is NULL");
     c->timing = on != 0;
@@ -395,8 +403,8 @@ static cteno_status upload_tables(DeviceMesh &dm, Alloc &&alloc_raw, hipStream_t
 template <class Alloc>
 static cteno_status upload_stage_lists(cteno_ctx *ctx, hipStream_t st, DeviceMesh &dm, bool f32, Alloc &&alloc_raw) {
     StageLists &l = dm.lists[f32];
-    l.bc = f32 && dm.vars != CTENO_VARS_CHARACTERISTIC && dm.N >= kWideCells && 2 * dm.row_bytes() <= kWideRowBytes
-               ? 256 : 64;
+    const bool wide = ctx->stage_block ? ctx->stage_block == 256 : dm.N >= kWideCells;
+    l.bc = f32 && wide && dm.vars != CTENO_VARS_CHARACTERISTIC && 2 * dm.row_bytes() <= kWideRowBytes ? 256 : 64;
     const int64_t ng = dm.groups(), nb = dm.stage_blocks(f32);
     DevBuf cnt(ctx, (size_t)(3 * ng + 1) * sizeof(int32_t));
     if (!cnt.p) return fail(CTENO_ERR_NOMEM, "device allocation failed");
@@ -605,6 +613,15 @@ extern "C" cteno_status cteno_mesh_upload(cteno_ctx *ctx, const cteno_mesh_desc 
     return CTENO_OK;
 }
 
+namespace {
+cteno_status check_precision(const cteno_mesh *m, int32_t precision, bool &f32) {
+    if (precision != CTENO_FP64 && precision != CTENO_MIXED) return fail(CTENO_ERR_INVALID, "precision must be FP64 or MIXED");
+    if (!(m->dm.precision & precision)) return fail(CTENO_ERR_INVALID, "mesh was uploaded without this precision");
+    f32 = precision == CTENO_MIXED;
+    return CTENO_OK;
+}
+}  // namespace
+
 extern "C" cteno_status cteno_mesh_info_get(const cteno_mesh *m, cteno_mesh_info *info) {
     if (!m || !info) return fail(CTENO_ERR_INVALID, "NULL argument");
     info->n_cells = m->host.N;
@@ -620,6 +637,14 @@ extern "C" cteno_status cteno_mesh_info_get(const cteno_mesh *m, cteno_mesh_info
     info->n_inadmissible = m->host.n_inadmissible;
     info->device_bytes = m->bytes;
     info->n_cross_cells = m->dm.n_cross256;
+    return CTENO_OK;
+}
+
+extern "C" cteno_status cteno_mesh_stage_block(const cteno_mesh *m, int32_t precision, int32_t *cells) {
+    if (!m || !cells) return fail(CTENO_ERR_INVALID, "NULL argument");
+    bool f32;
+    if (cteno_status rc = check_precision(m, precision, f32)) return rc;
+    *cells = m->dm.lists[f32].fused ? m->dm.lists[f32].bc : 0;
     return CTENO_OK;
 }
 
@@ -774,12 +799,6 @@ struct SolStatus {
 namespace {
 SolStatus *sol_status(const cteno_sol *s) { return s->status.as<SolStatus>(); }
 
-cteno_status check_precision(const cteno_mesh *m, int32_t precision, bool &f32) {
-    if (precision != CTENO_FP64 && precision != CTENO_MIXED) return fail(CTENO_ERR_INVALID, "precision must be FP64 or MIXED");
-    if (!(m->dm.precision & precision)) return fail(CTENO_ERR_INVALID, "mesh was uploaded without this precision");
-    f32 = precision == CTENO_MIXED;
-    return CTENO_OK;
-}
 }  // namespace
 
 extern "C" cteno_status cteno_sol_create(cteno_ctx *ctx, const cteno_mesh *m, const double *u0, double t0,

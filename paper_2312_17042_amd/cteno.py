@@ -97,10 +97,12 @@ _SIGS = {
     "cteno_last_error": [],
     "cteno_ctx_set_timing": [C.c_void_p, C.c_int32],
     "cteno_ctx_set_fused_stage": [C.c_void_p, C.c_int32],
+    "cteno_ctx_set_stage_block": [C.c_void_p, C.c_int32],
     "cteno_ctx_kernel_stats": [C.c_void_p, C.c_int32, C.POINTER(C.c_int64), C.POINTER(C.c_double)],
     "cteno_ctx_reset_stats": [C.c_void_p],
     "cteno_mesh_upload": [C.c_void_p, C.POINTER(MeshDesc), C.POINTER(Scheme), C.POINTER(C.c_void_p)],
     "cteno_mesh_info_get": [C.c_void_p, C.POINTER(MeshInfo)],
+    "cteno_mesh_stage_block": [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)],
     "cteno_mesh_stencils": [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p],
     "cteno_mesh_pinv": [C.c_void_p, C.c_void_p, C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p],
     "cteno_mesh_destroy": [C.c_void_p],
@@ -259,6 +261,10 @@ class Context:
         """degree <= 3 RK stages: fused kernels (default) or reconstruction + flux"""
         _check(lib().cteno_ctx_set_fused_stage(self.h, int(bool(on))))
 
+    def set_stage_block(self, cells: int):
+        """cells per block of the fused stage in MIXED for meshes uploaded from now on: 0 (by size), 64 or 256"""
+        _check(lib().cteno_ctx_set_stage_block(self.h, int(cells)))
+
     def kernel_stats(self, kernel: int):
         n = C.c_int64()
         ms = C.c_double()
@@ -321,6 +327,12 @@ class Mesh:
         # closed every live handle by then)
         if getattr(self, "h", None) and not _is_finalizing():
             self.close()
+
+    def stage_block(self, precision=MIXED) -> int:
+        """cells per block of the fused stage in this precision; 0: separate kernels"""
+        n = C.c_int32()
+        _check(lib().cteno_mesh_stage_block(self.h, precision, C.byref(n)))
+        return n.value
 
     def stencils(self):
         cen = np.empty((self.N, self.M), np.int32)
