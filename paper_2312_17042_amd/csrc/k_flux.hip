@@ -507,7 +507,7 @@ template <int R>
 __device__ __forceinline__ int32_t row_cell(const uint16_t *lslot, const int2 *desc, const int32_t *hlist,
                                             int64_t i, int j) {
     const int r = lslot[lslot_index<R>(i, j)];
-    return r < 64 ? (int32_t)((i & ~int64_t(63)) + r) : (hlist + (uint32_t)desc[i >> 6].x)[r - 64];
+    return r < 64 ? (int32_t)((i & ~int64_t(63)) + r) : hlist[desc[i >> 6].x + (r - 64)];
 }
 // RL: the degree, 0 for the slot table and for one variable above degree 3
 template <int RL>
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(256) void k_halo_lists(const int32_t *slot, int SP,
     __shared__ int key[kHaloSort], uniq[kHaloSort];
     const int n = group_halo(slot, SP, key, uniq);
     const int64_t i0 = (int64_t)blockIdx.x * 64;
-    for (int k = threadIdx.x; k < n; k += 256) (hlist + (uint32_t)desc[blockIdx.x].x)[k] = uniq[k];
+    for (int k = threadIdx.x; k < n; k += 256) hlist[desc[blockIdx.x].x + k] = uniq[k];
     for (int k = threadIdx.x; k < 64 * 4 * QuadDims<R>::SK; k += 256) {
         const int64_t i = i0 + (k & 63);
         const int j = k >> 6, m = j < SP ? slot[avix(i, j, SP, 4)] : (int)i;     // pads: the cell itself

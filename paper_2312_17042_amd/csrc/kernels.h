@@ -97,7 +97,7 @@ struct DeviceMesh {
     // (lslot_index): row < 64 a cell of the group, row - 64 a place in the
     // group's list of cells outside it
     uint16_t *lslot = nullptr;     // [Np][row_entries(r)]
-    int2 *desc = nullptr;          // [groups()] first place in hlist (32 bits unsigned), its length
+    int2 *desc = nullptr;          // [groups()] first place in hlist (negative before its middle), its length
     int32_t *hlist = nullptr;
     int max_halo = 0;              // the longest list
     uint8_t *flags = nullptr;      // [Np]

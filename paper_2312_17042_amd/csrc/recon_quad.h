@@ -234,10 +234,9 @@ struct GroupRows {
     // list reads its first entry, or the pad)
     __device__ __forceinline__ static int place(int t) { return NV == 4 ? t >> 2 : t; }
     __device__ __forceinline__ void list(const int32_t *hlist, int2 desc, int t) {
-        const int32_t *own = hlist + (uint32_t)desc.x;
         const int r = place(t);
 #pragma unroll
-        for (int k = 0; k < HS; ++k) hid[k] = own[r + k * RL < desc.y ? r + k * RL : 0];
+        for (int k = 0; k < HS; ++k) hid[k] = hlist[desc.x + (r + k * RL < desc.y ? r + k * RL : 0)];
     }
     __device__ __forceinline__ void averages(const double *U, int v) {
 #pragma unroll
@@ -251,7 +250,7 @@ struct GroupRows {
         for (int k = 0; k < HS; ++k)
             if (r0 + k * RL < desc.y) rows[(64 + r0 + k * RL) * NV + v] = hu[k];
         for (int r = r0 + HS * RL; r < desc.y; r += RL)
-            rows[(64 + r) * NV + v] = U[(int64_t)(hlist + (uint32_t)desc.x)[r] * NV + v];
+            rows[(64 + r) * NV + v] = U[(int64_t)hlist[desc.x + r] * NV + v];
     }
 };
 

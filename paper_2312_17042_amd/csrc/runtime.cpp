@@ -560,17 +560,24 @@ static cteno_status upload_device_mesh(cteno_ctx *ctx, hipStream_t st, HostMesh 
         HIP_TRY(hipStreamSynchronize(st));
         int64_t total = 0;
         for (int64_t g = 0; g < ng; ++g) {
-            desc[g] = make_int2((int)(uint32_t)total, hl[g]);
             total += hl[g];
             dm.max_halo = std::max(dm.max_halo, (int)hl[g]);
         }
         if (total > (int64_t)UINT32_MAX) return fail(CTENO_ERR_INVALID, "neighbour lists too long");
+        // places are 32 bits signed: those of very long lists count from the middle
+        const int64_t middle = total > INT32_MAX ? int64_t(1) << 31 : 0;
+        int64_t place = -middle;
+        for (int64_t g = 0; g < ng; ++g) {
+            desc[g] = make_int2((int)place, hl[g]);
+            place += hl[g];
+        }
         dm.desc = alloc_T(int2, (size_t)ng);
-        dm.hlist = alloc_T(int32_t, (size_t)total + 1);    // (a group without neighbours reads one entry)
+        int32_t *lists = alloc_T(int32_t, (size_t)total + 1);    // (a group without neighbours reads one entry)
         dm.lslot = alloc_T(uint16_t, Np * row_entries(hm.r));
-        if (!dm.desc || !dm.hlist || !dm.lslot) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+        if (!dm.desc || !lists || !dm.lslot) return fail(CTENO_ERR_NOMEM, "device allocation failed");
+        dm.hlist = lists + middle;
         HIP_TRY(h2d(dm.desc, desc, st));
-        HIP_TRY(launch_fill_u32((uint32_t *)dm.hlist + total, 0u, 1, st));
+        HIP_TRY(launch_fill_u32((uint32_t *)lists + total, 0u, 1, st));
         HIP_TRY(launch_halo_lists(dm, st));
         HIP_TRY(hipStreamSynchronize(st));
         dm.slot = nullptr;
