@@ -7,12 +7,12 @@
 namespace cteno {
 
 hipError_t launch_reconstruct(const DeviceMesh &m, bool fp32, const double *U, void *FV, uint8_t *delta, int dmode,
-                              const int *done, hipStream_t st, unsigned long long *fb_count) {
+                              const int *done, hipStream_t st, unsigned long long *fb_count, bool stage) {
     if (m.r >= 4)
         return fp32 ? reconstruct_hi<float>(m, U, FV, delta, dmode, done, st, fb_count)
                     : reconstruct_hi<double>(m, U, FV, delta, dmode, done, st, fb_count);
-    return fp32 ? reconstruct_lo<float>(m, U, FV, delta, dmode, done, st, fb_count)
-                : reconstruct_lo<double>(m, U, FV, delta, dmode, done, st, fb_count);
+    return fp32 ? reconstruct_lo<float>(m, U, FV, delta, dmode, done, st, fb_count, stage)
+                : reconstruct_lo<double>(m, U, FV, delta, dmode, done, st, fb_count, stage);
 }
 
 // Fluxes, residual (MODE 1) or RK stage (MODE 2) of cell i from all cells' face

@@ -26,15 +26,17 @@ __global__ __launch_bounds__(256) void k_reconstruct(const ReconArgs<real> a, co
 
 template <typename real, int R, int NV, int VARS>
 static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real> &a, const ReconPtrs<real> &p, real *FV,
-                               int dmode, unsigned grid, hipStream_t st) {
+                               int dmode, bool plain, unsigned grid, hipStream_t st) {
 #define CT_LAUNCH(SCH, GF, DM)                                                                                    \
     do {                                                                                                          \
-        if (m.stream_nontemporal(std::is_same<real, float>::value))                                               \
-            hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, true>), dim3(grid), dim3(256),      \
-                               m.row_bytes(), st, a, p, m.N, FV);                                                 \
-        else                                                                                                      \
-            hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, false>), dim3(grid), dim3(256),     \
-                               m.row_bytes(), st, a, p, m.N, FV);                                                 \
+        if constexpr (DM == 0)                                                                                    \
+            if (plain) {                                                                                          \
+                hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, false>), dim3(grid), dim3(256), \
+                                   m.row_bytes(), st, a, p, m.N, FV);                                             \
+                break;                                                                                            \
+            }                                                                                                     \
+        hipLaunchKernelGGL((k_reconstruct<real, R, NV, SCH, GF, DM, VARS, true>), dim3(grid), dim3(256),          \
+                           m.row_bytes(), st, a, p, m.N, FV);                                                     \
     } while (0)
 #define CT_DM(SCH, GF)                        \
     switch (dmode) {                          \
@@ -54,7 +56,7 @@ static void reconstruct_launch(const DeviceMesh &m, const ReconArgs<real> &a, co
 
 template <typename real, int R, int NV>
 static hipError_t reconstruct_t(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode,
-                                const int *done, hipStream_t st, unsigned long long *fb_count) {
+                                const int *done, hipStream_t st, unsigned long long *fb_count, bool stage) {
     if (m.E != QuadDims<R>::E || m.SP != QuadDims<R>::SP) return hipErrorInvalidValue;
     ReconArgs<real> a;
     fill_recon_constants<real>(m, a);
@@ -71,31 +73,32 @@ static hipError_t reconstruct_t(const DeviceMesh &m, const double *U, void *FV, 
     p.done = done;
     if (!p.P || !a.tab || !p.lslot || !p.desc || !p.hlist) return hipErrorInvalidValue;
     const unsigned grid = (unsigned)(m.Np / 64);
+    const bool plain = stage && !m.stream_nontemporal(std::is_same<real, float>::value);
     if (m.vars == CTENO_VARS_CHARACTERISTIC) {
         if constexpr (NV == 4) {
             if (!p.fr) return hipErrorInvalidValue;
-            reconstruct_launch<real, R, NV, 1>(m, a, p, (real *)FV, dmode, grid, st);
+            reconstruct_launch<real, R, NV, 1>(m, a, p, (real *)FV, dmode, plain, grid, st);
         } else {
             return hipErrorInvalidValue;
         }
     } else {
-        reconstruct_launch<real, R, NV, 0>(m, a, p, (real *)FV, dmode, grid, st);
+        reconstruct_launch<real, R, NV, 0>(m, a, p, (real *)FV, dmode, plain, grid, st);
     }
     return hipGetLastError();
 }
 
 template <typename real>
 hipError_t reconstruct_lo(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode,
-                          const int *done, hipStream_t st, unsigned long long *fb_count) {
+                          const int *done, hipStream_t st, unsigned long long *fb_count, bool stage) {
     if (m.nv == 4) {
         switch (m.r) {
-            case 2: return reconstruct_t<real, 2, 4>(m, U, FV, delta, dmode, done, st, fb_count);
-            case 3: return reconstruct_t<real, 3, 4>(m, U, FV, delta, dmode, done, st, fb_count);
+            case 2: return reconstruct_t<real, 2, 4>(m, U, FV, delta, dmode, done, st, fb_count, stage);
+            case 3: return reconstruct_t<real, 3, 4>(m, U, FV, delta, dmode, done, st, fb_count, stage);
         }
     } else {
         switch (m.r) {
-            case 2: return reconstruct_t<real, 2, 1>(m, U, FV, delta, dmode, done, st, fb_count);
-            case 3: return reconstruct_t<real, 3, 1>(m, U, FV, delta, dmode, done, st, fb_count);
+            case 2: return reconstruct_t<real, 2, 1>(m, U, FV, delta, dmode, done, st, fb_count, stage);
+            case 3: return reconstruct_t<real, 3, 1>(m, U, FV, delta, dmode, done, st, fb_count, stage);
         }
     }
     return hipErrorInvalidValue;

@@ -3,5 +3,5 @@
 
 namespace cteno {
 template hipError_t reconstruct_lo<double>(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode,
-                                  const int *done, hipStream_t st, unsigned long long *fb_count);
+                                  const int *done, hipStream_t st, unsigned long long *fb_count, bool stage);
 }  // namespace cteno

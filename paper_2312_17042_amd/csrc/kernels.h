@@ -71,14 +71,16 @@ constexpr int64_t kWideCells = 1200000;
 // characteristic variables spends more on the selection and the line lies higher:
 // 2M cells at 1.6, 2.4 and 3.0 65.5 / 67.2, 71.0 / 75.1, 112.1 / 104.1.
 constexpr double kFusedFaces = 1.5, kFusedFacesChar64 = 2.75;
-// Degree 2 and 3: what a stage reads and writes, of which the 256 MB memory-side
-// cache keeps a stream that fits, but not one that is loaded nontemporally.  20
-// steps, nontemporal / plain loads: one variable, degree 2, mixed 2677 / 2502 us at
-// 400k cells (200 MB), 3100 / 2924 at 500k (250 MB), 4191 / 4710 at 700k (350 MB);
-// degree 3 mixed 2967 / 2787 at 200k (204 MB), 4523 / 5048 at 353k (360 MB); FP64
-// 3845 / 3621 at 150k (264 MB), 4888 / 5270 at 200k.  Below, nontemporal streams
-// stay in it too and leave the L2s to the averages: one variable, degree 2, mixed
-// 1117 / 1183 at 100k (50 MB), 1395 / 1434 at 150k (75 MB).
+// Degree 2 and 3: what an RK stage reads and writes, of which the 256 MB
+// memory-side cache keeps a stream that fits for the next stage, but not one that
+// is loaded nontemporally.  20 steps, nontemporal / plain loads: one variable,
+// degree 2, mixed 2677 / 2502 us at 400k cells (200 MB), 3100 / 2924 at 500k (250
+// MB), 4191 / 4710 at 700k (350 MB); degree 3 mixed 2967 / 2787 at 200k (204 MB),
+// 4523 / 5048 at 353k (360 MB); FP64 3845 / 3621 at 150k (264 MB), 4888 / 5270 at
+// 200k.  Below, nontemporal streams stay in it too and leave the L2s to the
+// averages: one variable, degree 2, mixed 1117 / 1183 at 100k (50 MB), 1395 / 1434
+// at 150k (75 MB).  A single reconstruction finds its stream in memory, where
+// nontemporal loads are the better ones (residual of 81k cells in FP64 74 / 78 us).
 constexpr double kCachedStream[2] = {128e6, 268e6};
 constexpr size_t kWideRowBytes = 28 * 1024;
 
@@ -157,12 +159,13 @@ hipError_t reconstruct_lo(const DeviceMesh &m, const double *U, void *FV, uint8_
                           hipStream_t st, unsigned long long *fb_count);
 template <typename real>
 hipError_t reconstruct_hi(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode, const int *done,
-                          hipStream_t st, unsigned long long *fb_count);
+                          hipStream_t st, unsigned long long *fb_count, bool stage);
 
 // reconstruction; dmode: 0 none, 1 write delta, 2 forced delta
 // fb_count (may be null) counts the cells that take the positivity fallback
 hipError_t launch_reconstruct(const DeviceMesh &m, bool fp32, const double *U, void *FV, uint8_t *delta, int dmode,
-                              const int *done, hipStream_t st, unsigned long long *fb_count = nullptr);
+                              const int *done, hipStream_t st, unsigned long long *fb_count = nullptr,
+                              bool stage = false);
 
 // flux / residual / RK stage.  mode: 0 outward face fluxes, 1 residual, 2 RK stage
 struct FluxLaunch {

@@ -1070,7 +1070,9 @@ hipError_t issue_stage(cteno_ctx *ctx, cteno_sol *s, bool f32, int stage, const 
         if (e != hipSuccess) return e;
         return timed(ctx, 1, [&] { return launch_stage(dm, f32, fl, done, 1, st, &ss->fallbacks); });
     }
-    hipError_t e = timed(ctx, 0, [&] { return launch_reconstruct(dm, f32, in, fv, nullptr, 0, done, st, &ss->fallbacks); });
+    hipError_t e = timed(ctx, 0, [&] {
+        return launch_reconstruct(dm, f32, in, fv, nullptr, 0, done, st, &ss->fallbacks, true);
+    });
     if (e != hipSuccess) return e;
     return timed(ctx, 1, [&] { return launch_flux(dm, f32, fl, st); });
 }
