@@ -29,20 +29,21 @@ HBM_PEAK_GBS = 8000.0
 # Algorithmic bytes per cell-stage at r = 3 with four variables: what an
 # ideal fused stage must move, each value once (mixed / FP64):
 #   pseudo-inverses      162 central + 24 directional entries  744 / 1488
-#   central indices      18 x int32                               72 / 72
-#   directional indices  12 local indices (slot order here)       12 / 12
+#   stencil entries      18 row numbers of 16 bits (the first
+#                        12 are the directional stencils'), and
+#                        the group's list, some 96 cells for 64    42 / 42
 #   stage-input state    4 x FP64                                  32 / 32
 #   U^n                                                            32 / 32
 #   state write                                                    32 / 32
 #   cell area                                                       8 / 8
 #   face geometry        1.5 faces x (n_x, n_y, |A|)               18 / 36
-STAGE_BYTES = {"mixed": 950, "fp64": 1712}
+STAGE_BYTES = {"mixed": 908, "fp64": 1670}
 # the reconstruction kernel's share: pseudo-inverses, indices, stage input
-RECON_BYTES = {"mixed": 162 * 4 + 24 * 4 + 18 * 4 + 12 + 32, "fp64": 162 * 8 + 24 * 8 + 18 * 4 + 12 + 32}
+RECON_BYTES = {"mixed": 162 * 4 + 24 * 4 + 18 * 2 + 6 + 32, "fp64": 162 * 8 + 24 * 8 + 18 * 2 + 6 + 32}
 # the flux / residual / RK kernel's share: U^n, state write, area, geometry
 FLUX_BYTES = {k: STAGE_BYTES[k] - RECON_BYTES[k] for k in STAGE_BYTES}
 # a cross cell's share of the second fused-stage kernel: its state write
-# (k_stage reads its U^n, stage input and area)
+# (the first kernel reads its U^n, stage input and area)
 CROSS_UPDATE_BYTES = 32
 
 # HBM bytes per cell and launch measured with the FETCH_SIZE / WRITE_SIZE
@@ -108,15 +109,16 @@ def run_precision(T, ctx, mesh, sol, u0, prec, steps, warmup):
 
 def ho_recon_bytes(r, prec):
     """Algorithmic bytes per cell and launch of the reconstruction at degree
-    r >= 4: the useful pseudo-inverse entries (K x M central, K_d x M_d per
-    directional stencil), M slot indices, the flag byte, the cell's FP64
-    state and its 3 N_q x 4 face-point values."""
+    r >= 4: the useful pseudo-inverse entries (K x M central, K_d for each
+    cell of a directional stencil: M at most, since they lie in the central one
+    and hold a cell once), M slot indices, the flag byte, the cell's FP64 state
+    and its 3 N_q x 4 face-point values."""
     K = (r + 1) * (r + 2) // 2 - 1
     rd = (r + 1) // 2
     Kd = (rd + 1) * (rd + 2) // 2 - 1
     Md, M, Nq = 2 * Kd, 2 * K, (r + 2) // 2
     es = 4 if prec == "mixed" else 8
-    return (K * M + 3 * Kd * Md) * es + M * 4 + 1 + 32 + 3 * Nq * 4 * es
+    return (K * M + Kd * min(3 * Md, M)) * es + M * 4 + 1 + 32 + 3 * Nq * 4 * es
 
 
 def orders_bench(T, W, ctx, n=1000, steps=5, warmup=1):
@@ -538,12 +540,14 @@ def main():
     def gbs(nbytes, ms):
         return nbytes * N / (ms * 1e-3) / 1e9
 
-    # the fused stage: k_stage moves every cell's share but the state write
-    # of the cells k_stage_cross finishes (x_cross of them)
+    # the fused stage: the first kernel (k_stage_wide in blocks of 256 cells, else
+    # k_stage) moves every cell's share but the state write of the cells
+    # k_stage_cross finishes (x_cross of them in blocks of 256)
     def stage_split_bytes(prec):
         cross = x_cross * CROSS_UPDATE_BYTES
         return STAGE_BYTES[prec] - cross, cross
 
+    stage_kernel = "k_stage_wide" if m.stage_block(T.MIXED) == 256 else "k_stage"
     t0, t1 = kstats(mx)
     b0, b1 = stage_split_bytes("mixed")
     achieved = gbs(b0, t0)
@@ -573,9 +577,9 @@ def main():
         # algorithmic bytes; the whole stage (both kernels) on all of them
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-                     "kernel": "k_stage (FP32, fused reconstruction + in-block fluxes + RK)",
+                     "kernel": f"{stage_kernel} (FP32, fused reconstruction + in-block fluxes + RK)",
                      "bytes_per_cell": b0, "avg_launch_ms": t0,
-                     "stage": {"kernels": "k_stage + k_stage_cross (FP32)", "bytes_per_cell": STAGE_BYTES["mixed"],
+                     "stage": {"kernels": f"{stage_kernel} + k_stage_cross (FP32)", "bytes_per_cell": STAGE_BYTES["mixed"],
                                "avg_ms": t0 + t1, "achieved": stage_gbs, "frac": stage_gbs / HBM_PEAK_GBS},
                      "traffic_note": "HBM bytes per launch from FETCH_SIZE + WRITE_SIZE, scaled by the copy "
                                      "calibration; null unless taken on these kernel sources"},
@@ -612,7 +616,8 @@ def main():
                 "stage_GBs": gbs(STAGE_BYTES[name], rc + fl), "stage_frac": gbs(STAGE_BYTES[name], rc + fl) / HBM_PEAK_GBS,
                 "max_rel_diff_vs_fused": float(np.abs(r["u"] - res[name]["u"]).max() / np.abs(res[name]["u"]).max())}
         out["split_kernels"]["note"] = ("reconstruction and flux/RK as two kernels, face values through device "
-                                        "memory; reconstruct_frac on its 860 / 1604 B share")
+                                        "memory; reconstruct_frac on its "
+                                        f"{RECON_BYTES['mixed']} / {RECON_BYTES['fp64']} B share")
     # plain device copy of a known size: practical HBM ceiling, and the
     # calibration kernel for the hardware byte counters
     nbytes = 4 << 30

@@ -318,7 +318,8 @@ cteno_status cteno_rk_stage(cteno_ctx *ctx, const cteno_mesh *mesh, cteno_sol *s
    comes first, dt = cfl * min_i 2|V_i| / sum_f |A_f| s_if (s the normal
    signal speed |v.n| + c, or |a.n|), the last step clipped to land on
    t_final.  The time step is computed and applied on the device (no host
-   round trip per step); use_graph = 1 replays a captured HIP graph per step.
+   round trip per step); use_graph = 1 replays captured HIP graphs of four
+   steps, and of one for the rest of max_steps.
    steps_done (may be NULL) receives the number of steps taken by this call.
    Synchronises. */
 cteno_status cteno_solve(cteno_ctx *ctx, const cteno_mesh *mesh, cteno_sol *sol, int32_t precision, double t_final,

@@ -20,8 +20,10 @@ hipError_t launch_reconstruct(const DeviceMesh &m, bool fp32, const double *U, v
 // the CFL bound of the new state when requested, else +inf.  All lanes of a block
 // call it (live: the cell exists).  A lane per cell took its faces one after the
 // other, with 64 rows under each load: 9.5k cells of three Gauss points in FP64
-// 12.6 us, now 5.4; 215k cells 45.7, now 39.7 (165 MB).  What is left at large
-// sizes are the neighbours' face values, read from memory in rows of their own.
+// 12.6 us, now 5.4; 215k cells 45.7, now 39.7 (165 MB).  At 8M cells in mixed
+// precision 492, now 405 us; in FP64 the fourth lane's repeated face shows in an RK
+// stage (822, now 904; residual 765, 758; face fluxes 1183, 755).  What is left at
+// large sizes are the neighbours' face values, read from memory in rows of their own.
 template <typename real, int NV, int PHYS, int MODE, int NQ>
 __device__ __forceinline__ double flux_quad(const FluxArgs<real> a, const FluxPtrs<real> ptr, int64_t i, bool live) {
     const int q = threadIdx.x & 3, f = q < 2 ? q : 2, v = NV == 4 ? q : 0;

@@ -170,9 +170,9 @@ void k_stage(const ReconArgs<real> ra, const ReconPtrs<real> rp, const FluxArgs<
 // requested when the products have used this group's, so they are in flight
 // during the selection and the face values; the faces between the block's
 // groups stay on the chip, which leaves part 1 half the sides.  On 8M cells at
-// degree 3 this takes 1463 + 82 us, blocks of 64 cells 1455 + 273.  It moves 7.3
-// GB, 5 TB/s: a wave waits a third of its time for memory and a third for the
-// matrix and vector units' results.  Three waves per SIMD; at four the stream
+// degree 3 this takes 1463 + 82 us, blocks of 64 cells 1455 + 273.  It moves 7.6
+// GB, 5.1 TB/s; a wave waits 38 % of its cycles for memory, LDS and barriers and
+// 37 % for the matrix and vector units.  Three waves per SIMD; at four the stream
 // spills (1728 us).
 template <int R, int NV, int SCHEME, int GFORM, int PHYS>
 __global__ __launch_bounds__(256, 3)

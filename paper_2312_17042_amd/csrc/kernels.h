@@ -1,7 +1,8 @@
 // Kernel launchers of the CTENO/CTENOZ library, implemented in k_precompute.hip
 // (pseudo-inverses), k_recon_*.hip (reconstruction, per degree range and
-// arithmetic type) and k_flux.hip (fluxes, RK stages, step control, serving
-// batches, utilities); kernels_common.h holds the shared device code.
+// arithmetic type), k_stage_*.hip (fused stage of degree 2 and 3) and k_flux.hip
+// (fluxes, RK stages, step control, serving batches, mesh lists, utilities);
+// kernels_common.h and recon_quad.h hold the shared device code.
 //
 // HIP kernels (gfx950) of the CTENO/CTENOZ finite-volume hot path.
 //
@@ -10,24 +11,27 @@
 //                  least-squares matrix and the pseudo-inverse
 //                  P = R^-1 Q^T diag(|V'_m|), for the central stencil and
 //                  the three directional stencils; FP32 copies on request.
-//   k_reconstruct  per cell and stage: gather of neighbour averages, central
-//                  and directional products P d, p_1 (eq. e17), smoothness
-//                  indicators, CTENO (Algorithm 1) / CTENOZ (Algorithm 2)
-//                  selection, final polynomial at the face Gauss points.
-//   k_flux         per cell and stage: HLLC (sec. 2.6) or upwind flux at the
-//                  Gauss points of its three faces, the residual of the
+//   k_reconstruct  per cell and stage, a quad of lanes per cell: neighbour
+//                  averages, central and directional products P d on the
+//                  matrix cores, p_1 (eq. e17), smoothness indicators, CTENO
+//                  (Algorithm 1) / CTENOZ (Algorithm 2) selection, final
+//                  polynomial at the face Gauss points.
+//   k_flux         per cell and stage, a lane per face: HLLC (sec. 2.6) or
+//                  upwind flux at the Gauss points, the residual of the
 //                  semi-discrete form after eq. e1, and the SSP-RK3 stage;
 //                  each interior face flux is evaluated identically by both
 //                  of its cells (same operands, same order) so the update is
 //                  conservative to FP64 round-off without atomics.
-//   k_control      per RK step, one thread: time step from the reduced CFL
+//   k_stage, k_stage_wide, k_stage_cross   degree 2 and 3: both in one kernel,
+//                  face values in LDS, and the faces between its blocks.
+//   k_control      per RK step, one block: time step from the reduced CFL
 //                  bound, clipping to t_final, termination.
 //
-// Memory layout: per-cell static data (stencil slots, pseudo-inverses,
-// face geometry) in 64-cell tiles, entry-major inside a tile, so a wave
-// streams each entry as one contiguous 256/512-byte segment; the state and
-// the face-point values are cell-major (array of structures) so a gather of
-// one neighbour touches one cache line.
+// Memory layout: the pseudo-inverse streams in tiles of 16 cells in the order
+// that the matrix instructions read them (quad_index, ho_index), other static
+// per-cell data in 64-cell tiles; the state and the face-point values are
+// cell-major (array of structures) so a gather of one neighbour touches one
+// cache line.
 #pragma once
 
 #include <algorithm>
@@ -156,13 +160,14 @@ hipError_t launch_precompute(const DeviceMesh &m, const PrecomputeInputs &in, hi
 // k_recon_f32/f64.hip and k_recon_ho_f32/f64.hip
 template <typename real>
 hipError_t reconstruct_lo(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode, const int *done,
-                          hipStream_t st, unsigned long long *fb_count);
+                          hipStream_t st, unsigned long long *fb_count, bool stage);
 template <typename real>
 hipError_t reconstruct_hi(const DeviceMesh &m, const double *U, void *FV, uint8_t *delta, int dmode, const int *done,
-                          hipStream_t st, unsigned long long *fb_count, bool stage);
+                          hipStream_t st, unsigned long long *fb_count);
 
 // reconstruction; dmode: 0 none, 1 write delta, 2 forced delta
-// fb_count (may be null) counts the cells that take the positivity fallback
+// fb_count (may be null) counts the cells that take the positivity fallback;
+// stage: of an RK stage, one of several on this mesh in a row (dmode 0)
 hipError_t launch_reconstruct(const DeviceMesh &m, bool fp32, const double *U, void *FV, uint8_t *delta, int dmode,
                               const int *done, hipStream_t st, unsigned long long *fb_count = nullptr,
                               bool stage = false);

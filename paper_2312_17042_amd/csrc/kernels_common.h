@@ -1,8 +1,7 @@
 // Device helpers shared by the kernel translation units of the CTENO/CTENOZ
-// library: vector loads, face records, the XCD-aware block order, the
-// reconstruction body of degree 2 and 3 (used by the single-mesh and the
-// batched serving kernels), TENO-type selections, CWENO weights, HLLC and
-// the flux / residual / RK body.
+// library: vector loads, face records, the XCD-aware block order, TENO-type
+// selections, CWENO weights, HLLC and wall fluxes, boundary states, a face's
+// flux term, RK stage values and the CFL bound.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -27,7 +26,6 @@ template <> struct Vec<double> { using T = double2; static constexpr int W = 2; 
 
 __device__ __forceinline__ float comp(const float4 &v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 __device__ __forceinline__ double comp(const double2 &v, int c) { return c == 0 ? v.x : v.y; }
-__device__ __forceinline__ int comp(const int4 &v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 
 // Division, reciprocal and square root in the working precision.  FP64 keeps
 // the IEEE operations (the fluxes multiply by an IEEE reciprocal where
@@ -307,11 +305,12 @@ struct HoDims {
 // ===========================================================================
 
 // HLLC with Roe-averaged signal speeds (sec. 2.7), in the face-normal frame
-// (u normal, w tangential velocity); F returned in the global frame.  The sum
-// H_l + H_r D of the Roe average is contracted by hand: ALT 0 leaves H_l
-// unrounded in it, 1 H_r D, 2 decides by `alt`; 3 is 0 with the other product of
-// u_r unrounded (FP32 marches repeat their results bit for bit only if each face
-// keeps its own).
+// (u normal, w tangential velocity); F returned in the global frame.  In FP32
+// the sum H_l + H_r D of the Roe average is contracted by hand: ALT 0 leaves H_l
+// unrounded in it, 2 H_r D where `alt` is set and else H_l; 3 is 0 with the other
+// product of u_r unrounded.  An FP32 face value of the state rounds at 1e-8 of
+// it, so a march repeats its results bit for bit, whatever the blocks are, only
+// if each face keeps its own contraction.
 template <typename real, int ALT = -1>
 __device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, real nx, real ny, real *F,
                                      bool alt = false) {
@@ -339,7 +338,7 @@ __device__ __forceinline__ bool hllc(real g, const real *UL, const real *UR, rea
         Hs = Hl + Hr * D;
     } else {
         const real h0 = __builtin_fmaf(irl, El + pl, Hr * D), h1 = __builtin_fmaf(Hr, D, Hl);
-        Hs = ALT == 2 ? (alt ? h1 : h0) : ALT == 1 ? h1 : h0;
+        Hs = ALT == 2 && alt ? h1 : h0;
     }
     const real Ht = Hs * iD;
     const real ct = fsqrt((g - 1) * (Ht - h * (ut * ut + wt * wt)));

@@ -220,8 +220,7 @@ __device__ __forceinline__ int finish_field(const ReconArgs<real> a, real (&c1)[
 // The averages that the stencils of a group of 64 cells reach -- its own
 // cells, then its listed neighbours -- go to LDS, one row of NV per cell.  A
 // stencil entry is a row number: gathers of single averages from global
-// memory took two of three slots of the address unit and kept it busy 88 % of
-// the stage kernel's time.
+// memory took two of three slots of the address unit.
 template <int NV>
 struct GroupRows {
     static constexpr int RL = 256 / NV;   // rows that the group's threads write at once
