@@ -49,12 +49,12 @@ CROSS_UPDATE_BYTES = 32
 # HBM bytes per cell and launch measured with the FETCH_SIZE / WRITE_SIZE
 # counters (scaled by the copy-kernel calibration), valid only for the
 # kernel sources they were taken on
-MEASURED_TRAFFIC = {"kernels_sha256_prefix": "002632cd235042d6",
+MEASURED_TRAFFIC = {"kernels_sha256_prefix": "202f13642d596e14",
                     "source": "profiles/stage_vortex8M_hbm_counters.md",
-                    "bytes_per_cell": {"k_stage_f32": 994.5, "k_stage_cross_f32": 90.7,
-                                       "k_stage_f64": 1812.3, "k_stage_cross_f64": 108.9,
-                                       "k_reconstruct_f32": 968.2, "k_flux_f32": 291.6,
-                                       "k_reconstruct_f64": 1811.3, "k_flux_f64": 554.5}}
+                    "bytes_per_cell": {"k_stage_wide_f32": 946.9, "k_stage_cross_f32": 69.7,
+                                       "k_stage_f64": 1760.5, "k_stage_cross_f64": 167.3,
+                                       "k_reconstruct_f32": 929.8, "k_flux_f32": 239.4,
+                                       "k_reconstruct_f64": 1782.9, "k_flux_f64": 384.1}}
 
 
 KERNEL_SOURCES = ("kernels_common.h", "recon_quad.h", "k_recon.inl", "k_recon_ho.inl", "k_stage.inl",
@@ -554,7 +554,8 @@ def main():
     stage_gbs = gbs(STAGE_BYTES["mixed"], t0 + t1)
     fresh = kernels_hash() == MEASURED_TRAFFIC["kernels_sha256_prefix"]
     measured = MEASURED_TRAFFIC["bytes_per_cell"] if fresh else None
-    traffic = measured["k_stage_f32"] * N if fresh else None
+    per_cell = measured.get(f"{stage_kernel}_f32") if fresh else None
+    traffic = per_cell * N if per_cell else None
     out = {
         "metric": "cell-stage updates/s (mixed FP32 vs FP64) at stated error; serving p50/p99",
         "value": mx["value"],
